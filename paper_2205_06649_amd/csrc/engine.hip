@@ -916,14 +916,14 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
     c->tz_alpha = P.model.tz_alpha;
     // column-walk kernels (q = 2, p <= 8): each box in column blocks of
     // 64 - 2p outputs and row strips (a strip reloads the four rows around
-    // it): at least 32 rows for the adjoint, with at most one wave per
-    // 256-cell tile of the box (each wave owns one J slot of the box), and
-    // at least 16 for the forward (more waves in flight)
+    // it), with at most one wave per 256-cell tile of the box (each wave of
+    // the adjoint owns one J slot of the box)
     if (c->tz_q == 2 && c->tz_p <= 8) {
       const int cw = 64 - 2 * c->tz_p;
       // waves of every box with strips of at least rmin rows; false when some
       // box has more column blocks than tiles
       auto build_list = [&](int rmin, std::vector<TzWork>& wl, std::vector<int>& wb) {
+        wl.clear();
         wb.assign(c->subs.size() + 1, 0);
         for (size_t s = 0; s < c->subs.size(); ++s) {
           const SubDev& S = c->subs[s];
@@ -953,9 +953,43 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
         wb.back() = int(wl.size());
         return !wl.empty();
       };
-      std::vector<TzWork> wl, fl;
-      std::vector<int> wb, fb;
-      if (build_list(32, wl, wb) && build_list(16, fl, fb)) {
+      // Strip lengths.  A wave walks its rows one after another (about 0.5
+      // us a row of the adjoint), so that a launch takes rounds x (rows + 4)
+      // steps, rounds the waves over those the chip holds at once (the
+      // adjoint's registers: 4 per SIMD in FP32, 2 in FP64).  Adjoint: 32
+      // rows where those fill the chip (16 rows: 5 % slower in FP64 on 4
+      // whole-sphere boxes of 1024 x 2048), else the length of fewest steps
+      // (64 boxes of 72 x 136 cells, 576 waves of 32 rows: FP64 adjoint
+      // sweep 2.25 -> 1.08 ms with 8 rows, FP32 1.97 -> 0.90 ms with 6; 4
+      // boxes of 512 x 1024: FP32 2.62 -> 1.68 ms, FP64 3.2 -> 2.8 ms).
+      // Forward: 16 rows, 8 where those leave room on the chip (FP64 boxes
+      // above 0.76 -> 0.57 ms, 512 x 1024 FP32 0.86 -> 0.65 ms, with 4 rows
+      // 0.71 ms), 4 on problems that 8 rows leave nearly empty (4 boxes of
+      // 28 x 52: 0.27 -> 0.19 ms).
+      int cus = 0;
+      chk(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device), "attribute");
+      const int simds = 4 * cus;
+      const int held = simds * (c->prec == DD4DVAR_FP64 ? 2 : 4);
+      std::vector<TzWork> wl, fl, tl;
+      std::vector<int> wb, fb, tb;
+      bool col = build_list(32, wl, wb) && build_list(16, fl, fb);
+      if (col && int(wl.size()) < held) {
+        auto steps = [&](const std::vector<TzWork>& l) {
+          int rows = 0;
+          for (const TzWork& w : l) rows = std::max(rows, w.r1 - w.r0);
+          return ((int(l.size()) + held - 1) / held) * (rows + 4);
+        };
+        for (int rmin : {16, 8, 4})
+          if (build_list(rmin, tl, tb) && steps(tl) <= steps(wl)) {
+            wl.swap(tl);
+            wb.swap(tb);
+          }
+      }
+      if (col && int(fl.size()) < held) {
+        col = build_list(8, fl, fb);
+        if (col && int(fl.size()) < simds / 4) col = build_list(4, fl, fb);
+      }
+      if (col) {
         std::vector<int> otp(c->maxlev + 1, 0);
         std::vector<int32_t> otl;
         for (int n = 0; n < c->maxlev; ++n) {
