@@ -256,7 +256,7 @@ dd4dvar_status dd4dvar_adjoint_integrate(dd4dvar_ctx* ctx, int32_t scope,
  * dZ = M' dx for every subdomain from the packed FP64 control perturbation
  * dx_dev; the frozen halo ring is not perturbed.  dtraj_dev (nullable)
  * receives the packed FP64 perturbation trajectories (every level, h as is).
- * Step kernels in every execution mode.  E_INVALID with checkpoints on,
+ * E_INVALID with checkpoints on,
  * E_STATE if no forward ran.  Asynchronous. */
 dd4dvar_status dd4dvar_tangent_linear(dd4dvar_ctx* ctx, const double* dx_dev,
                                       double* dtraj_dev, void* stream);
@@ -290,7 +290,11 @@ dd4dvar_status dd4dvar_gather(dd4dvar_ctx* ctx, int32_t level, double* out_dev,
 
 /* Selects how local_cost_grad, forward_integrate (scope 1) and
  * adjoint_integrate launch their kernels:
- *   0 = one launch per time step over all subdomains (default);
+ *   0 = all subdomains in every launch (default): step kernels, one launch
+ *       per time step; in an FP64 context of the plain scheme with every
+ *       level stored, where they are faster, block sweeps of the same
+ *       results that take several steps, up to the whole window, per launch
+ *       (get_timing counts the launches);
  *   1 = one launch per subdomain per step (the plain baseline);
  *   2 = persistent sweeps: one workgroup per subdomain holds the current
  *       level in LDS and the level before it in registers, one launch per

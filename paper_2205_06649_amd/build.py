@@ -28,6 +28,7 @@ HIP_UNITS = [
                                   "-ffp-contract=off"]),
     ("tlm.hip", "tlm_f32.o", ["-DDD4DVAR_TLM_T=float"]),
     ("tlm.hip", "tlm_f64.o", ["-DDD4DVAR_TLM_T=double", "-ffp-contract=off"]),
+    ("blk.hip", "blk.o", ["-ffp-contract=off"]),
     ("tz.hip", "tz_f32.o", ["-DDD4DVAR_TZ_T=float"]),
     ("tz.hip", "tz_f64.o", ["-DDD4DVAR_TZ_T=double", "-ffp-contract=off"]),
     ("tzbox.hip", "tzbox.o", []),

@@ -1,0 +1,921 @@
+// Sweeps over several levels per launch (FP64 state): the step kernels'
+// arithmetic, cell by cell and bit for bit, on blocks of a box that keep
+// their levels on chip.
+//
+// A block is a run of whole 256-cell tiles of one box.  One workgroup takes
+// it through several levels in one launch: the current level (state,
+// perturbation, or lambda^{n+1}) sits in an LDS frame over the block's rows,
+// one column wider on either side and one row above and below, which carries
+// the frozen ring of the level (zeros for the perturbation and the adjoint)
+// or, for a box spanning the circle, copies of the box's own cells across the
+// seam or the pole; the level before it (the leapfrog base, lambda^{n+2}) sits
+// in registers, one value per thread and pass, and the two are swapped after
+// each level.  A block that is a whole box runs all its levels in one launch.
+// A box too large for one frame, or worth spreading over idle compute units,
+// is cut into blocks that compute, besides their own cells, e rows above and
+// below them at the level e levels before the launch's last one, so that no
+// block waits for another: neighbours compute those cells too, from the same
+// inputs by the same expressions.
+//
+// Cells map to threads in box order, 64 consecutive cells (an aligned chunk
+// of a tile) to a wave, so that a tile's share of J is the sum the step
+// kernel takes: a shuffle tree per chunk, then the chunks in order, level by
+// level.
+//
+// What bounds it: the step kernels launch once per level and move 72 B
+// (forward) and 111 B (adjoint) per cell and level; here a level is written
+// once (forward) or read once (adjoint), plus the launch's two levels in and
+// out.  Small blocks are bound by the vector unit (an adjoint pass of 64 cells
+// is about 340 instructions, 140 of them FP64: 1800 cycles of a SIMD; a
+// level costs 1.1 us forward and 2.8 us adjoint for 612 cells), large ones
+// by memory.  Step kernels -> blocks, per evaluation: 8 boxes of 18 x 36
+// cells, 13 levels 113 -> 80 us; 64 boxes of 40 x 72, 34 levels 518 -> 335
+// us; 1024 boxes of 72 x 136, 34 levels 16.6 -> 8.0 ms (forward 4.9 -> 2.4
+// ms, 3.3 TB/s of its 7.9 GB; adjoint 11.7 -> 5.6 ms).  Loads of the adjoint's
+// state one pass ahead, or the next level's lines touched early, gained
+// nothing (the waves hide them); 512 threads of twice the passes, with
+// registers to spare, were 25 % slower than 1024, which leave 128 registers:
+// hence the values pinned to their pass below.
+#include <algorithm>
+#include <type_traits>
+#include <vector>
+
+#include "kernels.h"
+#include "launch.h"
+#include "stencil.h"
+
+namespace dd4dvar {
+
+using namespace stencil;
+
+namespace {
+constexpr int kRowTab = 8;                 // doubles per row of the row table
+constexpr int kBorderMax = 1024;           // border items of a block
+constexpr int border_items(int threads) { return (kBorderMax + threads - 1) / threads; }
+
+// cells of the block [out0, out1) grown by e rows within the box
+struct Range {
+  int lo, hi;
+};
+__device__ __forceinline__ Range grown(const BlkWork& w, int e, int nx, int ncell) {
+  return {max(0, w.out0 - e * nx), min(ncell, w.out1 + e * nx)};
+}
+
+// a block's frame: rows rb - 1 .. re + 1 of the box, columns -1 .. nx
+struct Frame {
+  int rb, re, fw;
+  __device__ __forceinline__ int pos(int r, int c) const { return ((r - rb + 1) * fw + c + 1) * 3; }
+  __device__ __forceinline__ int size() const { return (re - rb + 3) * fw * 3; }
+  __device__ __forceinline__ int rows() const { return re - rb + 1; }
+};
+
+// the state of level n of a box (every level is stored: level n at slot n)
+__device__ __forceinline__ double* state(const Dom<double>& D, const SubDev& S, int n) {
+  return D.traj + S.zoff + int64_t(n) * 3 * S.ncell;
+}
+__device__ __forceinline__ V3<double> get(const double* f, int p) { return {f[p], f[p + 1], f[p + 2]}; }
+__device__ __forceinline__ void put(double* f, int p, const V3<double>& v) {
+  f[p] = v.h;
+  f[p + 1] = v.u;
+  f[p + 2] = v.v;
+}
+
+// a cell's value into the frame; in a box spanning the circle also into the
+// frame positions that wrap onto it (across a pole with u, v times sg)
+__device__ __forceinline__ void put_cell(double* f, const Frame& F, const SubDev& S, int half, int r,
+                                         int c, const V3<double>& v, double sg) {
+  put(f, F.pos(r, c), v);
+  if (S.span) {
+    if (c == 0) put(f, F.pos(r, S.nx), v);
+    if (c == S.nx - 1) put(f, F.pos(r, -1), v);
+    const int cc = c >= half ? c - half : c + half;
+    const V3<double> w = {v.h, sg * v.u, sg * v.v};
+    if (r == 0 && S.pole_s) put(f, F.pos(-1, cc), w);
+    if (r == S.ny - 1 && S.pole_n) put(f, F.pos(S.ny, cc), w);
+  }
+}
+
+// rows of the frame: forward table {a1, a2, a3, cf, ct, cN, cS}, adjoint
+// table {a1, a2, a3n, a3s, cf, ct, c} (a3 of the rows whose increments read
+// the row from the north and the south; a row at the box's edge takes its
+// own, where the reader's adjoint is zero or lies across a pole)
+template <int NT, bool ADJ>
+__device__ __forceinline__ void fill_rows(double* tab, const Dom<double>& D, const SubDev& S,
+                                          const Frame& F) {
+  for (int i = threadIdx.x; i < F.rows(); i += NT) {
+    const int r = F.rb + i, j = S.row0 + r;
+    const RowCoef<double> rc = D.rows[j];
+    double* q = tab + kRowTab * i;
+    q[0] = rc.a1;
+    q[1] = rc.a2;
+    if (ADJ) {
+      q[2] = D.rows[r + 1 < S.ny ? j + 1 : j].a3;
+      q[3] = D.rows[r > 0 ? j - 1 : j].a3;
+      q[4] = rc.cf;
+      q[5] = rc.ct;
+      q[6] = rc.c;
+    } else {
+      q[2] = rc.a3;
+      q[3] = D.cosx[j + 2];
+      q[4] = rc.cf;
+      q[5] = rc.ct;
+      q[6] = D.cosx[j];
+    }
+  }
+}
+
+// border items of a block: the west and the east column of its rows, then
+// the rows beyond the box's own first and last (positions that wrap inside
+// the box are not items)
+struct Border {
+  int cols, south, north;                  // items of each kind; cols per side
+  __device__ __forceinline__ Border(const SubDev& S, const Frame& F)
+      : cols(S.span ? 0 : F.rows()),
+        south(F.rb == 0 && !S.pole_s ? S.nx : 0),
+        north(F.re == S.ny - 1 && !S.pole_n ? S.nx : 0) {}
+  __device__ __forceinline__ int count() const { return 2 * cols + south + north; }
+  // first item of each kind
+  __device__ __forceinline__ int east0() const { return cols; }
+  __device__ __forceinline__ int south0() const { return 2 * cols; }
+  __device__ __forceinline__ int north0() const { return 2 * cols + south; }
+  // frame position and ring index of item i < count()
+  __device__ __forceinline__ void item(int i, const SubDev& S, const Frame& F, int* pos, int* k) const {
+    if (i < 2 * cols) {
+      const bool east = i >= cols;
+      const int r = F.rb + (east ? i - cols : i);
+      *pos = F.pos(r, east ? S.nx : -1);
+      *k = 2 * S.nx + (east ? S.ny : 0) + r;
+    } else if (i < north0()) {
+      *pos = F.pos(-1, i - south0());
+      *k = i - south0();
+    } else {
+      *pos = F.pos(S.ny, i - north0());
+      *k = S.nx + i - north0();
+    }
+  }
+};
+
+// A thread's cell in one word: frame row (11 bits), column (11), coverage (8).
+__device__ __forceinline__ int cell_word(int row, int c, int cover) { return row << 19 | c << 8 | cover; }
+__device__ __forceinline__ int cell_row(int w) { return w >> 19; }
+__device__ __forceinline__ int cell_col(int w) { return (w >> 8) & 0x7ff; }
+__device__ __forceinline__ int cell_cover(int w) { return w & 0xff; }
+
+// keeps what is computed from v inside the pass (left alone, the compiler
+// computes every pass's addresses ahead of the level loop and spills them)
+__device__ __forceinline__ int here(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// The stored state of level n at a cell and its neighbours, from the box's
+// level Z (uniform) by 32-bit offsets.  A neighbour on the frozen ring reads
+// the cell itself here (any address in the box) and takes its ring value from
+// the staged items in `fix`, once the loads are back.
+template <bool SPAN>
+struct State5 {
+  V3<double> C, E, W, N, S;
+  double sn, ss;
+  bool ringE, ringW, ringN, ringS;
+  static __device__ __forceinline__ V3<double> at(const double* Z, int64_t plane, uint32_t off) {
+    const char* z = reinterpret_cast<const char*>(Z);
+    const int64_t f = plane * int64_t(sizeof(double));
+    return {*reinterpret_cast<const double*>(z + off), *reinterpret_cast<const double*>(z + f + off),
+            *reinterpret_cast<const double*>(z + 2 * f + off)};
+  }
+  __device__ __forceinline__ void load(const double* Z, int64_t plane, const SubDev& B, int half,
+                                       int m, int r, int c) {
+    const bool e_in = c + 1 < B.nx, w_in = c > 0, n_in = r + 1 < B.ny, s_in = r > 0;
+    int de = e_in ? 1 : 0, dw = w_in ? -1 : 0, dn = n_in ? B.nx : 0, ds = s_in ? -B.nx : 0;
+    ringE = !e_in;
+    ringW = !w_in;
+    ringN = !n_in;
+    ringS = !s_in;
+    sn = ss = 1.0;
+    if (SPAN && B.span) {                    // uniform
+      const int across = c + half >= B.nx ? half - B.nx : half;
+      de = e_in ? 1 : 1 - B.nx;
+      dw = w_in ? -1 : B.nx - 1;
+      ringE = ringW = false;
+      if (B.pole_n) {
+        dn = n_in ? B.nx : across;
+        sn = n_in ? 1.0 : -1.0;
+        ringN = false;
+      }
+      if (B.pole_s) {
+        ds = s_in ? -B.nx : across;
+        ss = s_in ? 1.0 : -1.0;
+        ringS = false;
+      }
+    }
+    C = at(Z, plane, uint32_t(m) * 8u);
+    E = at(Z, plane, uint32_t(m + de) * 8u);
+    W = at(Z, plane, uint32_t(m + dw) * 8u);
+    N = at(Z, plane, uint32_t(m + dn) * 8u);
+    S = at(Z, plane, uint32_t(m + ds) * 8u);
+  }
+  // ring: the staged items of the level; row: the cell's row in the frame.
+  // At most one of the east and west neighbours is on the ring (a box has two
+  // columns at least), so one read without a branch serves both; the rows
+  // above and below the box concern few waves.
+  __device__ __forceinline__ void fix(const double* ring, const Border& b, int row, int c) {
+    if (b.cols > 0) {                        // uniform
+      const V3<double> r = get(ring, 3 * (ringE ? b.cols + row : row));
+      E = {ringE ? r.h : E.h, ringE ? r.u : E.u, ringE ? r.v : E.v};
+      W = {ringW ? r.h : W.h, ringW ? r.u : W.u, ringW ? r.v : W.v};
+    }
+    if (__any(ringN)) {
+      if (ringN) N = get(ring, 3 * (b.north0() + c));
+    }
+    if (__any(ringS)) {
+      if (ringS) S = get(ring, 3 * (b.south0() + c));
+    }
+    if (SPAN) {
+      N.u *= sn;
+      N.v *= sn;
+      S.u *= ss;
+      S.v *= ss;
+    }
+  }
+};
+}  // namespace
+
+// Levels n0 + 1 .. n0 + steps of the forward sweep from levels n0 and n0 - 1
+// (n0 = 0: from the packed FP64 controls x, level 0 written as well).
+// traj_out (nullable): the packed FP64 trajectory, written beside each level.
+template <int NT, int K>
+__global__ __launch_bounds__(NT) void k_fwd_blk(Dom<double> D, const BlkWork* __restrict__ work,
+                                                int n0, int steps, const double* __restrict__ x,
+                                                double* __restrict__ traj_out) {
+  constexpr int NI = border_items(NT);
+  extern __shared__ double lds[];
+  const BlkWork w = work[blockIdx.x];
+  if (D.active && !D.active[w.box]) return;
+  const SubDev S = D.subs[w.box];
+  const int L = S.nlev - 1;
+  if (n0 > L || (n0 == L && n0 > 0)) return;
+  steps = min(steps, L - n0);
+  const int t = threadIdx.x, nx = S.nx, ncell = S.ncell;
+  const int64_t plane = ncell;
+  const Range in = grown(w, steps, nx, ncell);
+  const Range first = grown(w, max(steps - 1, 0), nx, ncell);
+  const Frame F = {in.lo / nx, (in.hi - 1) / nx, nx + 2};
+  double* fr = lds;
+  double* tab = lds + F.size();
+  fill_rows<NT, false>(tab, D, S, F);
+  const double h0 = D.h0, st = D.st, stg = D.stg;
+
+  // level n0 into the frame
+  for (int m = in.lo + t; m < in.hi; m += NT) {
+    const int r = m / nx, c = m - r * nx;
+    V3<double> z;
+    if (n0 == 0) {
+      const double* xs = x + S.ctrl_off + m;
+      z = {xs[0] - h0, xs[plane], xs[2 * plane]};
+      if (m >= w.out0 && m < w.out1) {
+        double* o = state(D, S, 0) + m;
+        o[0] = z.h;
+        o[plane] = z.u;
+        o[2 * plane] = z.v;
+        if (traj_out) {
+          double* q = traj_out + S.traj_off + m;
+          q[0] = z.h + h0;
+          q[plane] = z.u;
+          q[2 * plane] = z.v;
+        }
+      }
+    } else {
+      z = ld_box(state(D, S, n0), plane, m, 1.0);
+    }
+    put_cell(fr, F, S, D.half, r, c, z, -1.0);
+  }
+  if (steps <= 0) return;                   // a one-level box: level 0 only
+  const Border B(S, F);
+  int bpos[NI], bk[NI];
+  bool bon[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    bon[i] = t + i * NT < B.count();
+    B.item(t + i * NT, S, F, &bpos[i], &bk[i]);
+  }
+  // (a level's ring values are loaded one level ahead)
+  auto ring_at = [&](int n, int b) {
+    return ld_ring(D.ring + S.ring_off + int64_t(n) * 3 * S.nring, S.nring, bk[b]);
+  };
+#pragma unroll
+  for (int b = 0; b < NI; ++b)
+    if (bon[b]) put(fr, bpos[b], ring_at(n0, b));
+  __syncthreads();
+
+  // the cells of this thread: chunk by chunk from the first computed one
+  const int cb = (first.lo & ~63) + t;
+  V3<double> prev[K];
+  int rc[K];
+#pragma unroll
+  for (int p = 0; p < K; ++p) {
+    const int m = cb + p * NT;
+    const int r = m / nx, c = m - r * nx;
+    rc[p] = cell_word(r - F.rb, c, 0);
+    prev[p] = {0.0, 0.0, 0.0};
+    if (m >= first.lo && m < first.hi)
+      prev[p] = n0 > 0 ? ld_box(state(D, S, n0 - 1), plane, m, 1.0) : get(fr, F.pos(r, c));
+  }
+
+  for (int i = 0; i < steps; ++i) {
+    const int n = n0 + i;
+    const Range g = grown(w, steps - 1 - i, nx, ncell);
+    const bool more = i + 1 < steps;
+    V3<double> ring[NI];
+#pragma unroll
+    for (int b = 0; b < NI; ++b)
+      if (more && bon[b]) ring[b] = ring_at(n + 1, b);
+    double* out = state(D, S, n + 1);
+    const double wgt = n == 0 ? 0.5 : 1.0;
+#pragma unroll
+    for (int p = 0; p < K; ++p) {
+      const int m = here(cb) + p * NT;
+      if (m < g.lo || m >= g.hi) continue;
+      const int cell = here(rc[p]), row = cell_row(cell);
+      const int q = ((row + 1) * F.fw + cell_col(cell) + 1) * 3, up = F.fw * 3;
+      const double* k = tab + kRowTab * row;
+      const V3<double> C = get(fr, q), E = get(fr, q + 3), W = get(fr, q - 3);
+      const V3<double> N = get(fr, q + up), Sv = get(fr, q - up);
+      const V3<double> f = swe_increment(C, E, W, N, Sv, k[0], k[1], k[2], k[4], k[5], k[3], k[6], st, stg, h0);
+      const V3<double> z = {prev[p].h + wgt * f.h, prev[p].u + wgt * f.u, prev[p].v + wgt * f.v};
+      prev[p] = z;
+      if (m >= w.out0 && m < w.out1) {
+        out[m] = z.h;
+        out[plane + m] = z.u;
+        out[2 * plane + m] = z.v;
+        if (traj_out) {
+          double* o = traj_out + S.traj_off + int64_t(n + 1) * 3 * plane + m;
+          o[0] = z.h + h0;
+          o[plane] = z.u;
+          o[2 * plane] = z.v;
+        }
+      }
+    }
+    if (!more) break;
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < K; ++p) {
+      const int m = here(cb) + p * NT;
+      if (m < g.lo || m >= g.hi) continue;
+      const int cell = here(rc[p]), r = F.rb + cell_row(cell), c = cell_col(cell);
+      const V3<double> old = get(fr, F.pos(r, c));
+      put_cell(fr, F, S, D.half, r, c, prev[p], -1.0);
+      prev[p] = old;
+    }
+#pragma unroll
+    for (int b = 0; b < NI; ++b)
+      if (bon[b]) put(fr, bpos[b], ring[b]);
+    __syncthreads();
+  }
+}
+
+// Levels n0 + 1 .. n0 + steps of the tangent-linear sweep about the stored
+// trajectory (n0 = 0: from the packed FP64 perturbation dx).  dtraj_out
+// (nullable): the packed FP64 perturbation trajectory.
+template <int NT, int K, bool SPAN>
+__global__ __launch_bounds__(NT) void k_tlm_blk(Dom<double> D, const BlkWork* __restrict__ work,
+                                                int n0, int steps, const double* __restrict__ dx,
+                                                double* __restrict__ dtraj_out) {
+  constexpr int NI = border_items(NT);
+  extern __shared__ double lds[];
+  const BlkWork w = work[blockIdx.x];
+  if (D.active && !D.active[w.box]) return;
+  const SubDev S = D.subs[w.box];
+  const int L = S.nlev - 1;
+  if (n0 > L || (n0 == L && n0 > 0)) return;
+  steps = min(steps, L - n0);
+  const int t = threadIdx.x, nx = S.nx, ncell = S.ncell;
+  const int64_t plane = ncell;
+  const Range in = grown(w, steps, nx, ncell);
+  const Range first = grown(w, max(steps - 1, 0), nx, ncell);
+  const Frame F = {in.lo / nx, (in.hi - 1) / nx, nx + 2};
+  double* fr = lds;
+  double* tab = lds + F.size();
+  fill_rows<NT, false>(tab, D, S, F);
+  const double h0 = D.h0, st = D.st, stg = D.stg;
+  double* dz = D.dz + S.zoff;
+  auto store = [&](int n, int m, const V3<double>& v) {
+    double* o = dz + int64_t(n) * 3 * plane + m;
+    o[0] = v.h;
+    o[plane] = v.u;
+    o[2 * plane] = v.v;
+    if (dtraj_out) {
+      double* q = dtraj_out + S.traj_off + int64_t(n) * 3 * plane + m;
+      q[0] = v.h;
+      q[plane] = v.u;
+      q[2 * plane] = v.v;
+    }
+  };
+  for (int m = in.lo + t; m < in.hi; m += NT) {
+    const int r = m / nx, c = m - r * nx;
+    const V3<double> z = ld_box(n0 == 0 ? dx + S.ctrl_off : dz + int64_t(n0) * 3 * plane, plane, m, 1.0);
+    if (n0 == 0 && m >= w.out0 && m < w.out1) store(0, m, z);
+    put_cell(fr, F, S, D.half, r, c, z, -1.0);
+  }
+  if (steps <= 0) return;
+  // the frozen ring is not perturbed: zeros on the frame's border; the state's
+  // ring of a level is staged behind the row table
+  const Border B(S, F);
+  double* ring = tab + kRowTab * F.rows();
+  int bk[NI];
+  auto ring_at = [&](int n, int b) {
+    return ld_ring(D.ring + S.ring_off + int64_t(n) * 3 * S.nring, S.nring, bk[b]);
+  };
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    int pos;
+    B.item(t + i * NT, S, F, &pos, &bk[i]);
+    if (t + i * NT < B.count()) {
+      put(fr, pos, {0.0, 0.0, 0.0});
+      put(ring, 3 * (t + i * NT), ring_at(n0, i));
+    }
+  }
+  __syncthreads();
+  // the cells of this thread, chunk by chunk from the first computed one; a
+  // lane past the computed range takes its nearest cell and keeps no result
+  const int cb = (first.lo & ~63) + t;
+  V3<double> prev[K];
+  int rc[K];
+#pragma unroll
+  for (int p = 0; p < K; ++p) {
+    const int m = min(max(cb + p * NT, first.lo), first.hi - 1);
+    const int r = m / nx, c = m - r * nx;
+    rc[p] = cell_word(r - F.rb, c, 0);
+    prev[p] = n0 > 0 ? ld_box(dz + int64_t(n0 - 1) * 3 * plane, plane, m, 1.0) : get(fr, F.pos(r, c));
+  }
+  // the state's loads of a pass are issued one pass ahead, the first pass's
+  // before the level before it is finished
+  auto issue = [&](State5<SPAN>& q, int p, int n, const Range& g) {
+    const int m = here(cb) + p * NT;
+    const int chunk = __builtin_amdgcn_readfirstlane(m & ~63);
+    if (chunk >= g.hi || chunk + 64 <= g.lo) return;          // uniform over the wave
+    const int cell = here(rc[p]);
+    q.load(state(D, S, n), plane, S, D.half, min(max(m, first.lo), first.hi - 1),
+           F.rb + cell_row(cell), cell_col(cell));
+  };
+  for (int i = 0; i < steps; ++i) {
+    const int n = n0 + i;
+    const Range g = grown(w, steps - 1 - i, nx, ncell);
+    const bool more = i + 1 < steps;
+    const double wgt = n == 0 ? 0.5 : 1.0;
+    V3<double> rv[NI];
+#pragma unroll
+    for (int b = 0; b < NI; ++b)
+      if (more && t + b * NT < B.count()) rv[b] = ring_at(n + 1, b);
+#pragma unroll
+    for (int p = 0; p < K; ++p) {
+      State5<SPAN> q;
+      issue(q, p, n, g);
+      const int m = here(cb) + p * NT;
+      const int chunk = __builtin_amdgcn_readfirstlane(m & ~63);
+      if (chunk >= g.hi || chunk + 64 <= g.lo) continue;
+      const int cell = here(rc[p]), row = cell_row(cell), c = cell_col(cell);
+      q.fix(ring, B, row, c);
+      const int a = ((row + 1) * F.fw + c + 1) * 3, up = F.fw * 3;
+      const double* k = tab + kRowTab * row;
+      const V3<double> f = swe_tangent(q.C, q.E, q.W, q.N, q.S, get(fr, a), get(fr, a + 3),
+                                       get(fr, a - 3), get(fr, a + up), get(fr, a - up), k[0], k[1],
+                                       k[2], k[4], k[5], k[3], k[6], st, stg, h0);
+      if (m >= g.lo && m < g.hi) {
+        prev[p] = {prev[p].h + wgt * f.h, prev[p].u + wgt * f.u, prev[p].v + wgt * f.v};
+        if (m >= w.out0 && m < w.out1) store(n + 1, m, prev[p]);
+      }
+    }
+    if (!more) break;
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < K; ++p) {
+      const int m = here(cb) + p * NT;
+      if (m < g.lo || m >= g.hi) continue;
+      const int cell = here(rc[p]), r = F.rb + cell_row(cell), c = cell_col(cell);
+      const V3<double> old = get(fr, F.pos(r, c));
+      put_cell(fr, F, S, D.half, r, c, prev[p], -1.0);
+      prev[p] = old;
+    }
+#pragma unroll
+    for (int b = 0; b < NI; ++b)
+      if (t + b * NT < B.count()) put(ring, 3 * (t + b * NT), rv[b]);
+    __syncthreads();
+  }
+}
+
+// Levels nhi .. nlo of the adjoint sweep (modes as k_adj).  lam: the adjoint
+// arena, four slots per box; the launch reads lambda^{nhi+1}, lambda^{nhi+2}
+// from slots 2 pin, 2 pin + 1 and leaves lambda^{nlo}, lambda^{nlo+1} in
+// slots 2 (1 - pin), 2 (1 - pin) + 1 (other blocks of the box still read the
+// first two).
+template <int NT, int K, int MODE, bool SPAN>
+__global__ __launch_bounds__(NT) void k_adj_blk(Dom<double> D, const BlkWork* __restrict__ work,
+                                                int nhi, int nlo, int pin,
+                                                const double* __restrict__ x,
+                                                const double* __restrict__ xb,
+                                                const double* __restrict__ forcing,
+                                                double* __restrict__ out) {
+  constexpr int NI = border_items(NT);
+  extern __shared__ double lds[];
+  const BlkWork w = work[blockIdx.x];
+  if (D.active && !D.active[w.box]) return;
+  const SubDev S = D.subs[w.box];
+  const int L = S.nlev - 1;
+  if (nlo > L) return;
+  const int top = min(nhi, L), steps = top - nlo + 1;
+  const bool begin = top == L;
+  const int t = threadIdx.x, nx = S.nx, ncell = S.ncell;
+  const int64_t plane = ncell;
+  const Range in = grown(w, steps, nx, ncell), first = grown(w, steps - 1, nx, ncell);
+  const Frame F = {in.lo / nx, (in.hi - 1) / nx, nx + 2};
+  double* fr = lds;
+  double* tab = lds + F.size();
+  // the state's ring of a level, staged; J of each 64-cell chunk of the block
+  const Border B(S, F);
+  double* ring = tab + kRowTab * F.rows();
+  double* pj = ring + 3 * B.count();
+  const int nchunk = (w.out1 - w.out0 + 63) / 64;
+  int* tcnt = reinterpret_cast<int*>(pj + ((nchunk + 3) & ~3));   // intervals covering a level
+  if (MODE != 1)
+    for (int i = t; i < steps; i += NT) tcnt[i] = D.tcount[S.lev0 + nlo + i];
+  fill_rows<NT, true>(tab, D, S, F);
+  const double h0 = D.h0, st = D.st, stg = D.stg;
+  double* A = D.adj + (S.adj_off / 9) * 12;
+  const double* l1 = A + int64_t(2 * pin) * 3 * plane;
+  const double* l2 = A + int64_t(2 * pin + 1) * 3 * plane;
+
+  // lambda^{top+1}, zero past the box's last level and on the border
+  for (int i = t; i < F.size(); i += NT) fr[i] = 0.0;
+  for (int i = t; i < ((nchunk + 3) & ~3); i += NT) pj[i] = 0.0;
+  int bk[NI];
+  auto ring_at = [&](int n, int b) {
+    return ld_ring(D.ring + S.ring_off + int64_t(n) * 3 * S.nring, S.nring, bk[b]);
+  };
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    int pos;
+    B.item(t + i * NT, S, F, &pos, &bk[i]);
+    if (t + i * NT < B.count()) {
+      put(ring, 3 * (t + i * NT), ring_at(top, i));
+    }
+  }
+  __syncthreads();
+  if (!begin)
+    for (int m = in.lo + t; m < in.hi; m += NT) {
+      const int r = m / nx;
+      put_cell(fr, F, S, D.half, r, m - r * nx, ld_box(l1, plane, m, 1.0), 1.0);
+    }
+  // the cells of this thread, chunk by chunk from the first computed one; a
+  // lane past the computed range takes its nearest cell and keeps no result
+  const int cb = (first.lo & ~63) + t;
+  V3<double> prev[K];
+  int rc[K];
+#pragma unroll
+  for (int p = 0; p < K; ++p) {
+    const int m = min(max(cb + p * NT, first.lo), first.hi - 1);
+    const int r = m / nx;
+    rc[p] = cell_word(r - F.rb, m - r * nx, MODE != 1 ? int(D.cover[S.cell_off + m]) : 0);
+    prev[p] = {0.0, 0.0, 0.0};
+    if (!begin) prev[p] = ld_box(l2, plane, m, 1.0);
+  }
+  // thread q: J of the block's q-th tile
+  const int ntile = (w.out1 - w.out0 + kTile - 1) / kTile;
+  double jt = 0.0;
+  double* jp = D.jpart + S.tile0 + w.out0 / kTile + t;
+  if ((MODE == 0 || MODE == 2) && !begin && t < ntile) jt = *jp;
+  __syncthreads();
+
+  // a pass's loads: the state around the cell, the overlap target (mode 3: the
+  // perturbation; mode 1: the caller's forcing), the tile's observations; they
+  // are issued one pass ahead, the first pass's before the level before it
+  // is finished
+  struct Pass {
+    State5<SPAN> q;
+    V3<double> f;
+    int bin;
+  };
+  auto issue = [&](Pass& b, int p, int n, const Range& g) {
+    const int m = here(cb) + p * NT;
+    const int chunk = __builtin_amdgcn_readfirstlane(m & ~63);
+    if (chunk >= g.hi || chunk + 64 <= g.lo) return;          // uniform over the wave
+    const int cell = here(rc[p]), mm = min(max(m, first.lo), first.hi - 1);
+    b.q.load(state(D, S, n), plane, S, D.half, mm, F.rb + cell_row(cell), cell_col(cell));
+    const int64_t lev = S.traj_off + int64_t(n) * 3 * plane;
+    if (MODE == 1) {
+      b.f = State5<SPAN>::at(forcing + lev, plane, uint32_t(mm) * 8u);
+    } else if (MODE == 3) {
+      b.f = State5<SPAN>::at(D.dz + S.zoff + int64_t(n) * 3 * plane, plane, uint32_t(mm) * 8u);
+    } else {
+      // cells no other box covers read element 0 (weight zero)
+      const bool covered = cell_cover(cell) * tcnt[n - nlo] > 1;
+      b.f = State5<SPAN>::at(D.targ + lev, plane, covered ? uint32_t(mm) * 8u : 0u);
+    }
+    // (a vector load: a scalar one would be waited for with the LDS reads)
+    if (MODE != 1)
+      b.bin = D.obs_bin[obs_key(S.tile0, S.ntile, D.maxlev, max(chunk, first.lo) / kTile, n) + here(0)];
+  };
+  for (int n = top; n >= nlo; --n) {
+    const Range g = grown(w, n - nlo, nx, ncell);
+    V3<double> rv[NI];
+#pragma unroll
+    for (int b = 0; b < NI; ++b)
+      if (n > nlo && t + b * NT < B.count()) rv[b] = ring_at(n - 1, b);
+    const int tc = MODE != 1 ? tcnt[n - nlo] : 0;
+#pragma unroll
+    for (int p = 0; p < K; ++p) {
+      Pass buf;
+      issue(buf, p, n, g);
+      const int m = here(cb) + p * NT;
+      const int chunk = __builtin_amdgcn_readfirstlane(m & ~63);
+      if (chunk >= g.hi || chunk + 64 <= g.lo) continue;      // uniform over the wave
+      State5<SPAN>& q = buf.q;
+      const V3<double>& tg = buf.f;
+      const int bin = buf.bin;
+      double jloc = 0.0;
+      {
+        const int cell = here(rc[p]), row = cell_row(cell), c = cell_col(cell);
+        const int kc = cell_cover(cell) * tc - 1;
+        double f[3] = {0.0, 0.0, 0.0};
+        if (MODE == 1) {
+          f[0] = tg.h;
+          f[1] = tg.u;
+          f[2] = tg.v;
+        }
+        q.fix(ring, B, row, c);
+        __builtin_amdgcn_sched_barrier(0);
+        const V3<double>& C = q.C;
+        const int a = ((row + 1) * F.fw + c + 1) * 3, up = F.fw * 3;
+        const double* k = tab + kRowTab * row;
+        const V3<double> l0 = get(fr, a);
+        const V3<double> ew = swe_adjoint_ew(C, q.E, q.W, q.N, q.S, l0, get(fr, a + 3), get(fr, a - 3),
+                                             k[0], k[1], k[4], k[5], st, h0);
+        __builtin_amdgcn_sched_barrier(0);
+        const V3<double> v = swe_adjoint_ns(ew, C, q.N, q.S, get(fr, a + up), get(fr, a - up), k[6],
+                                            k[2], k[3], q.sn, q.ss, st, stg, h0);
+        double ah = v.h, au = v.u, av = v.v;
+        asm volatile("" : "+v"(ah), "+v"(au), "+v"(av));   // computed here
+        if (n == 0) {
+          au = l0.u + 0.5 * au;
+          av = l0.v + 0.5 * av;
+          ah = l0.h + 0.5 * ah;
+        }
+        if (MODE != 1) {
+          if (__builtin_amdgcn_readfirstlane(bin) >= 0) obs_terms(D, bin, (chunk / 64) & 3, MODE == 3 ? tg : C, MODE == 3, f, jloc);
+          const double eh = MODE == 3 ? tg.h : C.h - tg.h;
+          const double eu = MODE == 3 ? tg.u : C.u - tg.u;
+          const double ev = MODE == 3 ? tg.v : C.v - tg.v;
+          const double mk = D.mu * double(kc);
+          f[0] += mk * eh * D.isb2[0];
+          f[1] += mk * eu * D.isb2[1];
+          f[2] += mk * ev * D.isb2[2];
+          if (MODE != 3)
+            jloc += 0.5 * mk * (eh * eh * D.isb2[0] + eu * eu * D.isb2[1] + ev * ev * D.isb2[2]);
+        }
+        const double bh = f[0] + ah + prev[p].h;
+        const double bu = f[1] + au + prev[p].u;
+        const double bv = f[2] + av + prev[p].v;
+        if (m >= g.lo && m < g.hi) prev[p] = {bh, bu, bv};
+        const bool own = m >= w.out0 && m < w.out1;
+        if (n == nlo && n > 0 && own) {
+          double* b0 = A + int64_t(2 - 2 * pin) * 3 * plane + m;
+          double* b1 = A + int64_t(3 - 2 * pin) * 3 * plane + m;
+          b0[0] = bh;
+          b0[plane] = bu;
+          b0[2 * plane] = bv;
+          b1[0] = l0.h;
+          b1[plane] = l0.u;
+          b1[2 * plane] = l0.v;
+        } else if (n == 0 && own) {
+          const int64_t o = S.ctrl_off + m;
+          double gh = bh, gu = bu, gv = bv;
+          if (MODE == 0) {
+            const double wb = D.weight_mode ? 1.0 : 1.0 / double(cell_cover(cell));
+            const double dh = x[o] - xb[o];
+            const double du = x[o + plane] - xb[o + plane];
+            const double dv = x[o + 2 * plane] - xb[o + 2 * plane];
+            gh = wb * dh * D.isb2[0] + bh;
+            gu = wb * du * D.isb2[1] + bu;
+            gv = wb * dv * D.isb2[2] + bv;
+            jloc += 0.5 * wb * (dh * dh * D.isb2[0] + du * du * D.isb2[1] + dv * dv * D.isb2[2]);
+          }
+          out[o] = gh;
+          out[o + plane] = gu;
+          out[o + 2 * plane] = gv;
+          flag_nonfinite(D.nonfinite, !(isfinite(gh) && isfinite(gu) && isfinite(gv)));
+        }
+        if (!own) jloc = 0.0;
+      }
+      if ((MODE == 0 || MODE == 2) && chunk >= w.out0 && chunk < w.out1) {
+        jloc = wave_sum(jloc);
+        if ((t & 63) == 0) pj[(chunk - w.out0) / 64] = jloc;
+      }
+    }
+    __syncthreads();
+    if ((MODE == 0 || MODE == 2) && t < ntile) {
+      const double* s = pj + 4 * t;
+      const double tot = 0.0 + s[0] + s[1] + s[2] + s[3];
+      jt = n == L ? tot : jt + tot;
+    }
+    if (n == nlo) break;
+#pragma unroll
+    for (int p = 0; p < K; ++p) {
+      const int m = here(cb) + p * NT;
+      if (m < g.lo || m >= g.hi) continue;
+      const int cell = here(rc[p]), r = F.rb + cell_row(cell), c = cell_col(cell);
+      const V3<double> old = get(fr, F.pos(r, c));
+      put_cell(fr, F, S, D.half, r, c, prev[p], 1.0);
+      prev[p] = old;
+    }
+#pragma unroll
+    for (int b = 0; b < NI; ++b)
+      if (t + b * NT < B.count()) put(ring, 3 * (t + b * NT), rv[b]);
+    __syncthreads();
+  }
+  if ((MODE == 0 || MODE == 2) && t < ntile) *jp = jt;
+}
+
+// ---- plan and launchers -------------------------------------------------------
+namespace {
+constexpr int kBlkThreads = 1024;
+constexpr int kBlkPassMax = 6;             // 128 registers hold six passes
+
+// whether a block fits one workgroup, and what its levels cost
+struct BlkFit {
+  bool ok;
+  int passes;                 // cells computed at a launch's first level, in passes
+  double us;                  // a level's time, both sweeps, on a compute unit of its own
+  double bytes;               // a level's memory traffic, both sweeps
+  size_t lds;
+};
+BlkFit blk_fit(const SubDev& S, const BlkWork& w, int steps) {
+  auto lo = [&](int e) { return std::max(0, w.out0 - e * S.nx); };
+  auto hi = [&](int e) { return std::min(S.ncell, w.out1 + e * S.nx); };
+  const int rows = (hi(steps) - 1) / S.nx - lo(steps) / S.nx + 1;
+  BlkFit f{};
+  f.lds = size_t(rows + 2) * (S.nx + 2) * 3 * sizeof(double) + size_t(rows) * kRowTab * sizeof(double) +
+          size_t(2 * rows + 2 * S.nx) * 3 * sizeof(double) +
+          size_t((w.out1 - w.out0 + 255) / 64) * sizeof(double) + size_t(std::max(steps, S.nlev) + 2) * sizeof(int);
+  f.passes = (hi(steps - 1) - (lo(steps - 1) & ~63) + kBlkThreads - 1) / kBlkThreads;
+  double cells = 0.0;
+  for (int e = 0; e < steps; ++e) cells += double(hi(e) - lo(e)) / steps;
+  const double own = w.out1 - w.out0, in = hi(steps) - lo(steps);
+  f.us = 1.7 + 0.0034 * cells;
+  f.bytes = 24.0 * (own + 1.65 * cells + (4.0 * in + 2.0 * own) / steps);
+  f.ok = f.lds <= kBlkLdsMax && f.passes <= kBlkPassMax && 2 * (rows + S.nx) <= kBorderMax &&
+         S.nx >= 2 && S.ny >= 2;
+  return f;
+}
+// box s as nb blocks of whole tiles
+void cut_box(const SubDev& S, int s, int nb, std::vector<BlkWork>& out) {
+  for (int b = 0; b < nb; ++b) {
+    const int t0 = int(int64_t(S.ntile) * b / nb), t1 = int(int64_t(S.ntile) * (b + 1) / nb);
+    out.push_back(BlkWork{s, t0 * kTile, std::min(S.ncell, t1 * kTile)});
+  }
+}
+}  // namespace
+
+// The decomposition into blocks that the model below finds fastest; not ok
+// where no box decomposition fits or the step kernels are faster.  Measured
+// (both sweeps, one block to a compute unit): a level takes 3.8 us for 612
+// cells and 9.8 us for 2340, 12 us per launch besides; memory moves 4 TB/s
+// under these kernels; the step kernels take a launch of at least 4.5 and 6.5
+// us per level, or 72 + 111 B per cell at 4.4 TB/s.  More blocks than boxes
+// spread few boxes over the chip (64 boxes of 40 x 72 cells: 64 whole ones 453
+// us per evaluation, 224 blocks of 7 levels 337 us, 480 of 5 454 us), at the
+// price of the rows that two blocks compute both.
+BlkPlan plan_blocks(const std::vector<SubDev>& subs, int maxlev, int cus) {
+  double cells = 0.0;
+  for (const SubDev& S : subs) cells += S.ncell;
+  const int levels = std::max(1, maxlev - 1);
+  BlkPlan best{};
+  double best_us = levels * (std::max(4.5, cells * 72 / 4.4e6) + std::max(6.5, cells * 111 / 4.4e6));
+  for (int k : {levels, 24, 16, 12, 10, 8, 7, 6, 5, 4, 3}) {
+    if (k > levels) continue;
+    for (int want : {1, cus / 2, cus, 2 * cus}) {     // blocks wanted on the whole
+      BlkPlan p{};
+      p.ok = true;
+      p.levels = k;
+      double sum = 0.0, longest = 0.0, bytes = 0.0;
+      std::vector<std::pair<double, BlkWork>> work;
+      for (size_t s = 0; s < subs.size() && p.ok; ++s) {
+        const SubDev& S = subs[s];
+        const bool whole = S.span || k == levels;   // not to be cut
+        int nb = whole ? 1 : std::max(1, int(want * (S.ncell / cells)));
+        for (;; ++nb) {
+          std::vector<BlkWork> cut;
+          cut_box(S, int(s), nb, cut);
+          bool ok = true;
+          double us = 0.0, most = 0.0, by = 0.0;
+          size_t lds = 0;
+          int passes = 0;
+          std::vector<double> each;
+          for (const BlkWork& w : cut) {
+            const BlkFit f = blk_fit(S, w, k);
+            ok = ok && f.ok;
+            lds = std::max(lds, f.lds);
+            passes = std::max(passes, f.passes);
+            us += f.us;
+            most = std::max(most, f.us);
+            by += f.bytes;
+            each.push_back(f.us * std::min(k, S.nlev));
+          }
+          if (ok) {
+            p.lds = std::max(p.lds, lds);
+            p.passes = std::max(p.passes, passes);
+            for (size_t i = 0; i < cut.size(); ++i) work.emplace_back(each[i], cut[i]);
+            sum += us;
+            bytes += by;
+            longest = std::max(longest, most);
+            break;
+          }
+          if (whole || nb >= S.ntile) {
+            p.ok = false;
+            break;
+          }
+        }
+      }
+      const double pack = int(work.size()) <= cus ? longest : sum / cus + 0.5 * longest;
+      const double us = (levels + k - 1) / k * 12.0 + levels * std::max(pack, bytes / 4.0e6);
+      if (!p.ok || us >= best_us) continue;
+      best = p;
+      best_us = us;
+      best.us = us;
+      if (k == levels) best.levels = maxlev;          // no box is cut: one launch per sweep
+      // launch order: the longest first where blocks differ, else box by box
+      // (one XCD holding neighbouring blocks, as the step kernels do: 8.0 ->
+      // 8.5 ms on 1024 boxes of 72 x 136 cells)
+      if (longest > 1.25 * sum / double(work.size()))
+        std::stable_sort(work.begin(), work.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+      best.work.clear();
+      for (const auto& w : work) best.work.push_back(w.second);
+    }
+  }
+  return best;
+}
+
+namespace {
+template <typename F>
+hipError_t blk_allow(F* k) {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             int(kBlkLdsMax));
+}
+template <int K, bool SPAN>
+hipError_t blk_prepare_k() {
+  hipError_t e = blk_allow(&k_fwd_blk<kBlkThreads, K>);
+  if (e == hipSuccess) e = blk_allow(&k_tlm_blk<kBlkThreads, K, SPAN>);
+  if (e == hipSuccess) e = blk_allow(&k_adj_blk<kBlkThreads, K, 0, SPAN>);
+  if (e == hipSuccess) e = blk_allow(&k_adj_blk<kBlkThreads, K, 1, SPAN>);
+  if (e == hipSuccess) e = blk_allow(&k_adj_blk<kBlkThreads, K, 2, SPAN>);
+  if (e == hipSuccess) e = blk_allow(&k_adj_blk<kBlkThreads, K, 3, SPAN>);
+  return e;
+}
+// f(passes, span) with the smallest compiled pass count that holds p
+template <typename F>
+void with_plan(int p, bool span, F f) {
+  auto go = [&](auto k) {
+    if (span) f(k, std::true_type{});
+    else f(k, std::false_type{});
+  };
+  if (p <= 1) go(std::integral_constant<int, 1>{});
+  else if (p <= 2) go(std::integral_constant<int, 2>{});
+  else if (p <= 3) go(std::integral_constant<int, 3>{});
+  else if (p <= 4) go(std::integral_constant<int, 4>{});
+  else go(std::integral_constant<int, kBlkPassMax>{});
+}
+}  // namespace
+
+hipError_t blk_prepare(int passes, bool span) {
+  hipError_t e = hipSuccess;
+  with_plan(passes, span, [&](auto k, auto s) { e = blk_prepare_k<decltype(k)::value, decltype(s)::value>(); });
+  return e;
+}
+
+void launch_fwd_blk(const Dom<double>& D, const BlkLaunch& b, int n0, int levels, const double* x, double* traj_out,
+                    hipStream_t st) {
+  with_plan(b.passes, false, [&](auto k, auto) {
+    auto* kern = &k_fwd_blk<kBlkThreads, decltype(k)::value>;
+    hipLaunchKernelGGL(kern, dim3(b.nwork), dim3(kBlkThreads), b.lds, st, D, b.work, n0, levels, x, traj_out);
+  });
+}
+void launch_tlm_blk(const Dom<double>& D, const BlkLaunch& b, int n0, int levels, const double* dx, double* dtraj_out,
+                    hipStream_t st) {
+  with_plan(b.passes, b.span, [&](auto k, auto s) {
+    auto* kern = &k_tlm_blk<kBlkThreads, decltype(k)::value, decltype(s)::value>;
+    hipLaunchKernelGGL(kern, dim3(b.nwork), dim3(kBlkThreads), b.lds, st, D, b.work, n0, levels, dx, dtraj_out);
+  });
+}
+void launch_adj_blk(const Dom<double>& D, const BlkLaunch& b, int mode, int nhi, int nlo, int pin,
+                    const double* x, const double* xb, const double* forcing, double* out,
+                    hipStream_t st) {
+  with_plan(b.passes, b.span, [&](auto k, auto s) {
+    constexpr int K = decltype(k)::value;
+    constexpr bool SPAN = decltype(s)::value;
+    auto* kern = mode == 0 ? &k_adj_blk<kBlkThreads, K, 0, SPAN>
+                 : mode == 1 ? &k_adj_blk<kBlkThreads, K, 1, SPAN>
+                 : mode == 2 ? &k_adj_blk<kBlkThreads, K, 2, SPAN> : &k_adj_blk<kBlkThreads, K, 3, SPAN>;
+    hipLaunchKernelGGL(kern, dim3(b.nwork), dim3(kBlkThreads), b.lds, st, D, b.work, nhi, nlo, pin, x, xb,
+                       forcing, out);
+  });
+}
+
+}  // namespace dd4dvar

@@ -63,7 +63,8 @@ struct dd4dvar_ctx {
   double* cosx64 = nullptr;
   uint8_t* cover = nullptr;
   int32_t* tcount = nullptr;
-  int32_t *obs_ptr = nullptr, *obs_code = nullptr;
+  int32_t *obs_ptr = nullptr, *obs_code = nullptr, *obs_bin = nullptr;
+  ObsTile* obs_tile = nullptr;
   double *obs_val = nullptr, *obs_q = nullptr;
   double *jpart = nullptr, *jc = nullptr, *jconst = nullptr;
   // per-tile cost partials in use: jpart, or the device's static scratch
@@ -82,6 +83,10 @@ struct dd4dvar_ctx {
   int box_kmin = 0;                     // passes that hold the largest box
   bool box_span = false;                // some box spans the circle
   int strip_k = 0;                      // rows per column strip of the strip adjoint (0: n/a)
+  // sweeps over several levels per launch (FP64, plain scheme): mode 0's
+  // launches where they apply and every level is stored
+  bool blk_ok = false;
+  BlkLaunch blk{};
   // Turkel-Zwas variant (tz_p > 0): step kernels only
   int tz_p = 0, tz_q = 1;
   double tz_alpha = 0;
@@ -246,6 +251,8 @@ Dom<T> local_dom(const dd4dvar_ctx* c) {
   D.obs_code = c->obs_code;
   D.obs_val = c->obs_val;
   D.obs_q = c->obs_q;
+  D.obs_bin = c->obs_bin;
+  D.obs_tile = c->obs_tile;
   D.jpart = c->jpart_use ? c->jpart_use : c->jpart;
   D.nbr_idx = c->nbr_idx;
   D.hsrc = c->hsrc;
@@ -375,6 +382,16 @@ void global_forward(dd4dvar_ctx* c, const double* x, double* traj, hipStream_t s
   chk(hipGetLastError(), "global forward launch");
 }
 
+// whether the sweeps over every box take several levels per launch
+bool blk_sweeps(const dd4dvar_ctx* c) { return c->blk_ok && c->exec_mode == 0 && c->ckpt == 0; }
+// launches over `levels` levels, and levels of each but the last (even shares
+// within the plan's limit)
+int blk_launches(const dd4dvar_ctx* c, int levels, int* each) {
+  const int n = std::max(1, (levels + c->blk.levels - 1) / c->blk.levels);
+  *each = std::max(1, (levels + n - 1) / n);
+  return n;
+}
+
 // local forward sweeps of every box; traj_out (nullable) receives the packed
 // FP64 trajectory, level by level as it is computed when levels share slots
 template <typename T>
@@ -393,6 +410,16 @@ void local_forward(dd4dvar_ctx* c, const double* x, hipStream_t st, double* traj
       chk(launch_fwd_box(D, x, c->d_order, c->nsub, c->box_lds, c->box_k, c->box_span, st),
           "persistent forward launch");
       if (traj_out) launch_traj_out<T>(D, traj_out, 0, c->ntiles, -1, st);
+      c->have_forward = true;
+      return;
+    }
+  }
+  if constexpr (std::is_same<T, double>::value) {
+    if (blk_sweeps(c)) {
+      int each = 0;
+      const int count = blk_launches(c, c->maxlev - 1, &each);
+      for (int i = 0; i < count; ++i) launch_fwd_blk(D, c->blk, i * each, each, x, traj_out, st);
+      chk(hipGetLastError(), "forward launch");
       c->have_forward = true;
       return;
     }
@@ -426,6 +453,18 @@ void local_adjoint(dd4dvar_ctx* c, int mode, const double* x, const double* forc
       chk(launch_adj_box(D, mode, x, c->xb, forcing, out, c->d_order, c->nsub, c->box_lds,
                          strip ? c->strip_k : c->box_k, c->box_span, strip, st),
           "persistent adjoint launch");
+      return;
+    }
+  }
+  if constexpr (std::is_same<T, double>::value) {
+    if (!ids && blk_sweeps(c)) {
+      int each = 0;
+      const int count = blk_launches(c, c->maxlev, &each);
+      for (int i = 0; i < count; ++i) {
+        const int hi = c->maxlev - 1 - i * each, lo = std::max(0, hi - each + 1);
+        launch_adj_blk(D, c->blk, mode, hi, lo, i & 1, x, c->xb, forcing, out, st);
+      }
+      chk(hipGetLastError(), "adjoint launch");
       return;
     }
   }
@@ -470,15 +509,22 @@ void ensure_dz(dd4dvar_ctx* c) {
 // the stored trajectory: dZ = M' dx, every level into the dz arena (the
 // persistent per-box kernel in modes 2 and 3, else the step kernels)
 template <typename T>
-void local_tlm(dd4dvar_ctx* c, const double* dx, hipStream_t st) {
+void local_tlm(dd4dvar_ctx* c, const double* dx, hipStream_t st, double* dtraj_out = nullptr) {
   ensure_dz(c);
   Dom<T> D = local_dom<T>(c);
   if constexpr (std::is_same<T, float>::value) {
     if (c->exec_mode >= 2) {
       chk(launch_tlm_box(D, dx, c->d_order, c->nsub, c->box_lds, c->box_k, c->box_span, st),
           "persistent tangent-linear launch");
+      if (dtraj_out) launch_dz_out<T>(D, dtraj_out, 0, c->ntiles, st);
       return;
     }
+  } else if (blk_sweeps(c)) {
+    int each = 0;
+    const int count = blk_launches(c, c->maxlev - 1, &each);
+    for (int i = 0; i < count; ++i) launch_tlm_blk(D, c->blk, i * each, each, dx, dtraj_out, st);
+    chk(hipGetLastError(), "tangent-linear launch");
+    return;
   }
   auto sweep = [&](int tile_base, int ntiles, int nlev) {
     launch_tlm_init<T>(D, dx, tile_base, ntiles, st);
@@ -498,6 +544,7 @@ void local_tlm(dd4dvar_ctx* c, const double* dx, hipStream_t st) {
   } else {
     for (const SubDev& S : c->subs) sweep(S.tile0, S.ntile, S.nlev);
   }
+  if (dtraj_out) launch_dz_out<T>(D, dtraj_out, 0, c->ntiles, st);
   chk(hipGetLastError(), "tangent-linear launch");
 }
 
@@ -575,8 +622,12 @@ void cost_grad_impl(dd4dvar_ctx* c, const std::vector<int32_t>* ids, const doubl
     if (!ids && (c->exec_mode == 2 || c->exec_mode == 4) && std::is_same<T, float>::value) {
       nf = na = 1;                      // one persistent launch per sweep
     } else if (!ids && c->exec_mode == 0) {
-      nf = c->maxlev;
-      na = c->maxlev;
+      nf = na = c->maxlev;
+      if (std::is_same<T, double>::value && blk_sweeps(c)) {
+        int each = 0;
+        nf = blk_launches(c, c->maxlev - 1, &each);
+        na = blk_launches(c, c->maxlev, &each);
+      }
     } else {
       for (const SubDev& S : c->subs)
         if (!ids || std::find(ids->begin(), ids->end(), int32_t(&S - c->subs.data())) != ids->end()) {
@@ -839,6 +890,41 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
     }
   }
 
+  // each bin's entries ordered by cell, then field, and (plain scheme) the
+  // masks by which a lane finds its own cell's entries
+  std::vector<int32_t> obin;
+  std::vector<ObsTile> otile;
+  {
+    std::vector<std::pair<int32_t, int32_t>> ord;
+    std::vector<double> v2, q2;
+    if (m.tz_p == 0) obin.assign(nkeys, -1);
+    for (int64_t k = 0; k < nkeys; ++k) {
+      const int32_t o0 = optr[k], o1 = optr[k + 1];
+      if (o1 == o0) continue;
+      if (!std::is_sorted(ocode.begin() + o0, ocode.begin() + o1)) {
+        ord.clear();
+        for (int32_t o = o0; o < o1; ++o) ord.emplace_back(ocode[o], o);
+        std::sort(ord.begin(), ord.end());
+        v2.assign(oval.begin() + o0, oval.begin() + o1);
+        q2.assign(oq.begin() + o0, oq.begin() + o1);
+        for (int32_t o = o0; o < o1; ++o) {
+          ocode[o] = ord[o - o0].first;
+          oval[o] = v2[ord[o - o0].second - o0];
+          oq[o] = q2[ord[o - o0].second - o0];
+        }
+      }
+      if (m.tz_p != 0) continue;
+      ObsTile t{};
+      for (int32_t o = o1; o-- > o0;) {
+        const int loc = (ocode[o] >> 2) % kTile;
+        t.mask[loc / 64][ocode[o] & 3] |= uint64_t(1) << (loc % 64);
+        t.base[loc / 64] = o;
+      }
+      obin[k] = int32_t(otile.size());
+      otile.push_back(t);
+    }
+  }
+
   // coverage CSR per global cell for the gather
   const int64_t ncell = int64_t(m.nlat) * m.nlon;
   std::vector<int32_t> cptr(ncell + 1, 0);
@@ -889,6 +975,8 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
   c->obs_code = upload(c, ocode, st);
   c->obs_val = upload(c, oval, st);
   c->obs_q = upload(c, oq, st);
+  c->obs_bin = upload(c, obin, st);
+  c->obs_tile = upload(c, otile, st);
   c->nbr_idx = upload(c, P.nbr_idx, st);
   c->hsrc = upload(c, P.halo_src, st);
   c->hoff = upload(c, P.halo_off, st);
@@ -909,7 +997,23 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
   c->targ = dalloc<char>(c, size_t(P.traj_total) * tsz + kBoxArenaTail);
   c->ring_bytes = size_t(std::max<int64_t>(ring_off, 1)) * tsz;
   c->ring = dalloc<char>(c, c->ring_bytes);
-  c->adj = dalloc<char>(c, size_t(std::max<int64_t>(adj_off, 1)) * tsz);
+  if (c->prec == DD4DVAR_FP64 && m.tz_p == 0) {
+    int cus = 0;
+    chk(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device), "attribute");
+    const BlkPlan plan = plan_blocks(c->subs, c->maxlev, cus);
+    if (plan.ok) {
+      bool span = false;
+      for (const SubDev& S : c->subs) span = span || S.span;
+      chk(blk_prepare(plan.passes, span), "block sweep set-up");
+      c->blk = BlkLaunch{upload(c, plan.work, st), int(plan.work.size()), plan.levels, plan.passes, span,
+                         plan.lds};
+      c->blk_ok = true;
+      // the pageable list is copied before it goes
+      chk(hipStreamSynchronize(st), "upload sync");
+    }
+  }
+  // rolling adjoint levels: three per box, four for the block sweeps
+  c->adj = dalloc<char>(c, size_t(std::max<int64_t>(c->blk_ok ? adj_off / 3 * 4 : adj_off, 1)) * tsz);
   if (P.model.tz_p > 0) {
     c->tz_p = P.model.tz_p;
     c->tz_q = P.model.tz_q;
@@ -1528,11 +1632,9 @@ dd4dvar_status dd4dvar_tangent_linear(dd4dvar_ctx* ctx, const double* dx_dev, do
   API_GUARD(ctx, {
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (ctx->prec == DD4DVAR_FP64) {
-      local_tlm<double>(ctx, dx_dev, st);
-      if (dtraj_dev) launch_dz_out<double>(local_dom<double>(ctx), dtraj_dev, 0, ctx->ntiles, st);
+      local_tlm<double>(ctx, dx_dev, st, dtraj_dev);
     } else {
-      local_tlm<float>(ctx, dx_dev, st);
-      if (dtraj_dev) launch_dz_out<float>(local_dom<float>(ctx), dtraj_dev, 0, ctx->ntiles, st);
+      local_tlm<float>(ctx, dx_dev, st, dtraj_dev);
     }
     chk(hipGetLastError(), "tangent-linear output launch");
     return DD4DVAR_OK;

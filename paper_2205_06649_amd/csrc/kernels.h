@@ -29,6 +29,15 @@ __host__ __device__ inline int64_t obs_key(int tile0, int ntile, int maxlev, int
   return int64_t(tile0) * maxlev + int64_t(n) * ntile + t_local;
 }
 
+// The observed cells of one non-empty (tile, level) bin: for each of the
+// tile's four 64-cell chunks one bit per cell and field, and the entry of
+// the chunk's first observation (a bin's entries are ordered by cell, then
+// field), so that a lane finds its own cell's entries by counting bits.
+struct ObsTile {
+  uint64_t mask[4][3];
+  int32_t base[4];
+};
+
 // One subdomain (or the whole grid) as the kernels see it.
 struct SubDev {
   int32_t row0, ny, col0, nx;
@@ -74,6 +83,8 @@ struct Dom {
   const int32_t* obs_code;   // local cell * 4 + field
   const double* obs_val;     // value (h as anomaly)
   const double* obs_q;       // lambda * w_o / sigma_o^2
+  const int32_t* obs_bin;    // per bin (obs_key): its ObsTile, -1 without entries
+  const ObsTile* obs_tile;
   double* jpart;             // per-tile cost accumulator
   const int32_t* nbr_idx;
   const int32_t* hsrc;

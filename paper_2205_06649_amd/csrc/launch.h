@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <vector>
+
 #include "kernels.h"
 
 namespace dd4dvar {
@@ -115,5 +117,43 @@ hipError_t launch_adj_box(const Dom<float>& D, int mode, const double* x, const 
 hipError_t launch_eval_box(const Dom<float>& D, const double* x, const double* xb, double* grad,
                            const int32_t* order, int nboxes, size_t lds_bytes, int passes,
                            bool span, hipStream_t st);
+
+// blk.hip: sweeps over several levels per launch (FP64 state, every level
+// stored), the step kernels' results bit for bit
+//
+// a run of whole tiles of one box: its own cells [out0, out1)
+struct BlkWork {
+  int32_t box, out0, out1;
+};
+// the decomposition of every box into blocks: levels per launch (all of them
+// where no box is cut), passes of 1024 cells, LDS bytes of the largest
+// block; us: the model's time per evaluation
+struct BlkPlan {
+  bool ok;
+  int levels, passes;
+  size_t lds;
+  double us;
+  std::vector<BlkWork> work;
+};
+constexpr size_t kBlkLdsMax = 160 * 1024 - 512;
+BlkPlan plan_blocks(const std::vector<SubDev>& subs, int maxlev, int cus);
+struct BlkLaunch {
+  const BlkWork* work;
+  int nwork, levels, passes;
+  bool span;                              // some box spans the circle
+  size_t lds;
+};
+hipError_t blk_prepare(int passes, bool span);   // once, before any launch: the LDS allowance
+// levels n0 + 1 .. n0 + levels, levels <= b.levels (n0 = 0: from the packed
+// controls, level 0 too)
+void launch_fwd_blk(const Dom<double>& D, const BlkLaunch& b, int n0, int levels, const double* x,
+                    double* traj_out, hipStream_t st);
+void launch_tlm_blk(const Dom<double>& D, const BlkLaunch& b, int n0, int levels, const double* dx,
+                    double* dtraj_out, hipStream_t st);
+// levels nhi .. nlo, at most b.levels of them; pin: the pair of adjoint slots the launch reads (the
+// other pair is written); the arena holds four levels per box
+void launch_adj_blk(const Dom<double>& D, const BlkLaunch& b, int mode, int nhi, int nlo, int pin,
+                    const double* x, const double* xb, const double* forcing, double* out,
+                    hipStream_t st);
 
 }  // namespace dd4dvar

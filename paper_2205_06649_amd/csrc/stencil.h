@@ -69,6 +69,129 @@ __device__ __forceinline__ V3<T> ld_lam(const T* L1, int64_t plane, int idx, int
   return {in ? h : T(0), in ? u : T(0), in ? v : T(0)};
 }
 
+// The increment F(Z^n) of a cell (discrete U, V, H of Sec. 7 with p = q = 1,
+// alpha = 0) from its five-point neighbourhood; cN, cS the cosines of the
+// rows to the north and south.
+template <typename T>
+__device__ __forceinline__ V3<T> swe_increment(const V3<T>& C, const V3<T>& E, const V3<T>& W,
+                                               const V3<T>& N, const V3<T>& Sv, T a1, T a2, T a3,
+                                               T cf, T ct, T cN, T cS, T st, T stg, T h0) {
+  const T cor = cf + ct * C.u;
+  const T U = -a1 * C.u * (E.u - W.u) - st * C.v * (N.u - Sv.u) - a2 * (E.h - W.h) + cor * C.v;
+  const T V = -a1 * C.u * (E.v - W.v) - st * C.v * (N.v - Sv.v) - stg * (N.h - Sv.h) - cor * C.u;
+  const T H = -a1 * (h0 * (E.u - W.u) + (E.h * E.u - W.h * W.u))
+              - a3 * (h0 * (N.v * cN - Sv.v * cS) + (N.h * N.v * cN - Sv.h * Sv.v * cS));
+  return {H, U, V};
+}
+
+// Its tangent linear at the same neighbourhood applied to dC .. dS.
+template <typename T>
+__device__ __forceinline__ V3<T> swe_tangent(const V3<T>& C, const V3<T>& E, const V3<T>& W,
+                                             const V3<T>& N, const V3<T>& Sv, const V3<T>& dC,
+                                             const V3<T>& dE, const V3<T>& dW, const V3<T>& dN,
+                                             const V3<T>& dS, T a1, T a2, T a3, T cf, T ct, T cN,
+                                             T cS, T st, T stg, T h0) {
+  const T cor = cf + ct * C.u;
+  const T dU = -a1 * (dC.u * (E.u - W.u) + C.u * (dE.u - dW.u)) -
+               st * (dC.v * (N.u - Sv.u) + C.v * (dN.u - dS.u)) - a2 * (dE.h - dW.h) +
+               (cor * dC.v + ct * dC.u * C.v);
+  const T dV = -a1 * (dC.u * (E.v - W.v) + C.u * (dE.v - dW.v)) -
+               st * (dC.v * (N.v - Sv.v) + C.v * (dN.v - dS.v)) - stg * (dN.h - dS.h) -
+               (cor * dC.u + ct * dC.u * C.u);
+  const T dH = -a1 * (((h0 + E.h) * dE.u + dE.h * E.u) - ((h0 + W.h) * dW.u + dW.h * W.u)) -
+               a3 * (((h0 + N.h) * dN.v + dN.h * N.v) * cN - ((h0 + Sv.h) * dS.v + dS.h * Sv.v) * cS);
+  return {dH, dU, dV};
+}
+
+// J_F(Z^n)^T lambda^{n+1} at a cell, in two steps that share few values: its
+// own terms and those of the east and west neighbours, then those of the
+// north and south ones, whose increments read it (east k sees it as west,
+// north k as south, across a pole the north k sees it as north with u, v
+// negated).  l0 .. kS: lambda^{n+1} at the cell and its neighbours (zero at
+// frozen ring positions); a3n, a3s, the a3 of the rows of the north and south
+// readers; sn, ss the across-pole signs.
+template <typename T>
+__device__ __forceinline__ V3<T> swe_adjoint_ew(const V3<T>& C, const V3<T>& E, const V3<T>& W,
+                                                const V3<T>& N, const V3<T>& Sv, const V3<T>& l0,
+                                                const V3<T>& kE, const V3<T>& kW, T a1, T a2, T cf,
+                                                T ct, T st, T h0) {
+  const T hm = h0 + C.h;
+  T au = l0.u * (-a1 * (E.u - W.u) + ct * C.v) + l0.v * (-a1 * (E.v - W.v) - cf - T(2) * ct * C.u);
+  T av = l0.u * (-st * (N.u - Sv.u) + cf + ct * C.u) + l0.v * (-st * (N.v - Sv.v));
+  T ah = T(0);
+  au += a1 * (kE.u * E.u + kE.h * hm) - a1 * (kW.u * W.u + kW.h * hm);
+  av += a1 * kE.v * E.u - a1 * kW.v * W.u;
+  ah += (a2 * kE.u + a1 * kE.h * C.u) - (a2 * kW.u + a1 * kW.h * C.u);
+  return {ah, au, av};
+}
+template <typename T>
+__device__ __forceinline__ V3<T> swe_adjoint_ns(const V3<T>& a, const V3<T>& C, const V3<T>& N,
+                                                const V3<T>& Sv, const V3<T>& kN, const V3<T>& kS,
+                                                T c, T a3n, T a3s, T sn, T ss, T st, T stg, T h0) {
+  const T hm = h0 + C.h;
+  const T vkn = sn * N.v, vks = ss * Sv.v;              // raw v at the neighbours
+  T ah = a.h, au = a.u, av = a.v;
+  au += kN.u * st * vkn - kS.u * st * vks;
+  av += (kN.v * st * vkn + kN.h * a3n * hm * c) - (kS.v * st * vks + kS.h * a3s * hm * c);
+  ah += (sn * kN.v * stg + kN.h * a3n * C.v * c) - (ss * kS.v * stg + kS.h * a3s * C.v * c);
+  return {ah, au, av};
+}
+
+// Observation entries of the calling lane's cell at one level, one wave per
+// 64-cell chunk of a tile (bin: the tile's entry of Dom::obs_bin, uniform;
+// lane m of the tile).  z is the state (or, dz true, the perturbation, whose
+// misfit is itself); adds nothing where the lane's cell is not observed.
+// Forcing q r into f, the terms of J into jloc, field by field.
+template <typename T>
+__device__ __forceinline__ void obs_terms(const Dom<T>& D, int bin, int chunk, const V3<T>& z,
+                                          bool dz, double* f, double& jloc) {
+  const ObsTile& o = D.obs_tile[__builtin_amdgcn_readfirstlane(bin)];
+  const uint64_t m[3] = {o.mask[chunk][0], o.mask[chunk][1], o.mask[chunk][2]};   // scalar registers
+  const int lane = int(threadIdx.x & 63);
+  int k = o.base[chunk];
+#pragma unroll
+  for (int i = 0; i < 3; ++i)               // entries of the lanes below
+    k = __builtin_amdgcn_mbcnt_hi(uint32_t(m[i] >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m[i]), k));
+  const T zz[3] = {z.h, z.u, z.v};
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    if (!(m[i] >> lane & 1)) continue;
+    const double qo = D.obs_q[k];
+    const double rr = dz ? double(zz[i]) : double(zz[i]) - D.obs_val[k];
+    f[i] = qo * rr;
+    if (!dz) jloc += 0.5 * qo * rr * rr;
+    ++k;
+  }
+}
+
+// Sum of a wave's 64 values in every lane, in the order of block_sum's
+// shuffle tree (lanes 32, 16, 8, 4, 2, 1 apart; a sum of two does not depend on
+// their order, so that exchanging partners gives both lanes the tree's
+// value).  By lane permutations of the vector unit: the shuffles go through
+// the LDS crossbar, six dependent round trips of it.
+template <int CTRL>
+__device__ __forceinline__ double lane_exchange(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, int(uint32_t(b)), CTRL, 0xf, 0xf, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, int(uint32_t(b >> 32)), CTRL, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, uint64_t(hi) << 32 | lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  auto half = [](double x, auto swap) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const auto lo = swap(uint32_t(b)), hi = swap(uint32_t(b >> 32));
+    return __builtin_bit_cast(double, uint64_t(hi[0]) << 32 | lo[0]) +
+           __builtin_bit_cast(double, uint64_t(hi[1]) << 32 | lo[1]);
+  };
+  v = half(v, [](uint32_t x) { return __builtin_amdgcn_permlane32_swap(x, x, false, false); });
+  v = half(v, [](uint32_t x) { return __builtin_amdgcn_permlane16_swap(x, x, false, false); });
+  v += lane_exchange<0x128>(v);            // 8 apart: rotation within 16 lanes
+  v += lane_exchange<0x124>(v);            // 4
+  v += lane_exchange<0x4e>(v);             // 2: quad_perm [2,3,0,1]
+  v += lane_exchange<0xb1>(v);             // 1: quad_perm [1,0,3,2]
+  return v;
+}
+
 __device__ __forceinline__ double block_sum(double v, double* sh) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
