@@ -25,11 +25,12 @@
 // What bounds it: the step kernels launch once per level and move 72 B
 // (forward) and 111 B (adjoint) per cell and level; here a level is written
 // once (forward) or read once (adjoint), plus the launch's two levels in and
-// out.  Small blocks are bound by the vector unit (an adjoint pass of 64 cells
-// is about 340 instructions, 140 of them FP64: 1800 cycles of a SIMD; a
-// level costs 1.1 us forward and 2.8 us adjoint for 612 cells), large ones
-// by memory.  Step kernels -> blocks, per evaluation: 8 boxes of 18 x 36
-// cells, 13 levels 113 -> 80 us; 64 boxes of 40 x 72, 34 levels 518 -> 335
+// out.  Small blocks are bound by their passes' instructions and latencies (an
+// adjoint pass of 64 cells is about 200 vector instructions, 75 of them FP64;
+// of the adjoint's 211 us on 64 boxes of 40 x 72 cells, 50 are the launches'
+// starts, 17 the swaps between levels, 38 waiting for the state's loads), large
+// ones by memory.  Step kernels -> blocks, per evaluation: 8 boxes of 18 x 36
+// cells, 13 levels 113 -> 61 us; 64 boxes of 40 x 72, 34 levels 518 -> 290
 // us; 1024 boxes of 72 x 136, 34 levels 16.6 -> 8.0 ms (forward 4.9 -> 2.4
 // ms, 3.3 TB/s of its 7.9 GB; adjoint 11.7 -> 5.6 ms).  Loads of the adjoint's
 // state one pass ahead, or the next level's lines touched early, gained
@@ -37,6 +38,8 @@
 // registers to spare, were 25 % slower than 1024, which leave 128 registers:
 // hence the values pinned to their pass below.
 #include <algorithm>
+#include <array>
+#include <map>
 #include <type_traits>
 #include <vector>
 
@@ -540,6 +543,7 @@ __global__ __launch_bounds__(NT) void k_adj_blk(Dom<double> D, const BlkWork* __
     for (int i = t; i < steps; i += NT) tcnt[i] = D.tcount[S.lev0 + nlo + i];
   fill_rows<NT, true>(tab, D, S, F);
   const double h0 = D.h0, st = D.st, stg = D.stg;
+  const double mis[3] = {D.mu * D.isb2[0], D.mu * D.isb2[1], D.mu * D.isb2[2]};
   double* A = D.adj + (S.adj_off / 9) * 12;
   const double* l1 = A + int64_t(2 * pin) * 3 * plane;
   const double* l2 = A + int64_t(2 * pin + 1) * 3 * plane;
@@ -654,22 +658,17 @@ __global__ __launch_bounds__(NT) void k_adj_blk(Dom<double> D, const BlkWork* __
                                             k[2], k[3], q.sn, q.ss, st, stg, h0);
         double ah = v.h, au = v.u, av = v.v;
         asm volatile("" : "+v"(ah), "+v"(au), "+v"(av));   // computed here
-        if (n == 0) {
+        if (n == 0) {                        // (a branch, not selects at every level)
+          asm volatile("");
           au = l0.u + 0.5 * au;
           av = l0.v + 0.5 * av;
           ah = l0.h + 0.5 * ah;
         }
         if (MODE != 1) {
-          if (__builtin_amdgcn_readfirstlane(bin) >= 0) obs_terms(D, bin, (chunk / 64) & 3, MODE == 3 ? tg : C, MODE == 3, f, jloc);
-          const double eh = MODE == 3 ? tg.h : C.h - tg.h;
-          const double eu = MODE == 3 ? tg.u : C.u - tg.u;
-          const double ev = MODE == 3 ? tg.v : C.v - tg.v;
-          const double mk = D.mu * double(kc);
-          f[0] += mk * eh * D.isb2[0];
-          f[1] += mk * eu * D.isb2[1];
-          f[2] += mk * ev * D.isb2[2];
-          if (MODE != 3)
-            jloc += 0.5 * mk * (eh * eh * D.isb2[0] + eu * eu * D.isb2[1] + ev * ev * D.isb2[2]);
+          if (__builtin_amdgcn_readfirstlane(bin) >= 0)
+            obs_terms(D, bin, (chunk / 64) & 3, MODE == 3 ? tg : C, MODE == 3, f, jloc);
+          const V3<double> e = MODE == 3 ? tg : V3<double>{C.h - tg.h, C.u - tg.u, C.v - tg.v};
+          overlap_terms(e, kc, mis, MODE != 3, f, jloc);
         }
         const double bh = f[0] + ah + prev[p].h;
         const double bu = f[1] + au + prev[p].u;
@@ -759,7 +758,7 @@ BlkFit blk_fit(const SubDev& S, const BlkWork& w, int steps) {
   double cells = 0.0;
   for (int e = 0; e < steps; ++e) cells += double(hi(e) - lo(e)) / steps;
   const double own = w.out1 - w.out0, in = hi(steps) - lo(steps);
-  f.us = 1.7 + 0.0034 * cells;
+  f.us = 2.0 + 0.0031 * cells;
   f.bytes = 24.0 * (own + 1.65 * cells + (4.0 * in + 2.0 * own) / steps);
   f.ok = f.lds <= kBlkLdsMax && f.passes <= kBlkPassMax && 2 * (rows + S.nx) <= kBorderMax &&
          S.nx >= 2 && S.ny >= 2;
@@ -776,12 +775,12 @@ void cut_box(const SubDev& S, int s, int nb, std::vector<BlkWork>& out) {
 
 // The decomposition into blocks that the model below finds fastest; not ok
 // where no box decomposition fits or the step kernels are faster.  Measured
-// (both sweeps, one block to a compute unit): a level takes 3.8 us for 612
-// cells and 9.8 us for 2340, 12 us per launch besides; memory moves 4 TB/s
+// (both sweeps, one block to a compute unit): a level takes 3.9 us for 570
+// cells and 9.4 us for 2350, 10 us per launch besides; memory moves 4 TB/s
 // under these kernels; the step kernels take a launch of at least 4.5 and 6.5
 // us per level, or 72 + 111 B per cell at 4.4 TB/s.  More blocks than boxes
-// spread few boxes over the chip (64 boxes of 40 x 72 cells: 64 whole ones 453
-// us per evaluation, 224 blocks of 7 levels 337 us, 480 of 5 454 us), at the
+// spread few boxes over the chip (64 boxes of 40 x 72 cells: 64 whole ones 430
+// us per evaluation, 256 blocks of 7 levels 301 us, 480 of 5 454 us), at the
 // price of the rows that two blocks compute both.
 BlkPlan plan_blocks(const std::vector<SubDev>& subs, int maxlev, int cus) {
   double cells = 0.0;
@@ -791,51 +790,57 @@ BlkPlan plan_blocks(const std::vector<SubDev>& subs, int maxlev, int cus) {
   double best_us = levels * (std::max(4.5, cells * 72 / 4.4e6) + std::max(6.5, cells * 111 / 4.4e6));
   for (int k : {levels, 24, 16, 12, 10, 8, 7, 6, 5, 4, 3}) {
     if (k > levels) continue;
-    for (int want : {1, cus / 2, cus, 2 * cus}) {     // blocks wanted on the whole
+    for (int want : {1, cus / 2, cus * 3 / 4, cus * 7 / 8, cus, 2 * cus}) {     // blocks wanted on the whole
       BlkPlan p{};
       p.ok = true;
       p.levels = k;
       double sum = 0.0, longest = 0.0, bytes = 0.0;
       std::vector<std::pair<double, BlkWork>> work;
+      // boxes of one shape are cut alike
+      struct Cut {
+        bool ok = false;
+        std::vector<std::pair<double, BlkWork>> blocks;
+        double us = 0.0, most = 0.0, bytes = 0.0;
+        size_t lds = 0;
+        int passes = 0;
+      };
+      std::map<std::array<int, 4>, Cut> cuts;
       for (size_t s = 0; s < subs.size() && p.ok; ++s) {
         const SubDev& S = subs[s];
         const bool whole = S.span || k == levels;   // not to be cut
-        int nb = whole ? 1 : std::max(1, int(want * (S.ncell / cells)));
-        for (;; ++nb) {
-          std::vector<BlkWork> cut;
-          cut_box(S, int(s), nb, cut);
-          bool ok = true;
-          double us = 0.0, most = 0.0, by = 0.0;
-          size_t lds = 0;
-          int passes = 0;
-          std::vector<double> each;
-          for (const BlkWork& w : cut) {
+        auto [it, fresh] = cuts.try_emplace({S.ny, S.nx, S.nlev, S.span});
+        Cut& c = it->second;
+        int nb = whole ? 1 : std::min(S.ntile, std::max(1, int(want * (S.ncell / cells) + 0.5)));
+        for (; fresh && nb <= S.ntile; ++nb) {
+          c = Cut{};
+          c.ok = true;
+          std::vector<BlkWork> blocks;
+          cut_box(S, 0, nb, blocks);
+          for (const BlkWork& w : blocks) {
             const BlkFit f = blk_fit(S, w, k);
-            ok = ok && f.ok;
-            lds = std::max(lds, f.lds);
-            passes = std::max(passes, f.passes);
-            us += f.us;
-            most = std::max(most, f.us);
-            by += f.bytes;
-            each.push_back(f.us * std::min(k, S.nlev));
+            c.ok = c.ok && f.ok;
+            c.lds = std::max(c.lds, f.lds);
+            c.passes = std::max(c.passes, f.passes);
+            c.us += f.us;
+            c.most = std::max(c.most, f.us);
+            c.bytes += f.bytes;
+            c.blocks.emplace_back(f.us * std::min(k, S.nlev), w);
           }
-          if (ok) {
-            p.lds = std::max(p.lds, lds);
-            p.passes = std::max(p.passes, passes);
-            for (size_t i = 0; i < cut.size(); ++i) work.emplace_back(each[i], cut[i]);
-            sum += us;
-            bytes += by;
-            longest = std::max(longest, most);
-            break;
-          }
-          if (whole || nb >= S.ntile) {
-            p.ok = false;
-            break;
-          }
+          if (c.ok || whole) break;
         }
+        p.ok = c.ok;
+        p.lds = std::max(p.lds, c.lds);
+        p.passes = std::max(p.passes, c.passes);
+        for (auto w : c.blocks) {
+          w.second.box = int(s);
+          work.push_back(w);
+        }
+        sum += c.us;
+        bytes += c.bytes;
+        longest = std::max(longest, c.most);
       }
       const double pack = int(work.size()) <= cus ? longest : sum / cus + 0.5 * longest;
-      const double us = (levels + k - 1) / k * 12.0 + levels * std::max(pack, bytes / 4.0e6);
+      const double us = (levels + k - 1) / k * 10.0 + levels * std::max(pack, bytes / 4.0e6);
       if (!p.ok || us >= best_us) continue;
       best = p;
       best_us = us;

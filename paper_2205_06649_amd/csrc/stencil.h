@@ -69,38 +69,45 @@ __device__ __forceinline__ V3<T> ld_lam(const T* L1, int64_t plane, int idx, int
   return {in ? h : T(0), in ? u : T(0), in ? v : T(0)};
 }
 
+// ---- FP64 arithmetic shared by the step kernels and the block sweeps, whose
+// results are equal bit for bit: contracted by hand (the FP64 sources are
+// compiled without contraction), with factors that several terms share taken
+// out.  Products that cancel in a steady state (h u of the east and the west)
+// are rounded alike.
+
 // The increment F(Z^n) of a cell (discrete U, V, H of Sec. 7 with p = q = 1,
 // alpha = 0) from its five-point neighbourhood; cN, cS the cosines of the
 // rows to the north and south.
-template <typename T>
-__device__ __forceinline__ V3<T> swe_increment(const V3<T>& C, const V3<T>& E, const V3<T>& W,
-                                               const V3<T>& N, const V3<T>& Sv, T a1, T a2, T a3,
-                                               T cf, T ct, T cN, T cS, T st, T stg, T h0) {
-  const T cor = cf + ct * C.u;
-  const T U = -a1 * C.u * (E.u - W.u) - st * C.v * (N.u - Sv.u) - a2 * (E.h - W.h) + cor * C.v;
-  const T V = -a1 * C.u * (E.v - W.v) - st * C.v * (N.v - Sv.v) - stg * (N.h - Sv.h) - cor * C.u;
-  const T H = -a1 * (h0 * (E.u - W.u) + (E.h * E.u - W.h * W.u))
-              - a3 * (h0 * (N.v * cN - Sv.v * cS) + (N.h * N.v * cN - Sv.h * Sv.v * cS));
-  return {H, U, V};
+__device__ __forceinline__ V3<double> swe_increment(const V3<double>& C, const V3<double>& E,
+                                                    const V3<double>& W, const V3<double>& N,
+                                                    const V3<double>& Sv, double a1, double a2,
+                                                    double a3, double cf, double ct, double cN,
+                                                    double cS, double st, double stg, double h0) {
+  const double cor = fma(ct, C.u, cf), ua = a1 * C.u, va = st * C.v;
+  const double due = E.u - W.u, vn = N.v * cN, vs = Sv.v * cS;
+  const double U = fma(cor, C.v, -fma(a2, E.h - W.h, fma(va, N.u - Sv.u, ua * due)));
+  const double V = -fma(cor, C.u, fma(stg, N.h - Sv.h, fma(va, N.v - Sv.v, ua * (E.v - W.v))));
+  const double x = fma(h0, due, E.h * E.u - W.h * W.u);
+  const double y = fma(h0, vn - vs, N.h * vn - Sv.h * vs);
+  return {-fma(a3, y, a1 * x), U, V};
 }
 
 // Its tangent linear at the same neighbourhood applied to dC .. dS.
-template <typename T>
-__device__ __forceinline__ V3<T> swe_tangent(const V3<T>& C, const V3<T>& E, const V3<T>& W,
-                                             const V3<T>& N, const V3<T>& Sv, const V3<T>& dC,
-                                             const V3<T>& dE, const V3<T>& dW, const V3<T>& dN,
-                                             const V3<T>& dS, T a1, T a2, T a3, T cf, T ct, T cN,
-                                             T cS, T st, T stg, T h0) {
-  const T cor = cf + ct * C.u;
-  const T dU = -a1 * (dC.u * (E.u - W.u) + C.u * (dE.u - dW.u)) -
-               st * (dC.v * (N.u - Sv.u) + C.v * (dN.u - dS.u)) - a2 * (dE.h - dW.h) +
-               (cor * dC.v + ct * dC.u * C.v);
-  const T dV = -a1 * (dC.u * (E.v - W.v) + C.u * (dE.v - dW.v)) -
-               st * (dC.v * (N.v - Sv.v) + C.v * (dN.v - dS.v)) - stg * (dN.h - dS.h) -
-               (cor * dC.u + ct * dC.u * C.u);
-  const T dH = -a1 * (((h0 + E.h) * dE.u + dE.h * E.u) - ((h0 + W.h) * dW.u + dW.h * W.u)) -
-               a3 * (((h0 + N.h) * dN.v + dN.h * N.v) * cN - ((h0 + Sv.h) * dS.v + dS.h * Sv.v) * cS);
-  return {dH, dU, dV};
+__device__ __forceinline__ V3<double> swe_tangent(
+    const V3<double>& C, const V3<double>& E, const V3<double>& W, const V3<double>& N,
+    const V3<double>& Sv, const V3<double>& dC, const V3<double>& dE, const V3<double>& dW,
+    const V3<double>& dN, const V3<double>& dS, double a1, double a2, double a3, double cf,
+    double ct, double cN, double cS, double st, double stg, double h0) {
+  const double cor = fma(ct, C.u, cf), dcor = ct * dC.u;
+  const double ue = fma(dC.u, E.u - W.u, C.u * (dE.u - dW.u));
+  const double un = fma(dC.v, N.u - Sv.u, C.v * (dN.u - dS.u));
+  const double ve = fma(dC.u, E.v - W.v, C.u * (dE.v - dW.v));
+  const double vn = fma(dC.v, N.v - Sv.v, C.v * (dN.v - dS.v));
+  const double dU = fma(dcor, C.v, cor * dC.v) - fma(a2, dE.h - dW.h, fma(st, un, a1 * ue));
+  const double dV = -(fma(dcor, C.u, cor * dC.u) + fma(stg, dN.h - dS.h, fma(st, vn, a1 * ve)));
+  const double x = fma(h0 + E.h, dE.u, dE.h * E.u) - fma(h0 + W.h, dW.u, dW.h * W.u);
+  const double y = fma(h0 + N.h, dN.v, dN.h * N.v) * cN - fma(h0 + Sv.h, dS.v, dS.h * Sv.v) * cS;
+  return {-fma(a3, y, a1 * x), dU, dV};
 }
 
 // J_F(Z^n)^T lambda^{n+1} at a cell, in two steps that share few values: its
@@ -110,31 +117,43 @@ __device__ __forceinline__ V3<T> swe_tangent(const V3<T>& C, const V3<T>& E, con
 // negated).  l0 .. kS: lambda^{n+1} at the cell and its neighbours (zero at
 // frozen ring positions); a3n, a3s, the a3 of the rows of the north and south
 // readers; sn, ss the across-pole signs.
-template <typename T>
-__device__ __forceinline__ V3<T> swe_adjoint_ew(const V3<T>& C, const V3<T>& E, const V3<T>& W,
-                                                const V3<T>& N, const V3<T>& Sv, const V3<T>& l0,
-                                                const V3<T>& kE, const V3<T>& kW, T a1, T a2, T cf,
-                                                T ct, T st, T h0) {
-  const T hm = h0 + C.h;
-  T au = l0.u * (-a1 * (E.u - W.u) + ct * C.v) + l0.v * (-a1 * (E.v - W.v) - cf - T(2) * ct * C.u);
-  T av = l0.u * (-st * (N.u - Sv.u) + cf + ct * C.u) + l0.v * (-st * (N.v - Sv.v));
-  T ah = T(0);
-  au += a1 * (kE.u * E.u + kE.h * hm) - a1 * (kW.u * W.u + kW.h * hm);
-  av += a1 * kE.v * E.u - a1 * kW.v * W.u;
-  ah += (a2 * kE.u + a1 * kE.h * C.u) - (a2 * kW.u + a1 * kW.h * C.u);
+__device__ __forceinline__ V3<double> swe_adjoint_ew(const V3<double>& C, const V3<double>& E,
+                                                     const V3<double>& W, const V3<double>& N,
+                                                     const V3<double>& Sv, const V3<double>& l0,
+                                                     const V3<double>& kE, const V3<double>& kW,
+                                                     double a1, double a2, double cf, double ct,
+                                                     double st, double h0) {
+  const double cor = fma(ct, C.u, cf), dkh = kE.h - kW.h;
+  double au = fma(l0.u, fma(-a1, E.u - W.u, ct * C.v), -(l0.v * fma(a1, E.v - W.v, fma(ct, C.u, cor))));
+  double av = fma(l0.u, fma(-st, N.u - Sv.u, cor), -(l0.v * (st * (N.v - Sv.v))));
+  au = fma(a1, fma(h0 + C.h, dkh, fma(kE.u, E.u, -(kW.u * W.u))), au);
+  av = fma(a1, fma(kE.v, E.u, -(kW.v * W.u)), av);
+  return {fma(a2, kE.u - kW.u, (a1 * C.u) * dkh), au, av};
+}
+__device__ __forceinline__ V3<double> swe_adjoint_ns(const V3<double>& a, const V3<double>& C,
+                                                     const V3<double>& N, const V3<double>& Sv,
+                                                     const V3<double>& kN, const V3<double>& kS,
+                                                     double c, double a3n, double a3s, double sn,
+                                                     double ss, double st, double stg, double h0) {
+  const double vkn = sn * N.v, vks = ss * Sv.v;          // raw v at the neighbours
+  const double q = fma(kN.h, a3n, -(kS.h * a3s)) * c;
+  const double au = fma(st, fma(kN.u, vkn, -(kS.u * vks)), a.u);
+  const double av = fma(h0 + C.h, q, fma(st, fma(kN.v, vkn, -(kS.v * vks)), a.v));
+  const double ah = fma(C.v, q, fma(stg, fma(sn, kN.v, -(ss * kS.v)), a.h));
   return {ah, au, av};
 }
-template <typename T>
-__device__ __forceinline__ V3<T> swe_adjoint_ns(const V3<T>& a, const V3<T>& C, const V3<T>& N,
-                                                const V3<T>& Sv, const V3<T>& kN, const V3<T>& kS,
-                                                T c, T a3n, T a3s, T sn, T ss, T st, T stg, T h0) {
-  const T hm = h0 + C.h;
-  const T vkn = sn * N.v, vks = ss * Sv.v;              // raw v at the neighbours
-  T ah = a.h, au = a.u, av = a.v;
-  au += kN.u * st * vkn - kS.u * st * vks;
-  av += (kN.v * st * vkn + kN.h * a3n * hm * c) - (kS.v * st * vks + kS.h * a3s * hm * c);
-  ah += (sn * kN.v * stg + kN.h * a3n * C.v * c) - (ss * kS.v * stg + kS.h * a3s * C.v * c);
-  return {ah, au, av};
+
+// Overlap misfit of a cell that K other boxes cover: forcing K mu e / sigma_b^2
+// added to f, its term of J to jloc (cost false: the forcing alone).  mis: mu
+// / sigma_b^2.
+__device__ __forceinline__ void overlap_terms(const V3<double>& e, int K, const double* mis, bool cost,
+                                              double* f, double& jloc) {
+  const double k = double(K);
+  const double gh = (mis[0] * k) * e.h, gu = (mis[1] * k) * e.u, gv = (mis[2] * k) * e.v;
+  f[0] += gh;
+  f[1] += gu;
+  f[2] += gv;
+  if (cost) jloc = fma(0.5, fma(gv, e.v, fma(gu, e.u, gh * e.h)), jloc);
 }
 
 // Observation entries of the calling lane's cell at one level, one wave per

@@ -73,11 +73,19 @@ __global__ __launch_bounds__(kTile) void k_fwd(Dom<T> D, int n, int tile_base) {
   const RowCoef<T> rc = D.rows[j];
   const T cN = D.cosx[j + 2], cS = D.cosx[j];
   const T st = D.st, stg = D.stg, h0 = D.h0;
-  const T cor = rc.cf + rc.ct * C.u;
-  const T U = -rc.a1 * C.u * (E.u - W.u) - st * C.v * (N.u - Sv.u) - rc.a2 * (E.h - W.h) + cor * C.v;
-  const T V = -rc.a1 * C.u * (E.v - W.v) - st * C.v * (N.v - Sv.v) - stg * (N.h - Sv.h) - cor * C.u;
-  const T H = -rc.a1 * (h0 * (E.u - W.u) + (E.h * E.u - W.h * W.u))
-              - rc.a3 * (h0 * (N.v * cN - Sv.v * cS) + (N.h * N.v * cN - Sv.h * Sv.v * cS));
+  T H, U, V;
+  if constexpr (sizeof(T) == 8) {
+    const V3<T> F = swe_increment(C, E, W, N, Sv, rc.a1, rc.a2, rc.a3, rc.cf, rc.ct, cN, cS, st, stg, h0);
+    H = F.h;
+    U = F.u;
+    V = F.v;
+  } else {
+    const T cor = rc.cf + rc.ct * C.u;
+    U = -rc.a1 * C.u * (E.u - W.u) - st * C.v * (N.u - Sv.u) - rc.a2 * (E.h - W.h) + cor * C.v;
+    V = -rc.a1 * C.u * (E.v - W.v) - st * C.v * (N.v - Sv.v) - stg * (N.h - Sv.h) - cor * C.u;
+    H = -rc.a1 * (h0 * (E.u - W.u) + (E.h * E.u - W.h * W.u))
+                - rc.a3 * (h0 * (N.v * cN - Sv.v * cS) + (N.h * N.v * cN - Sv.h * Sv.v * cS));
+  }
   const T wgt = n == 0 ? T(0.5) : T(1);
   T* out = zlevel(D, S, n + 1);
   out[m] = B.h + wgt * H;
@@ -171,23 +179,32 @@ __global__ __launch_bounds__(kTile) void k_adj(Dom<T> D, int n, int tile_base,
     if (!has1) l0 = kE = kW = kN = kS = V3<T>{T(0), T(0), T(0)};
     if (!has2) l2 = V3<T>{T(0), T(0), T(0)};
     const T st = D.st, stg = D.stg;
-    const T hm = D.h0 + C.h;
+    T ah, au, av;
+    if constexpr (sizeof(T) == 8) {
+      const V3<T> ew = swe_adjoint_ew(C, E, W, N, Sv, l0, kE, kW, rc.a1, rc.a2, rc.cf, rc.ct, st, D.h0);
+      const V3<T> a = swe_adjoint_ns(ew, C, N, Sv, kN, kS, rc.c, a3n, a3s, T(q.sn), T(q.ss), st, stg, D.h0);
+      ah = a.h;
+      au = a.u;
+      av = a.v;
+    } else {
+      const T hm = D.h0 + C.h;
 
-    // J_F(Z^n)^T lambda^{n+1}: self terms, then the neighbours k whose
-    // increment reads this cell (east k sees it as west, north k as south,
-    // across a pole the north k sees it as north with u, v negated)
-    T au = l0.u * (-rc.a1 * (E.u - W.u) + rc.ct * C.v) +
-           l0.v * (-rc.a1 * (E.v - W.v) - rc.cf - T(2) * rc.ct * C.u);
-    T av = l0.u * (-st * (N.u - Sv.u) + rc.cf + rc.ct * C.u) + l0.v * (-st * (N.v - Sv.v));
-    T ah = T(0);
-    au += rc.a1 * (kE.u * E.u + kE.h * hm) - rc.a1 * (kW.u * W.u + kW.h * hm);
-    av += rc.a1 * kE.v * E.u - rc.a1 * kW.v * W.u;
-    ah += (rc.a2 * kE.u + rc.a1 * kE.h * C.u) - (rc.a2 * kW.u + rc.a1 * kW.h * C.u);
-    const T vkn = T(q.sn) * N.v, vks = T(q.ss) * Sv.v;    // raw v at the neighbours
-    au += kN.u * st * vkn - kS.u * st * vks;
-    av += (kN.v * st * vkn + kN.h * a3n * hm * rc.c) - (kS.v * st * vks + kS.h * a3s * hm * rc.c);
-    ah += (T(q.sn) * kN.v * stg + kN.h * a3n * C.v * rc.c) -
-          (T(q.ss) * kS.v * stg + kS.h * a3s * C.v * rc.c);
+      // J_F(Z^n)^T lambda^{n+1}: self terms, then the neighbours k whose
+      // increment reads this cell (east k sees it as west, north k as south,
+      // across a pole the north k sees it as north with u, v negated)
+      au = l0.u * (-rc.a1 * (E.u - W.u) + rc.ct * C.v) +
+             l0.v * (-rc.a1 * (E.v - W.v) - rc.cf - T(2) * rc.ct * C.u);
+      av = l0.u * (-st * (N.u - Sv.u) + rc.cf + rc.ct * C.u) + l0.v * (-st * (N.v - Sv.v));
+      ah = T(0);
+      au += rc.a1 * (kE.u * E.u + kE.h * hm) - rc.a1 * (kW.u * W.u + kW.h * hm);
+      av += rc.a1 * kE.v * E.u - rc.a1 * kW.v * W.u;
+      ah += (rc.a2 * kE.u + rc.a1 * kE.h * C.u) - (rc.a2 * kW.u + rc.a1 * kW.h * C.u);
+      const T vkn = T(q.sn) * N.v, vks = T(q.ss) * Sv.v;    // raw v at the neighbours
+      au += kN.u * st * vkn - kS.u * st * vks;
+      av += (kN.v * st * vkn + kN.h * a3n * hm * rc.c) - (kS.v * st * vks + kS.h * a3s * hm * rc.c);
+      ah += (T(q.sn) * kN.v * stg + kN.h * a3n * C.v * rc.c) -
+            (T(q.ss) * kS.v * stg + kS.h * a3s * C.v * rc.c);
+    }
     if (n == 0) {
       au = l0.u + T(0.5) * au;
       av = l0.v + T(0.5) * av;
@@ -195,15 +212,25 @@ __global__ __launch_bounds__(kTile) void k_adj(Dom<T> D, int n, int tile_base,
     }
     // overlap misfit: K copies of (Z - mean target) / sigma_b^2
     if (MODE != 1) {
-      const double eh = MODE == 3 ? double(tg.h) : double(C.h) - double(tg.h);
-      const double eu = MODE == 3 ? double(tg.u) : double(C.u) - double(tg.u);
-      const double ev = MODE == 3 ? double(tg.v) : double(C.v) - double(tg.v);
-      const double mk = D.mu * double(K);
-      fh += mk * eh * D.isb2[0];
-      fu += mk * eu * D.isb2[1];
-      fv += mk * ev * D.isb2[2];
-      if (MODE != 3)
-        jloc += 0.5 * mk * (eh * eh * D.isb2[0] + eu * eu * D.isb2[1] + ev * ev * D.isb2[2]);
+      if constexpr (sizeof(T) == 8) {
+        const double mis[3] = {D.mu * D.isb2[0], D.mu * D.isb2[1], D.mu * D.isb2[2]};
+        const V3<double> e = MODE == 3 ? tg : V3<double>{C.h - tg.h, C.u - tg.u, C.v - tg.v};
+        double f[3] = {fh, fu, fv};
+        overlap_terms(e, K, mis, MODE != 3, f, jloc);
+        fh = f[0];
+        fu = f[1];
+        fv = f[2];
+      } else {
+        const double eh = MODE == 3 ? double(tg.h) : double(C.h) - double(tg.h);
+        const double eu = MODE == 3 ? double(tg.u) : double(C.u) - double(tg.u);
+        const double ev = MODE == 3 ? double(tg.v) : double(C.v) - double(tg.v);
+        const double mk = D.mu * double(K);
+        fh += mk * eh * D.isb2[0];
+        fu += mk * eu * D.isb2[1];
+        fv += mk * ev * D.isb2[2];
+        if (MODE != 3)
+          jloc += 0.5 * mk * (eh * eh * D.isb2[0] + eu * eu * D.isb2[1] + ev * ev * D.isb2[2]);
+      }
     }
     const double bh = fh + double(ah) + double(l2.h);
     const double bu = fu + double(au) + double(l2.u);

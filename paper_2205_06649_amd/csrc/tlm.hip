@@ -89,15 +89,24 @@ __global__ __launch_bounds__(kTile) void k_tlm(Dom<T> D, int n, int tile_base) {
   const RowCoef<T> rc = D.rows[j];
   const T cN = D.cosx[j + 2], cS = D.cosx[j];
   const T st = D.st, stg = D.stg, h0 = D.h0;
-  const T cor = rc.cf + rc.ct * C.u;
-  const T dU = -rc.a1 * (dC.u * (E.u - W.u) + C.u * (dE.u - dW.u)) -
-               st * (dC.v * (N.u - Sv.u) + C.v * (dN.u - dS.u)) - rc.a2 * (dE.h - dW.h) +
-               (cor * dC.v + rc.ct * dC.u * C.v);
-  const T dV = -rc.a1 * (dC.u * (E.v - W.v) + C.u * (dE.v - dW.v)) -
-               st * (dC.v * (N.v - Sv.v) + C.v * (dN.v - dS.v)) - stg * (dN.h - dS.h) -
-               (cor * dC.u + rc.ct * dC.u * C.u);
-  const T dH = -rc.a1 * (((h0 + E.h) * dE.u + dE.h * E.u) - ((h0 + W.h) * dW.u + dW.h * W.u)) -
-               rc.a3 * (((h0 + N.h) * dN.v + dN.h * N.v) * cN - ((h0 + Sv.h) * dS.v + dS.h * Sv.v) * cS);
+  T dH, dU, dV;
+  if constexpr (sizeof(T) == 8) {
+    const V3<T> F = swe_tangent(C, E, W, N, Sv, dC, dE, dW, dN, dS, rc.a1, rc.a2, rc.a3, rc.cf, rc.ct,
+                                cN, cS, st, stg, h0);
+    dH = F.h;
+    dU = F.u;
+    dV = F.v;
+  } else {
+    const T cor = rc.cf + rc.ct * C.u;
+    dU = -rc.a1 * (dC.u * (E.u - W.u) + C.u * (dE.u - dW.u)) -
+                 st * (dC.v * (N.u - Sv.u) + C.v * (dN.u - dS.u)) - rc.a2 * (dE.h - dW.h) +
+                 (cor * dC.v + rc.ct * dC.u * C.v);
+    dV = -rc.a1 * (dC.u * (E.v - W.v) + C.u * (dE.v - dW.v)) -
+                 st * (dC.v * (N.v - Sv.v) + C.v * (dN.v - dS.v)) - stg * (dN.h - dS.h) -
+                 (cor * dC.u + rc.ct * dC.u * C.u);
+    dH = -rc.a1 * (((h0 + E.h) * dE.u + dE.h * E.u) - ((h0 + W.h) * dW.u + dW.h * W.u)) -
+                 rc.a3 * (((h0 + N.h) * dN.v + dN.h * N.v) * cN - ((h0 + Sv.h) * dS.v + dS.h * Sv.v) * cS);
+  }
   const T wgt = n == 0 ? T(0.5) : T(1);
   T* out = dzlevel(D, S, n + 1);
   out[m] = B.h + wgt * dH;
