@@ -135,11 +135,16 @@ class Context:
         return x
 
     def cost_grad(self, x, J=None, grad=None, sub_ids=None):
+        # an evaluation of every subdomain writes every entry; with sub_ids the
+        # other subdomains read NaN and zero
         if J is None:
-            J = self.torch.full((self.nsub,), float("nan"), dtype=self.torch.float64,
-                                device=self.device)
+            J = self.torch.empty(self.nsub, dtype=self.torch.float64, device=self.device)
+            if sub_ids is not None:
+                J.fill_(float("nan"))
         if grad is None:
-            grad = self.torch.zeros(self.ctrl_len, dtype=self.torch.float64, device=self.device)
+            grad = self.empty(self.ctrl_len)
+            if sub_ids is not None:
+                grad.zero_()
         L.dd4dvar_local_cost_grad(self.handle, x.data_ptr(), J.data_ptr(), grad.data_ptr(),
                                   self._stream(), sub_ids=sub_ids)
         self.traj_generation += 1
