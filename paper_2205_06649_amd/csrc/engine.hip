@@ -227,6 +227,7 @@ void build_parts(dd4dvar_ctx* c, int len, hipStream_t st) {
   c->parts.part = upload(c, parts, st);
   c->parts.box = upload(c, boxp, st);
   c->parts.nparts = int(parts.size());
+  c->parts.len = len;
   c->parts.acc = dalloc<double>(c, size_t(kPartSlots) * parts.size());
   c->part_len = len;
   // the host vectors are pageable: the copies complete before they go
@@ -1725,18 +1726,33 @@ dd4dvar_status dd4dvar_solve_mixed(dd4dvar_ctx* ctx, dd4dvar_ctx* ctx_lo,
 namespace dd4dvar {
 
 namespace {
-// device buffers of one solve, released on every exit path
+// device buffers of one solve, released on every exit path, out of shared
+// blocks (an allocation and its release cost about 30 us, some thirty buffers
+// a tenth of a small solve); larger ones on their own
 struct SolveBuffers {
+  size_t block;
   std::vector<void*> p;
+  char* at = nullptr;
+  size_t left = 0;
+  explicit SolveBuffers(size_t b) : block(b) {}
   ~SolveBuffers() {
     for (void* q : p) (void)hipFree(q);
   }
   template <typename P>
   P* get(size_t n) {
-    void* q = nullptr;
-    chk(hipMalloc(&q, std::max<size_t>(n, 1) * sizeof(P)), "hipMalloc solve");
-    p.push_back(q);
-    return static_cast<P*>(q);
+    const size_t bytes = (std::max<size_t>(n, 1) * sizeof(P) + 255) & ~size_t(255);
+    if (bytes > left || bytes > block) {
+      void* q = nullptr;
+      chk(hipMalloc(&q, std::max(bytes, block)), "hipMalloc solve");
+      p.push_back(q);
+      if (bytes > block) return static_cast<P*>(q);
+      at = static_cast<char*>(q);
+      left = block;
+    }
+    P* r = reinterpret_cast<P*>(at);
+    at += bytes;
+    left -= bytes;
+    return r;
   }
 };
 
@@ -1760,7 +1776,8 @@ dd4dvar_status solve_typed(dd4dvar_ctx* c, const dd4dvar_solve_opts* o, const do
   chk(hipDeviceSynchronize(), "sync");
   const int nsub = c->nsub;
   const int64_t N = c->plan.ctrl_total;
-  SolveBuffers B;
+  // (blocks for the ten or so vectors of a small problem)
+  SolveBuffers B(std::min<size_t>(size_t(64) << 20, (size_t(4) << 20) + size_t(10 * N) * sizeof(double)));
   LbState L{};
   L.subs = c->d_subs;
   L.nsub = nsub;
@@ -1799,7 +1816,7 @@ dd4dvar_status solve_typed(dd4dvar_ctx* c, const dd4dvar_solve_opts* o, const do
   L.iters = B.get<int32_t>(nsub);
   L.trials = B.get<int32_t>(nsub);
   L.ls = B.get<uint8_t>(nsub);
-  L.pending = B.get<int32_t>(1);
+  L.pending = B.get<int32_t>(4);
   L.P = c->parts;
   L.alph = B.get<double>(size_t(L.m) * nsub);
   L.acc = B.get<uint8_t>(nsub);
@@ -1932,6 +1949,24 @@ dd4dvar_status solve_typed(dd4dvar_ctx* c, const dd4dvar_solve_opts* o, const do
         c->eval_mask = nullptr;
         ++evals;
         gn_after(G, st);
+      }
+    } else if (lb_one_part(L)) {
+      lb_start(L, st);
+      chk(hipMemsetAsync(L.pending, 0, 4 * sizeof(int32_t), st), "memset");
+      lb_count(L, st);
+      int2 left = make_int2(0, read1(L.pending, st));      // boxes searching, boxes iterating
+      if (left.y) chk(hipMemsetAsync(L.pending, 0, 4 * sizeof(int32_t), st), "memset");
+      for (int round = 0; left.y > 0;) {
+        lb_direction_one(L, st);
+        do {
+          c->eval_mask = L.ls;
+          cost_grad_impl<T>(c, nullptr, L.xphys, L.Jt, L.gradx, st);
+          c->eval_mask = nullptr;
+          ++evals;
+          lb_armijo_one(L, round, st);
+          left = read1(reinterpret_cast<const int2*>(L.pending + 2 * (round & 1)), st);
+          ++round;
+        } while (left.x > 0);
       }
     } else {
       lb_start(L, st);

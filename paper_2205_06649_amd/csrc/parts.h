@@ -28,6 +28,7 @@ struct PartMap {
   const Part* part;   // every box's parts, box by box, in entry order
   const int2* box;    // per box: (first part, number of parts)
   int nparts;
+  int len;            // entries of a part (a box's last one has the rest)
   double* acc;        // [kPartSlots][nparts] partial sums
 };
 

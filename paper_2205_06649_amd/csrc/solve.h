@@ -24,7 +24,7 @@ struct LbState {
   double *J, *Jt, *gd, *alpha, *rho /* [m][nsub] */, *gamma, *g0norm, *gnorm, *step;
   int32_t *npairs, *head, *status, *iters, *trials;
   uint8_t* ls;              // in the line search (also the evaluation mask)
-  int32_t* pending;         // device counter
+  int32_t* pending;         // device counters (lb_armijo_one: two pairs, used in turn)
   // vector work by parts; per box the recursion's a_k ([m][nsub]), the
   // accepted trial of the current line-search round and the ring slot its
   // pair went to (-1: not kept)
@@ -41,6 +41,13 @@ void lb_direction(const LbState& L, hipStream_t st);
 void lb_trial(const LbState& L, hipStream_t st);
 void lb_armijo(const LbState& L, hipStream_t st);
 void lb_count(const LbState& L, hipStream_t st);
+// where every box is one part of at most kPartLen entries: direction and first
+// trial in one launch; an Armijo round (accept or halve and try again, pair,
+// move) in one, which leaves {boxes searching, boxes iterating} in the pair of
+// counters of its round and clears the other pair (clear both before round 0)
+bool lb_one_part(const LbState& L);
+void lb_direction_one(const LbState& L, hipStream_t st);
+void lb_armijo_one(const LbState& L, int round, hipStream_t st);
 void lb_step(const LbState& L, hipStream_t st);
 
 }  // namespace dd4dvar

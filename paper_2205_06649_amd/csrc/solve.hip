@@ -17,6 +17,7 @@
 #include "kernels.h"
 #include "parts.h"
 #include "solve.h"
+#include "stencil.h"
 
 namespace dd4dvar {
 
@@ -337,6 +338,208 @@ __global__ __launch_bounds__(64 * kBoxWaves) void k_lb_step_s(LbState L) {
   if ((threadIdx.x & 63) == 0) L.step[s] = mx;
 }
 
+// ---- boxes of one part each ------------------------------------------------
+// Where every box's control is one part (at most 16384 entries), one workgroup
+// takes a box through a whole stage of the iteration: the two-loop recursion
+// with the direction's end and the first trial point, or an Armijo round with
+// the pair, the move and a rejected step's next trial.  The direction sits in
+// registers (16 entries per thread) and every dot product stays in the
+// workgroup: 2 launches per iteration and round instead of 2 m + 5 and 4, whose
+// gaps and starts were the time (64 boxes of 8640 entries, m = 8: direction
+// and trial 19 launches, 196 us, -> 1 of 24 us; Armijo round 37 -> 10 us).
+// Sums: per thread over its entries, the wave's shuffle tree, the waves in
+// order.
+namespace {
+constexpr int kOneB = 1024;                // threads per box
+constexpr int kOneE = kPartLen / kOneB;    // entries per thread
+
+// sum over the workgroup, in every thread
+__device__ __forceinline__ double one_sum(double v, double* sh) {
+  v = stencil::wave_sum(v);
+  __syncthreads();                         // sh may still be read from a previous call
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double r = 0.0;
+#pragma unroll
+  for (int i = 0; i < kOneB / 64; ++i) r += sh[i];
+  return r;
+}
+// f(entry in registers, entry of the box) over the thread's entries below n
+template <typename F>
+__device__ __forceinline__ void one_each(int n, F f) {
+#pragma unroll
+  for (int j = 0; j < kOneE; ++j) {
+    const int i = int(threadIdx.x) + j * kOneB;
+    if (i < n) f(j, i);
+  }
+}
+// sigma_b of entry i without a division per entry
+__device__ __forceinline__ double one_sigma(const LbState& L, int ncell, int i) {
+  return i < ncell ? L.sb[0] : (i < 2 * ncell ? L.sb[1] : L.sb[2]);
+}
+}  // namespace
+
+__global__ __launch_bounds__(kOneB) void k_lb_dir_one(LbState L) {
+  __shared__ double sh[kOneB / 64];
+  __shared__ double alph[kMaxPairs];
+  const Part pt = L.P.part[blockIdx.x];
+  const int s = pt.box;
+  if (L.status[s] != 0) return;
+  const int n = pt.hi, np = L.npairs[s];
+  const double* g = L.g + pt.off;
+  double q[kOneE];
+  double acc = 0.0;
+  if (np > 0) {
+    one_each(n, [&](int j, int i) { q[j] = g[i]; });
+    for (int k = 0; k < np; ++k) {         // newest pair first
+      const int slot = pair_slot(L, s, k);
+      const double* sv = L.S + int64_t(slot) * L.N + pt.off;
+      const double* yv = L.Y + int64_t(slot) * L.N + pt.off;
+      acc = 0.0;
+      one_each(n, [&](int j, int i) { acc += sv[i] * q[j]; });
+      const double a = L.rho[int64_t(slot) * L.nsub + s] * one_sum(acc, sh);
+      if (threadIdx.x == 0) alph[k] = a;
+      one_each(n, [&](int j, int i) { q[j] -= a * yv[i]; });
+    }
+    const double gamma = L.gamma[s];
+    one_each(n, [&](int j, int) { q[j] *= gamma; });
+    for (int k = np - 1; k >= 0; --k) {
+      const int slot = pair_slot(L, s, k);
+      const double* sv = L.S + int64_t(slot) * L.N + pt.off;
+      const double* yv = L.Y + int64_t(slot) * L.N + pt.off;
+      acc = 0.0;
+      one_each(n, [&](int j, int i) { acc += yv[i] * q[j]; });
+      const double b = L.rho[int64_t(slot) * L.nsub + s] * one_sum(acc, sh);
+      const double ab = alph[k] - b;       // (written before one_sum's barriers)
+      one_each(n, [&](int j, int i) { q[j] += sv[i] * ab; });
+    }
+    acc = 0.0;
+    one_each(n, [&](int j, int i) {
+      q[j] = -q[j];
+      acc += g[i] * q[j];
+    });
+  }
+  double gd = np > 0 ? one_sum(acc, sh) : 0.0;
+  if (!(gd < 0.0)) {                       // no pairs, or not a descent direction
+    acc = 0.0;
+    one_each(n, [&](int j, int i) {
+      q[j] = -g[i];
+      acc += q[j] * q[j];
+    });
+    gd = -one_sum(acc, sh);
+  }
+  // a full step could not show a decrease above the noise floor of J
+  const bool flat = -gd <= L.jnoise * fabs(L.J[s]);
+  const double* xi = L.xi + pt.off;
+  const double* xb = L.xb + pt.off;
+  double* d = L.d + pt.off;
+  double* xt = L.xt + pt.off;
+  double* x = L.xphys + pt.off;
+  one_each(n, [&](int j, int i) {
+    d[i] = q[j];
+    if (flat) return;
+    const double v = xi[i] + q[j];
+    xt[i] = v;
+    x[i] = xb[i] + one_sigma(L, pt.ncell, i) * v;
+  });
+  __syncthreads();                         // every thread has read J
+  if (threadIdx.x != 0) return;
+  L.gd[s] = gd;
+  L.alpha[s] = 1.0;
+  L.trials[s] = 0;
+  L.ls[s] = flat ? 0 : 1;
+  if (flat) L.status[s] = 1;
+}
+
+// Armijo test of the evaluated trial.  count[0] += boxes still searching,
+// count[1] += boxes still iterating; the other pair of counters is cleared.
+__global__ __launch_bounds__(kOneB) void k_lb_armijo_one(LbState L, int32_t* count, int32_t* clear) {
+  __shared__ double sh[kOneB / 64];
+  if (blockIdx.x == 0 && threadIdx.x < 2) clear[threadIdx.x] = 0;
+  const Part pt = L.P.part[blockIdx.x];
+  const int s = pt.box, n = pt.hi;
+  if (!L.ls[s]) {
+    if (threadIdx.x == 0 && L.status[s] == 0) atomicAdd(count + 1, 1);
+    return;
+  }
+  double* xi = L.xi + pt.off;
+  double* g = L.g + pt.off;
+  double* xt = L.xt + pt.off;
+  const double* gx = L.gradx + pt.off;
+  const double alpha = L.alpha[s], gd = L.gd[s], J = L.J[s], Jt = L.Jt[s];
+  if (!(Jt <= J + L.c1 * alpha * gd)) {
+    // rejected: half the step, or the search given up (the iterate kept)
+    const int t = L.trials[s] + 1;
+    const double a = 0.5 * alpha;
+    const bool stop = t >= L.max_ls || a * fabs(gd) <= L.jnoise * fabs(J);
+    if (!stop) {
+      const double* d = L.d + pt.off;
+      const double* xb = L.xb + pt.off;
+      double* x = L.xphys + pt.off;
+      one_each(n, [&](int, int i) {
+        const double v = xi[i] + a * d[i];
+        xt[i] = v;
+        x[i] = xb[i] + one_sigma(L, pt.ncell, i) * v;
+      });
+    }
+    __syncthreads();                       // every thread has read the scalars
+    if (threadIdx.x != 0) return;
+    L.trials[s] = t;
+    L.alpha[s] = a;
+    if (stop) {
+      L.ls[s] = 0;
+      L.status[s] = 2;
+    } else {
+      atomicAdd(count, 1);
+      atomicAdd(count + 1, 1);
+    }
+    return;
+  }
+  const int slot = L.head[s], np = L.npairs[s], it = L.iters[s] + 1;
+  const double g0 = L.g0norm[s];
+  double sy = 0, yy = 0, ss = 0, gg = 0;
+  one_each(n, [&](int, int i) {
+    const double gn = one_sigma(L, pt.ncell, i) * gx[i];
+    const double a = xt[i] - xi[i];
+    const double b = gn - g[i];
+    sy += a * b;
+    yy += b * b;
+    ss += a * a;
+    gg += gn * gn;
+  });
+  sy = one_sum(sy, sh);
+  yy = one_sum(yy, sh);
+  ss = one_sum(ss, sh);
+  gg = one_sum(gg, sh);
+  const bool keep = sy > 1e-12 * sqrt(ss) * sqrt(yy);
+  double* sv = L.S + int64_t(slot) * L.N + pt.off;
+  double* yv = L.Y + int64_t(slot) * L.N + pt.off;
+  one_each(n, [&](int, int i) {
+    const double gn = one_sigma(L, pt.ncell, i) * gx[i];
+    if (keep) {
+      sv[i] = xt[i] - xi[i];
+      yv[i] = gn - g[i];
+    }
+    xi[i] = xt[i];
+    g[i] = gn;
+  });
+  if (threadIdx.x != 0) return;            // (the sums' barriers: every thread has read the scalars)
+  if (keep) {
+    L.rho[int64_t(slot) * L.nsub + s] = 1.0 / sy;
+    L.gamma[s] = sy / yy;
+    L.head[s] = (slot + 1) % L.m;
+    L.npairs[s] = min(np + 1, L.m);
+  }
+  const double gn = sqrt(gg);
+  L.J[s] = Jt;
+  L.gnorm[s] = gn;
+  L.iters[s] = it;
+  L.ls[s] = 0;
+  if (gn <= L.grad_rtol * g0) L.status[s] = 1;
+  else if (it >= L.max_iter) L.status[s] = 3;
+  else atomicAdd(count + 1, 1);
+}
+
 namespace {
 dim3 parts_grid(const LbState& L) { return dim3(unsigned(L.P.nparts)); }
 }  // namespace
@@ -365,6 +568,14 @@ void lb_armijo(const LbState& L, hipStream_t st) {
   hipLaunchKernelGGL(k_lb_pair_v, parts_grid(L), dim3(kPartB), 0, st, L);
   hipLaunchKernelGGL(k_lb_pair_s, dim3(box_wave_blocks(L.nsub)), dim3(64 * kBoxWaves), 0, st, L);
   hipLaunchKernelGGL(k_lb_move, parts_grid(L), dim3(kPartB), 0, st, L);
+}
+bool lb_one_part(const LbState& L) { return L.P.nparts == L.nsub && L.P.len <= kPartLen; }
+void lb_direction_one(const LbState& L, hipStream_t st) {
+  hipLaunchKernelGGL(k_lb_dir_one, parts_grid(L), dim3(kOneB), 0, st, L);
+}
+void lb_armijo_one(const LbState& L, int round, hipStream_t st) {
+  hipLaunchKernelGGL(k_lb_armijo_one, parts_grid(L), dim3(kOneB), 0, st, L, L.pending + 2 * (round & 1),
+                     L.pending + 2 * (~round & 1));
 }
 void lb_count(const LbState& L, hipStream_t st) {
   hipLaunchKernelGGL(k_lb_count, dim3((L.nsub + kPartB - 1) / kPartB), dim3(kPartB), 0, st, L);
