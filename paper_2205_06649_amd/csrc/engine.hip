@@ -62,11 +62,13 @@ struct dd4dvar_ctx {
   RowCoef<double>* rows64 = nullptr;
   double* cosx64 = nullptr;
   uint8_t* cover = nullptr;
+  int32_t* perm = nullptr;
   int32_t* tcount = nullptr;
   int32_t *obs_ptr = nullptr, *obs_code = nullptr, *obs_bin = nullptr;
   ObsTile* obs_tile = nullptr;
   double *obs_val = nullptr, *obs_q = nullptr;
   double *jpart = nullptr, *jc = nullptr, *jconst = nullptr;
+  int jc_split = 1;  // sums over levels per wave of the overlap targets
   // per-tile cost partials in use: jpart, or the device's static scratch
   // during dd4dvar_local_cost_grad_noalloc
   double* jpart_use = nullptr;
@@ -247,6 +249,7 @@ Dom<T> local_dom(const dd4dvar_ctx* c) {
   D.rows = static_cast<const RowCoef<T>*>(c->rows);
   D.cosx = static_cast<const T*>(c->cosx);
   D.cover = c->cover;
+  D.perm = c->perm;
   D.tcount = c->tcount;
   D.obs_ptr = c->obs_ptr;
   D.obs_code = c->obs_code;
@@ -672,10 +675,10 @@ void exchange_lockstep(dd4dvar_ctx* c, const double* x, hipStream_t st) {
       const int n = g - lev0[j];
       if (n < 0 || n >= nlev[j]) continue;
       launch_ring_from_local<T>(Dn, j * nsp, nsp, c->ring_blocks, n, st);
-      launch_targets_from_local<T>(D, n, tb[j], nt[j], c->jc, st);
+      launch_targets_from_local<T>(D, n, tb[j], nt[j], c->jc_split, c->jc, st);
     }
   }
-  launch_reduce_jconst(c->d_subs, c->nsub, c->jc, 0.5 * P.model.mu_overlap, c->jconst, st);
+  launch_reduce_jconst(c->d_subs, c->nsub, c->jc, c->jc_split, 0.5 * P.model.mu_overlap, c->jconst, st);
   chk(hipGetLastError(), "exchange launch");
   // every frozen ring entry of every level has been staged; copied (not
   // swapped) so that recorded graphs keep pointing at the live rings
@@ -692,8 +695,8 @@ void exchange_impl(dd4dvar_ctx* c, const double* x, hipStream_t st) {
   local_forward<T>(c, x, st);
   Dom<T> D = local_dom<T>(c);
   launch_ring_from_local<T>(D, 0, c->nsub, c->ring_blocks, -1, st);
-  launch_targets_from_local<T>(D, -1, 0, c->ntiles, c->jc, st);   // every level
-  launch_reduce_jconst(c->d_subs, c->nsub, c->jc, 0.5 * c->plan.model.mu_overlap, c->jconst, st);
+  launch_targets_from_local<T>(D, -1, 0, c->ntiles, c->jc_split, c->jc, st);   // every level
+  launch_reduce_jconst(c->d_subs, c->nsub, c->jc, c->jc_split, 0.5 * c->plan.model.mu_overlap, c->jconst, st);
   chk(hipGetLastError(), "exchange launch");
 }
 
@@ -767,7 +770,7 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
     S.nbr1 = int32_t(P.nbr_ptr[s + 1]);
     if (S.nbr1 - S.nbr0 > 64)
       throw DevError{DD4DVAR_E_INVALID, "a box overlaps more than 64 others (exchange limit)"};
-    S.pad_ = 0;
+    S.perm0 = int32_t(P.cell_ptr[s % P.nspace]);   // (pieces come first, interval by interval)
     S.traj_off = b.traj_off;
     S.zoff = b.traj_off;
     S.ring_off = ring_off;
@@ -846,6 +849,37 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
   for (size_t i = 0; i < cover.size(); ++i) {
     if (P.cover_box[i] > 255) throw DevError{DD4DVAR_E_INVALID, "coverage count above 255"};
     cover[i] = uint8_t(P.cover_box[i]);
+  }
+  // cells of every spatial piece in the exchange's order: those that other
+  // boxes of the interval cover first, ordered by the set of those boxes (a
+  // wave then visits the boxes that its own cells share, and the tiles of the
+  // other cells have nothing to do at levels that one interval holds)
+  std::vector<int32_t> perm(size_t(P.cell_ptr[P.nspace]));
+  {
+    std::vector<std::pair<uint64_t, int32_t>> band;
+    for (int i = 0; i < P.nspace; ++i) {
+      const BoxInfo& b = P.boxes[i];
+      const int32_t* cov = P.cover_box.data() + P.cell_ptr[i];
+      int32_t* out = perm.data() + P.cell_ptr[i];
+      band.clear();
+      for (int e = 0; e < int(b.ncell()); ++e) {
+        if (cov[e] <= 1) continue;
+        uint64_t set = 0;
+        for (int64_t q = P.nbr_ptr[i]; q < P.nbr_ptr[i + 1]; ++q) {
+          const BoxInfo& o = P.boxes[P.nbr_idx[q]];
+          if (P.nbr_idx[q] >= P.nspace) break;        // (sorted: the first interval's boxes come first)
+          int cc = b.col0 + e % b.nx - o.col0;
+          cc = ((cc % m.nlon) + m.nlon) % m.nlon;
+          const int rr = b.row0 + e / b.nx - o.row0;
+          if (rr >= 0 && rr < o.ny && cc < o.nx) set |= uint64_t(1) << (q - P.nbr_ptr[i]);
+        }
+        band.emplace_back(set, e);
+      }
+      std::sort(band.begin(), band.end());
+      for (const auto& cell : band) *out++ = cell.second;
+      for (int e = 0; e < int(b.ncell()); ++e)
+        if (cov[e] <= 1) *out++ = e;
+    }
   }
   const int64_t nkeys = int64_t(tile) * c->maxlev;
   std::vector<int32_t> optr(nkeys + 1, 0);
@@ -971,6 +1005,7 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
     c->cosx = upload(c, c32, st);
   }
   c->cover = upload(c, cover, st);
+  c->perm = upload(c, perm, st);
   c->tcount = upload(c, P.time_count, st);
   c->obs_ptr = upload(c, optr, st);
   c->obs_code = upload(c, ocode, st);
@@ -986,7 +1021,14 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
   c->cptr = upload(c, cptr, st);
   c->cpiece = upload(c, cpiece, st);
   c->jpart = dalloc<double>(c, tile);
-  c->jc = dalloc<double>(c, tile);
+  // A wave of the overlap targets waits for its loads level after level (about
+  // 2 us each); where the tiles' waves are fewer than twice those that the
+  // chip holds, several take the levels of a tile in turn.  One number for all
+  // exchanges of a context: with shared level slots (one launch per level)
+  // the sums are the same bits.  FP64, 128 x 256 in 32 boxes of half of 50 steps:
+  // 110 us in rows with one sum, 64 us in the order of perm, 28 us with several.
+  c->jc_split = std::max(1, std::min({8, 4096 / std::max(1, tile), c->maxlev}));
+  c->jc = dalloc<double>(c, int64_t(tile) * (kTile / 64) * c->jc_split);
   c->jconst = dalloc<double>(c, P.nsub);
   c->xb = dalloc<double>(c, P.ctrl_total);
   c->d_ids = dalloc<int32_t>(c, P.nsub);

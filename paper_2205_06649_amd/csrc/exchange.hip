@@ -11,6 +11,7 @@
 // * Before any local solve both come from the global background run.
 #include "kernels.h"
 #include "launch.h"
+#include "stencil.h"
 
 namespace dd4dvar {
 
@@ -20,17 +21,13 @@ namespace {
 template <typename T>
 constexpr int kGather = sizeof(T) == 4 ? 8 : 4;
 
-__device__ __forceinline__ double block_sum2(double v, double* sh) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  if (lane == 0) sh[wid] = v;
-  __syncthreads();
-  double r = 0.0;
-  if (threadIdx.x == 0)
-    for (int i = 0; i < int(blockDim.x >> 6); ++i) r += sh[i];
-  return r;
-}
+// blocks that share a box's levels in the ring kernels (a position's levels
+// one after another in one thread left the chip waiting: FP64, 128 x 256 in 32
+// boxes of half of 50 steps 33.6 -> 8.4 us; FP32, 512 x 1024 in 256 boxes of 33
+// levels 130 us either way: a memory line per value of an east or west ring)
+constexpr int kRingSplit = 8;
 
+constexpr int kWaves = kTile / 64;         // partial sums per tile
 }  // namespace
 
 // targets (and backgrounds at level 0) from the global FP64 trajectory, whose
@@ -71,7 +68,7 @@ __global__ void k_ring_from_global(Dom<T> D, const double* __restrict__ bg, int6
   if (src < 0) return;
   const int64_t g = D.hgcell[S.hmap_off + k];
   const T sg = T(D.hsign[S.hmap_off + k]);
-  for (int n = 0; n < S.nlev; ++n) {
+  for (int n = blockIdx.z; n < S.nlev; n += gridDim.z) {
     const double* B = bg + int64_t(S.lev0 + n) * 3 * gplane;
     T* R = D.ring + S.ring_off + int64_t(n) * 3 * S.nring;
     R[k] = T(B[g]);
@@ -91,8 +88,9 @@ __global__ void k_ring_from_local(Dom<T> D, int box_base, int level) {
   const SubDev P = D.subs[src];
   const int64_t off = D.hoff[S.hmap_off + k];
   const T sg = T(D.hsign[S.hmap_off + k]);
-  const int n0 = level < 0 ? 0 : level, n1 = level < 0 ? S.nlev : (level < S.nlev ? level + 1 : level);
-  for (int n = n0; n < n1; ++n) {   // same interval: same levels
+  const int n0 = level < 0 ? int(blockIdx.z) : level;
+  const int n1 = level < 0 ? S.nlev : (level < S.nlev ? level + 1 : level);
+  for (int n = n0; n < n1; n += gridDim.z) {   // same interval: same levels
     const T* Z = zlevel(D, P, n);
     T* R = D.ring + S.ring_off + int64_t(n) * 3 * S.nring;
     R[k] = Z[off];
@@ -102,80 +100,104 @@ __global__ void k_ring_from_local(Dom<T> D, int box_base, int level) {
 }
 
 // Overlap targets of one local level (level >= 0) or of every level (level
-// < 0) of the boxes of a tile range.  Each cell first marks, once, the
-// entries of its box's neighbour list whose extended boxes contain it in
-// space (one bit per entry, at most 64; the list itself is staged in LDS),
-// then at each level visits the entries marked by some lane of its wave and
-// takes the mean and the spread of the marked neighbours that hold the
-// level, in one pass with sums shifted by the first value (the values of one
-// cell differ little between boxes, so the shifted sums lose nothing to
+// < 0) of the boxes of a tile range.  Lane i of every wave holds entry i of
+// its box's neighbour list (at most 64).  Each cell first marks, once, the
+// entries whose extended boxes contain it in space (one bit per entry), then
+// at each level visits the entries marked by some lane of its wave and takes
+// the mean and the spread of the marked neighbours that hold the level, in
+// one pass with sums shifted by the first value (the values of one cell
+// differ little between boxes, so the shifted sums lose nothing to
 // cancellation).
+//
+// The cells come in the order of Dom::perm: in rows, almost every wave of a
+// box touches its east and west overlaps and visits their boxes with a
+// fraction of its lanes; in that order a wave's cells share their boxes and
+// the waves without a covered cell have nothing to do.  The waves need
+// nothing of each other: each adds up its own spreads, over the levels in
+// order (or every split-th of them, see dd4dvar_ctx::jc_split).  FP32, 64
+// pieces of 512 x 1024 in 4 intervals of 33 levels: 712 us in rows with a
+// barrier per level (the vector units 80 % busy, 199 instructions per wave and
+// level), 536 us now, held by the memory: 2 GB move, three times the values,
+// since an overlap is 8 of the 32 cells of a line wide.
 template <typename T>
 __global__ __launch_bounds__(kTile) void k_targets_from_local(Dom<T> D, int level, int tile_base,
-                                                              double* __restrict__ jc) {
-  __shared__ double red[kTile / 64];
-  // the box's neighbour list, staged once: first level, levels, first row
-  // and column, width, cells, state offset
-  __shared__ int nb_lev0[64], nb_nlev[64], nb_row0[64], nb_col0[64], nb_nx[64], nb_ny[64],
-      nb_ncell[64];
-  __shared__ int64_t nb_zoff[64];
+                                                              int split, double* __restrict__ jc) {
   const int w = tile_base + xcd_tile(blockIdx.x, gridDim.x);
   const int2 wt = D.tiles[w];
   const SubDev S = D.subs[wt.x];
-  const int n0 = level < 0 ? 0 : level, n1 = level < 0 ? S.nlev : level + 1;
+  // levels n0, n0 + split, ...: one of the sums z = 0 .. split - 1 of the wave
+  const int n0 = level < 0 ? int(blockIdx.y) : level, n1 = level < 0 ? S.nlev : level + 1;
   if (n0 >= S.nlev) return;                 // uniform over the block
   const int nq = S.nbr1 - S.nbr0;           // <= 64 (checked at set-up)
-  for (int i = threadIdx.x; i < nq; i += kTile) {
-    const SubDev P = D.subs[D.nbr_idx[S.nbr0 + i]];
-    nb_lev0[i] = P.lev0;
-    nb_nlev[i] = P.nlev;
-    nb_row0[i] = P.row0;
-    nb_col0[i] = P.col0;
-    nb_nx[i] = P.nx;
-    nb_ny[i] = P.ny;
-    nb_ncell[i] = P.ncell;
-    nb_zoff[i] = P.zoff;
+  const int lane = threadIdx.x & 63;
+  // the lane's entry: first level, levels, first row and column, width,
+  // height, cells, state offset
+  int my_lev0 = 0, my_nlev = 0, my_row0 = 0, my_col0 = 0, my_nx = 0, my_ny = 0, my_ncell = 0;
+  int64_t my_zoff = 0;
+  if (lane < nq) {
+    const SubDev& P = D.subs[D.nbr_idx[S.nbr0 + lane]];
+    my_lev0 = P.lev0;
+    my_nlev = P.nlev;
+    my_row0 = P.row0;
+    my_col0 = P.col0;
+    my_nx = P.nx;
+    my_ny = P.ny;
+    my_ncell = P.ncell;
+    my_zoff = P.zoff;
   }
-  __syncthreads();
-  const int m = wt.y * kTile + threadIdx.x;
-  const bool valid = m < S.ncell;
-  const int mm = valid ? m : 0;
-  const int r = mm / S.nx, c = mm - r * S.nx;
+  // the wave's cells in the exchange's order
+  const int e = wt.y * kTile + threadIdx.x;
+  const bool valid = e < S.ncell;
+  const int m = D.perm[S.perm0 + (valid ? e : 0)];
+  const int r = m / S.nx, c = m - r * S.nx;
   const int grow = S.row0 + r;
   int gcol = S.col0 + c;
   if (gcol >= D.nlon) gcol -= D.nlon;
   // per lane: the entries whose boxes contain the cell; per wave: their union
-  uint64_t hits = 0;
+  uint64_t hits = 0, wave_hits = 0;
   for (int i = 0; i < nq; ++i) {
-    const int rr = grow - nb_row0[i];
-    int cc = gcol - nb_col0[i];
+    const int rr = grow - __builtin_amdgcn_readlane(my_row0, i);
+    int cc = gcol - __builtin_amdgcn_readlane(my_col0, i);
     if (cc < 0) cc += D.nlon;
-    if (valid && rr >= 0 && rr < nb_ny[i] && cc < nb_nx[i])
-      hits |= uint64_t(1) << i;
+    const bool hit = valid && rr >= 0 && rr < __builtin_amdgcn_readlane(my_ny, i) &&
+                     cc < __builtin_amdgcn_readlane(my_nx, i);
+    hits |= uint64_t(hit) << i;
+    wave_hits |= uint64_t(__ballot(hit) != 0) << i;
   }
-  uint32_t wlo = uint32_t(hits), whi = uint32_t(hits >> 32);
-  for (int off = 32; off > 0; off >>= 1) {
-    wlo |= __shfl_xor(wlo, off, 64);
-    whi |= __shfl_xor(whi, off, 64);
-  }
-  // the union is the same in every lane: keep it in scalar registers
-  const uint64_t wave_hits = (uint64_t(__builtin_amdgcn_readfirstlane(whi)) << 32) |
-                             uint32_t(__builtin_amdgcn_readfirstlane(wlo));
-  // lane i < nq holds entry i's level range, for one ballot per level
-  const int lane = threadIdx.x & 63;
-  const int my_lev0 = lane < nq ? nb_lev0[lane] : 0, my_nlev = lane < nq ? nb_nlev[lane] : 0;
-  const int cov = valid ? int(D.cover[S.cell_off + mm]) : 0;
+  const int cov = valid ? int(D.cover[S.cell_off + m]) : 0;
+  const bool band = __any(cov > 1);         // a cell that other boxes of the interval cover
   const int64_t plane = S.ncell;
-  double acc = 0.0;                         // thread 0: the tile's sum over levels
-  for (int n = n0; n < n1; ++n) {
-    double jloc = 0.0;
-    const int K = cov * D.tcount[S.lev0 + n] - 1;
-    const int gl = S.lev0 + n;
+  double acc = 0.0;                         // the wave's sum over levels
+  // at each level: boxes of the level's intervals, and the slot that the
+  // lane's entry holds the level in (both loaded a turn ahead)
+  auto slot = [&](int n) {
+    const int pl = S.lev0 + n - my_lev0;
+    return pl >= 0 && pl < my_nlev ? D.zslot[pl] : -1;
+  };
+  int tc_next = D.tcount[S.lev0 + n0], slot_next = slot(n0);
+  for (int n = n0; n < n1; n += split) {
+    const int tc = tc_next, my_slot = slot_next;
+    if (n + split < n1) {
+      tc_next = D.tcount[S.lev0 + n + split];
+      slot_next = slot(n + split);
+    }
+    if (tc == 1 && !band) continue;          // none of the cells is covered (uniform)
+    const int K = cov * tc - 1;
     // entries that some lane of the wave hits and that hold the level, in
     // list order; the first kGather<T> of them are loaded together, before any
     // is used, then summed in list order
-    const int my_pl = gl - my_lev0;
-    uint64_t rem = wave_hits & uint64_t(__ballot(my_pl >= 0 && my_pl < my_nlev));
+    const int64_t my_base = my_zoff + int64_t(my_slot) * 3 * my_ncell;
+    const int my_lo = int(uint32_t(my_base)), my_hi = int(my_base >> 32);
+    uint64_t rem = wave_hits & uint64_t(__ballot(my_slot >= 0));
+    auto cell_of = [&](int i, int& pc) -> const T* {           // i: uniform
+      const int rr = grow - __builtin_amdgcn_readlane(my_row0, i);
+      int cc = gcol - __builtin_amdgcn_readlane(my_col0, i);
+      if (cc < 0) cc += D.nlon;
+      pc = __builtin_amdgcn_readlane(my_ncell, i);
+      const int64_t base = int64_t(uint32_t(__builtin_amdgcn_readlane(my_lo, i))) |
+                           (int64_t(__builtin_amdgcn_readlane(my_hi, i)) << 32);
+      return D.traj + base + (rr * __builtin_amdgcn_readlane(my_nx, i) + cc);
+    };
     T zh[kGather<T>], zu[kGather<T>], zv[kGather<T>];
     bool hk[kGather<T>];
 #pragma unroll
@@ -185,17 +207,13 @@ __global__ __launch_bounds__(kTile) void k_targets_from_local(Dom<T> D, int leve
       if (rem) {                                               // uniform
         const int i = __builtin_ctzll(rem);
         rem &= rem - 1;
+        int pc;
+        const T* Z = cell_of(i, pc);
         hk[k] = (hits >> i) & 1;
         if (hk[k]) {
-          const int pl = gl - nb_lev0[i];
-          const int rr = grow - nb_row0[i];
-          int cc = gcol - nb_col0[i];
-          if (cc < 0) cc += D.nlon;
-          const int64_t pc = nb_ncell[i];
-          const T* Z = D.traj + nb_zoff[i] + int64_t(D.zslot[pl]) * 3 * pc + int64_t(rr) * nb_nx[i] + cc;
           zh[k] = Z[0];
           zu[k] = Z[pc];
-          zv[k] = Z[2 * pc];
+          zv[k] = Z[2 * int64_t(pc)];
         }
       }
     }
@@ -222,16 +240,13 @@ __global__ __launch_bounds__(kTile) void k_targets_from_local(Dom<T> D, int leve
       if (hk[k]) add(double(zh[k]), double(zu[k]), double(zv[k]));
     for (; rem; rem &= rem - 1) {                              // beyond kGather<T> entries
       const int i = __builtin_ctzll(rem);
+      int pc;
+      const T* Z = cell_of(i, pc);
       if (!((hits >> i) & 1)) continue;
-      const int pl = gl - nb_lev0[i];
-      const int rr = grow - nb_row0[i];
-      int cc = gcol - nb_col0[i];
-      if (cc < 0) cc += D.nlon;
-      const int64_t pc = nb_ncell[i];
-      const T* Z = D.traj + nb_zoff[i] + int64_t(D.zslot[pl]) * 3 * pc + int64_t(rr) * nb_nx[i] + cc;
-      add(double(Z[0]), double(Z[pc]), double(Z[2 * pc]));
+      add(double(Z[0]), double(Z[pc]), double(Z[2 * int64_t(pc)]));
     }
-    if (K > 0 && cnt > 0) {
+    double jloc = 0.0;
+    if (valid && K > 0 && cnt > 0) {
       const double inv = 1.0 / double(cnt);
       T* Tg = D.targ + S.traj_off + int64_t(n) * 3 * plane;
       Tg[m] = T(ch + ah * inv);
@@ -241,25 +256,27 @@ __global__ __launch_bounds__(kTile) void k_targets_from_local(Dom<T> D, int leve
       const double sh = bh - ah * ah * inv, su = bu - au * au * inv, sv = bv - av * av * inv;
       jloc = sh * D.isb2[0] + su * D.isb2[1] + sv * D.isb2[2];
     }
-    // the level's tile sum, added in level order (as one launch per level
-    // adds them), so both ways give the same bits
-    __syncthreads();                        // red may still be read from the previous level
-    const double tot = block_sum2(jloc, red);
-    if (threadIdx.x == 0) acc = (n == n0) ? tot : acc + tot;
+    // the level's sum, added in level order (as one launch per level adds
+    // them), so both ways give the same bits; where one other box covers
+    // every cell of the wave there is no spread to sum
+    if (__any(jloc != 0.0)) acc += stencil::wave_sum(jloc);
   }
-  if (threadIdx.x == 0) jc[w] = (n0 == 0) ? acc : jc[w] + acc;
+  double* J = jc + (int64_t(w) * kWaves + (threadIdx.x >> 6)) * split + n0 % split;
+  if (lane == 0) *J = (n0 < split) ? acc : *J + acc;
 }
 
-// one wave per box: lane l sums tiles l, l + 64, ... in order, then a
+// one wave per box: lane l sums the partial sums l, l + 64, ... in order, then a
 // butterfly whose pairs add the same two values in either order
 __global__ __launch_bounds__(256) void k_reduce_jconst(const SubDev* __restrict__ subs, int nsub,
-                                                       const double* __restrict__ jc, double half_mu,
-                                                       double* __restrict__ jconst) {
+                                                       const double* __restrict__ jc, int split,
+                                                       double half_mu, double* __restrict__ jconst) {
   const int s = int(blockIdx.x) * 4 + int(threadIdx.x >> 6);
   if (s >= nsub) return;                    // uniform over the wave
   const SubDev S = subs[s];
   double acc = 0.0;
-  for (int t = int(threadIdx.x & 63); t < S.ntile; t += 64) acc += jc[S.tile0 + t];
+  const int nz = S.nlev < split ? S.nlev : split;        // sums that hold levels
+  for (int t = int(threadIdx.x & 63); t < S.ntile * kWaves * nz; t += 64)
+    acc += jc[(int64_t(S.tile0) * kWaves + t / nz) * split + t % nz];
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
   if ((threadIdx.x & 63) == 0) jconst[s] = half_mu * acc;
 }
@@ -315,25 +332,25 @@ void launch_from_global(const Dom<T>& D, const double* bg, int64_t gplane, doubl
 template <typename T>
 void launch_ring_from_global(const Dom<T>& D, int nsub, int ring_blocks, const double* bg,
                              int64_t gplane, hipStream_t st) {
-  hipLaunchKernelGGL(k_ring_from_global<T>, dim3(nsub, ring_blocks), dim3(256), 0, st, D, bg,
+  hipLaunchKernelGGL(k_ring_from_global<T>, dim3(nsub, ring_blocks, kRingSplit), dim3(256), 0, st, D, bg,
                      gplane);
 }
 template <typename T>
 void launch_ring_from_local(const Dom<T>& D, int box_base, int nbox, int ring_blocks, int level,
                             hipStream_t st) {
-  hipLaunchKernelGGL(k_ring_from_local<T>, dim3(nbox, ring_blocks), dim3(256), 0, st, D, box_base,
-                     level);
+  hipLaunchKernelGGL(k_ring_from_local<T>, dim3(nbox, ring_blocks, level < 0 ? kRingSplit : 1), dim3(256), 0,
+                     st, D, box_base, level);
 }
 template <typename T>
-void launch_targets_from_local(const Dom<T>& D, int level, int tile_base, int ntiles, double* jc,
-                               hipStream_t st) {
-  hipLaunchKernelGGL(k_targets_from_local<T>, dim3(ntiles), dim3(kTile), 0, st, D, level, tile_base,
-                     jc);
+void launch_targets_from_local(const Dom<T>& D, int level, int tile_base, int ntiles, int split,
+                               double* jc, hipStream_t st) {
+  hipLaunchKernelGGL(k_targets_from_local<T>, dim3(ntiles, level < 0 ? split : 1), dim3(kTile), 0, st, D,
+                     level, tile_base, split, jc);
 }
-void launch_reduce_jconst(const SubDev* subs, int nsub, const double* jc, double half_mu,
-                          double* jconst, hipStream_t st) {
-  hipLaunchKernelGGL(k_reduce_jconst, dim3((nsub + 3) / 4), dim3(256), 0, st, subs, nsub, jc, half_mu,
-                     jconst);
+void launch_reduce_jconst(const SubDev* subs, int nsub, const double* jc, int split,
+                          double half_mu, double* jconst, hipStream_t st) {
+  hipLaunchKernelGGL(k_reduce_jconst, dim3((nsub + 3) / 4), dim3(256), 0, st, subs, nsub, jc, split,
+                     half_mu, jconst);
 }
 template <typename T>
 void launch_gather(const Dom<T>& D, int nspace, int ntime, int level, int64_t ncell,
@@ -357,7 +374,8 @@ void launch_fill(double* p, int64_t n, double v, hipStream_t st) {
   template void launch_ring_from_global<T>(const Dom<T>&, int, int, const double*, int64_t,      \
                                            hipStream_t);                                         \
   template void launch_ring_from_local<T>(const Dom<T>&, int, int, int, int, hipStream_t);       \
-  template void launch_targets_from_local<T>(const Dom<T>&, int, int, int, double*, hipStream_t); \
+  template void launch_targets_from_local<T>(const Dom<T>&, int, int, int, int, double*,           \
+                                             hipStream_t);                                 \
   template void launch_gather<T>(const Dom<T>&, int, int, int, int64_t, const int32_t*,          \
                                  const int32_t*, double*, hipStream_t);
 DD4DVAR_INST(float)

@@ -45,7 +45,7 @@ struct SubDev {
   int32_t span, pole_s, pole_n;
   int32_t ncell, nring, tile0, ntile;
   int32_t nbr0, nbr1;        // neighbour list range
-  int32_t pad_;
+  int32_t perm0;             // first entry of the box's piece in Dom::perm
   int64_t traj_off;          // packed FP64 trajectory and overlap-target offset
   int64_t ring_off;          // ring arena offset, level stride 3*nring
   int64_t adj_off;           // adjoint arena offset: 3 slots x 3 x ncell
@@ -78,6 +78,8 @@ struct Dom {
   const RowCoef<T>* rows;    // [nlat]
   const T* cosx;             // [nlat+2]: cos of rows -1..nlat (pole-mapped)
   const uint8_t* cover;      // spatial coverage count per box cell
+  const int32_t* perm;       // per spatial piece, its box cells: those that other boxes of the
+                             // interval cover first, like sets of boxes together
   const int32_t* tcount;     // temporal coverage count per global level
   const int32_t* obs_ptr;    // CSR over the (tile, level) bins, keyed by obs_key
   const int32_t* obs_code;   // local cell * 4 + field

@@ -33,10 +33,10 @@ template <typename T>
 void launch_ring_from_local(const Dom<T>& D, int box_base, int nbox, int ring_blocks, int level,
                             hipStream_t st);
 template <typename T>
-void launch_targets_from_local(const Dom<T>& D, int level, int tile_base, int ntiles, double* jc,
-                               hipStream_t st);
-void launch_reduce_jconst(const SubDev* subs, int nsub, const double* jc, double half_mu,
-                          double* jconst, hipStream_t st);
+void launch_targets_from_local(const Dom<T>& D, int level, int tile_base, int ntiles, int split,
+                               double* jc, hipStream_t st);
+void launch_reduce_jconst(const SubDev* subs, int nsub, const double* jc, int split,
+                          double half_mu, double* jconst, hipStream_t st);
 template <typename T>
 void launch_gather(const Dom<T>& D, int nspace, int ntime, int level, int64_t ncell,
                    const int32_t* cptr, const int32_t* cpiece, double* out, hipStream_t st);

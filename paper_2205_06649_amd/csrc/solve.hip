@@ -346,7 +346,8 @@ __global__ __launch_bounds__(64 * kBoxWaves) void k_lb_step_s(LbState L) {
 // registers (16 entries per thread) and every dot product stays in the
 // workgroup: 2 launches per iteration and round instead of 2 m + 5 and 4, whose
 // gaps and starts were the time (64 boxes of 8640 entries, m = 8: direction
-// and trial 19 launches, 196 us, -> 1 of 24 us; Armijo round 37 -> 10 us).
+// and trial 20 launches, 270 us with their gaps, -> 1 of 43 us; Armijo round 36
+// -> 19 us).
 // Sums: per thread over its entries, the wave's shuffle tree, the waves in
 // order.
 namespace {
