@@ -78,6 +78,10 @@ struct dd4dvar_ctx {
   int32_t *cptr = nullptr, *cpiece = nullptr;
   int32_t* d_ids = nullptr;
   uint32_t* nonfinite = nullptr;
+  // host memory that a solve's kernels and copies write: the counters of its
+  // rounds, then scalars of the boxes (allocated by the first solve)
+  SolveNote* note = nullptr;
+  uint32_t note_seq = 0;
   const uint8_t* eval_mask = nullptr;   // subdomains evaluated by the sweeps (null = all)
   bool box_ok = false;                  // persistent per-box sweeps possible
   size_t box_lds = 0;
@@ -160,6 +164,7 @@ struct dd4dvar_ctx {
       (void)hipGraphDestroy(g.graph);
     }
     if (cap_stream) (void)hipStreamDestroy(cap_stream);
+    if (note) (void)hipHostFree(note);
   }
 };
 
@@ -717,7 +722,7 @@ void background_impl(dd4dvar_ctx* c, hipStream_t st) {
                        hipMemcpyHostToDevice, st), "upload xb0");
     global_forward(c, x0, bg, st);
     Dom<T> D = local_dom<T>(c);
-    for (int n = 0; n < c->maxlev; ++n) launch_from_global<T>(D, bg, ncell, c->xb, n, c->ntiles, st);
+    launch_from_global<T>(D, bg, ncell, c->xb, c->maxlev, c->ntiles, st);
     launch_ring_from_global<T>(D, c->nsub, c->ring_blocks, bg, ncell, st);
     launch_fill(c->jconst, c->nsub, 0.0, st);
     chk(hipGetLastError(), "background launch");
@@ -1806,6 +1811,20 @@ P read1(const P* d, hipStream_t st) {
   return h;
 }
 
+// The counters of the round that the last lb_direction_next notes, as soon as
+// that kernel has written them.
+int2 read_note(dd4dvar_ctx* c, hipStream_t st) {
+  const auto noted = [&] { return __atomic_load_n(&c->note->seq, __ATOMIC_ACQUIRE) == c->note_seq; };
+  for (unsigned turn = 1; !noted(); ++turn) {
+    if (turn % 1024) continue;
+    const hipError_t e = hipStreamQuery(st);       // (an error, or all done: the wait ends)
+    if (e == hipErrorNotReady) continue;
+    chk(e, "round");
+    if (!noted()) throw DevError{DD4DVAR_E_DEVICE, "a round of the local solves left no counters"};
+  }
+  return make_int2(c->note->searching, c->note->iterating);
+}
+
 // lo (nullable, Gauss-Newton only): an FP32-state context of the same plan
 // whose sweeps supply the normal-matrix products, linearized about its own
 // trajectory of the current iterate; c evaluates J and the gradient
@@ -1921,6 +1940,22 @@ dd4dvar_status solve_typed(dd4dvar_ctx* c, const dd4dvar_solve_opts* o, const do
     }
   }
   double* xa_dev = B.get<double>(size_t(3) * c->plan.model.nlat * c->plan.model.nlon);
+  // scalars of the boxes on the host (copies to it need no wait of their own)
+  if (!c->note)
+    chk(hipHostMalloc(reinterpret_cast<void**>(&c->note), 64 + nsub * (5 * sizeof(double) + sizeof(int32_t))),
+        "hipHostMalloc solve");
+  double* box_h[5];
+  for (int k = 0; k < 5; ++k)
+    box_h[k] = reinterpret_cast<double*>(reinterpret_cast<char*>(c->note) + 64) + int64_t(k) * nsub;
+  int32_t* iters_h = reinterpret_cast<int32_t*>(box_h[4] + nsub);
+  c->note->seq = c->note_seq;
+  struct Event {
+    hipEvent_t e = nullptr;
+    ~Event() {
+      if (e) (void)hipEventDestroy(e);
+    }
+  } reads;
+  chk(hipEventCreateWithFlags(&reads.e, hipEventDisableTiming), "event");
 
   struct MaskReset {
     dd4dvar_ctx *c, *lo;
@@ -1941,7 +1976,6 @@ dd4dvar_status solve_typed(dd4dvar_ctx* c, const dd4dvar_solve_opts* o, const do
   }
   int evals = 0, outer = 0, lbfgs_iters = 0, products = 0;
   bool met = false;
-  std::vector<int32_t> iters_h(nsub);
   for (outer = 1; outer <= o->max_outer; ++outer) {
     // local solves, all subdomains at once
     c->eval_mask = nullptr;
@@ -1997,18 +2031,19 @@ dd4dvar_status solve_typed(dd4dvar_ctx* c, const dd4dvar_solve_opts* o, const do
       chk(hipMemsetAsync(L.pending, 0, 4 * sizeof(int32_t), st), "memset");
       lb_count(L, st);
       int2 left = make_int2(0, read1(L.pending, st));      // boxes searching, boxes iterating
-      if (left.y) chk(hipMemsetAsync(L.pending, 0, 4 * sizeof(int32_t), st), "memset");
-      for (int round = 0; left.y > 0;) {
+      if (left.y) {
+        chk(hipMemsetAsync(L.pending, 0, 4 * sizeof(int32_t), st), "memset");
         lb_direction_one(L, st);
-        do {
-          c->eval_mask = L.ls;
-          cost_grad_impl<T>(c, nullptr, L.xphys, L.Jt, L.gradx, st);
-          c->eval_mask = nullptr;
-          ++evals;
-          lb_armijo_one(L, round, st);
-          left = read1(reinterpret_cast<const int2*>(L.pending + 2 * (round & 1)), st);
-          ++round;
-        } while (left.x > 0);
+      }
+      for (int round = 0; left.y > 0; ++round) {
+        c->eval_mask = L.ls;
+        cost_grad_impl<T>(c, nullptr, L.xphys, L.Jt, L.gradx, st);
+        c->eval_mask = nullptr;
+        ++evals;
+        lb_armijo_one(L, round, st);
+        // a new direction where no box searches any more
+        lb_direction_next(L, round, c->note, ++c->note_seq, st);
+        left = read_note(c, st);
       }
     } else {
       lb_start(L, st);
@@ -2029,19 +2064,17 @@ dd4dvar_status solve_typed(dd4dvar_ctx* c, const dd4dvar_solve_opts* o, const do
         }
       }
     }
-    chk(hipMemcpyAsync(iters_h.data(), L.iters, nsub * sizeof(int32_t), hipMemcpyDeviceToHost, st),
-        "read iters");
+    chk(hipMemcpyAsync(iters_h, L.iters, nsub * sizeof(int32_t), hipMemcpyDeviceToHost, st), "read iters");
     lb_step(L, st);
-    std::vector<double> step(nsub);
-    chk(hipMemcpyAsync(step.data(), L.step, nsub * sizeof(double), hipMemcpyDeviceToHost, st),
-        "read step");
-    chk(hipStreamSynchronize(st), "sync");
-    lbfgs_iters += *std::max_element(iters_h.begin(), iters_h.end());
+    chk(hipMemcpyAsync(box_h[0], L.step, nsub * sizeof(double), hipMemcpyDeviceToHost, st), "read step");
+    chk(hipEventRecord(reads.e, st), "event");
     // exchange (Alg. 1): integrate the new controls, refresh rings and targets
     lb_to_x(L, 0, 0, st);
     exchange_impl<T>(c, L.xphys, st);
     if (lo) exchange_impl<float>(lo, L.xphys, st);
-    const double mx = *std::max_element(step.begin(), step.end());
+    chk(hipEventSynchronize(reads.e), "sync");
+    lbfgs_iters += *std::max_element(iters_h, iters_h + nsub);
+    const double mx = *std::max_element(box_h[0], box_h[0] + nsub);
     if (!std::isfinite(mx)) {
       c->err = "non-finite iterate in the local solves";
       return DD4DVAR_E_NONFINITE;
@@ -2057,20 +2090,21 @@ dd4dvar_status solve_typed(dd4dvar_ctx* c, const dd4dvar_solve_opts* o, const do
   launch_gather<T>(local_dom<T>(c), c->plan.nspace, c->plan.ntime, 0, ncell, c->cptr, c->cpiece,
                    xa_dev, st);
   chk(hipGetLastError(), "gather launch");
-  chk(hipMemcpyAsync(xa_host, xa_dev, size_t(3 * ncell) * sizeof(double), hipMemcpyDeviceToHost, st),
-      "copy analysis");
   if (x_out)
     chk(hipMemcpyAsync(x_out, L.xphys, size_t(N) * sizeof(double), hipMemcpyDeviceToDevice, st),
         "copy controls");
-  std::vector<double> J(nsub), gn(nsub), g0(nsub);
-  chk(hipMemcpyAsync(J.data(), L.J, nsub * sizeof(double), hipMemcpyDeviceToHost, st), "read J");
-  chk(hipMemcpyAsync(gn.data(), L.gnorm, nsub * sizeof(double), hipMemcpyDeviceToHost, st), "read g");
-  chk(hipMemcpyAsync(g0.data(), L.g0norm, nsub * sizeof(double), hipMemcpyDeviceToHost, st), "read g0");
-  std::vector<double> rlo(nsub, 0.0), rhi(nsub, 0.0);
+  double *J = box_h[0], *gn = box_h[1], *g0 = box_h[2], *rlo = box_h[3], *rhi = box_h[4];
+  chk(hipMemcpyAsync(J, L.J, nsub * sizeof(double), hipMemcpyDeviceToHost, st), "read J");
+  chk(hipMemcpyAsync(gn, L.gnorm, nsub * sizeof(double), hipMemcpyDeviceToHost, st), "read g");
+  chk(hipMemcpyAsync(g0, L.g0norm, nsub * sizeof(double), hipMemcpyDeviceToHost, st), "read g0");
   if (use_gn && G.krylov == 1) {
-    chk(hipMemcpyAsync(rlo.data(), G.ritz_lo, nsub * sizeof(double), hipMemcpyDeviceToHost, st), "read ritz");
-    chk(hipMemcpyAsync(rhi.data(), G.ritz_hi, nsub * sizeof(double), hipMemcpyDeviceToHost, st), "read ritz");
+    chk(hipMemcpyAsync(rlo, G.ritz_lo, nsub * sizeof(double), hipMemcpyDeviceToHost, st), "read ritz");
+    chk(hipMemcpyAsync(rhi, G.ritz_hi, nsub * sizeof(double), hipMemcpyDeviceToHost, st), "read ritz");
+  } else {
+    std::fill(rlo, rlo + 2 * nsub, 0.0);
   }
+  chk(hipMemcpyAsync(xa_host, xa_dev, size_t(3 * ncell) * sizeof(double), hipMemcpyDeviceToHost, st),
+      "copy analysis");
   chk(hipStreamSynchronize(st), "sync");
   if (rep) {
     rep->outer_iters = outer;

@@ -34,8 +34,8 @@ constexpr int kWaves = kTile / 64;         // partial sums per tile
 // h is stored as h - h_ref
 template <typename T>
 __global__ __launch_bounds__(kTile) void k_from_global(Dom<T> D, const double* __restrict__ bg,
-                                                       int64_t gplane, double* __restrict__ xb,
-                                                       int n) {
+                                                       int64_t gplane, double* __restrict__ xb) {
+  const int n = blockIdx.y;
   const int2 wt = D.tiles[xcd_tile(blockIdx.x, gridDim.x)];
   const SubDev S = D.subs[wt.x];
   if (n >= S.nlev) return;
@@ -324,9 +324,9 @@ __global__ void k_fill(double* p, int64_t n, double v) {
 
 // ---- launchers --------------------------------------------------------------
 template <typename T>
-void launch_from_global(const Dom<T>& D, const double* bg, int64_t gplane, double* xb, int level,
+void launch_from_global(const Dom<T>& D, const double* bg, int64_t gplane, double* xb, int nlev,
                         int ntiles, hipStream_t st) {
-  hipLaunchKernelGGL(k_from_global<T>, dim3(ntiles), dim3(kTile), 0, st, D, bg, gplane, xb, level);
+  hipLaunchKernelGGL(k_from_global<T>, dim3(ntiles, nlev), dim3(kTile), 0, st, D, bg, gplane, xb);
 }
 // grid.y covers the largest ring; positions beyond a box's own ring exit
 template <typename T>

@@ -25,7 +25,7 @@ void launch_traj_out(const Dom<T>& D, double* out, int tile_base, int ntiles, in
 // exchange.hip
 template <typename T>
 void launch_from_global(const Dom<T>& D, const double* bg, int64_t gplane, double* xb,
-                        int level, int ntiles, hipStream_t st);
+                        int nlev, int ntiles, hipStream_t st);
 template <typename T>
 void launch_ring_from_global(const Dom<T>& D, int nsub, int ring_blocks, const double* bg,
                              int64_t gplane, hipStream_t st);

@@ -11,6 +11,13 @@ namespace dd4dvar {
 
 constexpr int kMaxPairs = 32;
 
+// What the host reads of a running solve (host memory, written by the device):
+// boxes searching and iterating after the round that seq names.
+struct SolveNote {
+  int32_t searching, iterating;
+  uint32_t seq;
+};
+
 struct LbState {
   const SubDev* subs;
   int nsub, m, max_iter, max_ls;
@@ -44,9 +51,13 @@ void lb_count(const LbState& L, hipStream_t st);
 // where every box is one part of at most kPartLen entries: direction and first
 // trial in one launch; an Armijo round (accept or halve and try again, pair,
 // move) in one, which leaves {boxes searching, boxes iterating} in the pair of
-// counters of its round and clears the other pair (clear both before round 0)
+// counters of its round and clears the other pair (clear both before round 0).
+// lb_direction_next is launched behind a round without waiting for it: it
+// notes the round's counters for the host and does nothing more while boxes
+// are still searching.
 bool lb_one_part(const LbState& L);
 void lb_direction_one(const LbState& L, hipStream_t st);
+void lb_direction_next(const LbState& L, int round, SolveNote* note, uint32_t seq, hipStream_t st);
 void lb_armijo_one(const LbState& L, int round, hipStream_t st);
 void lb_step(const LbState& L, hipStream_t st);
 

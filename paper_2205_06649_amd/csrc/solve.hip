@@ -380,9 +380,23 @@ __device__ __forceinline__ double one_sigma(const LbState& L, int ncell, int i) 
 }
 }  // namespace
 
-__global__ __launch_bounds__(kOneB) void k_lb_dir_one(LbState L) {
+// With counters of a round (count): the host learns them at once, in memory of
+// its own, and has this kernel's time to launch the next evaluation; a copy
+// and a wait for it left the device idle for 45 us a round (28 rounds, a
+// tenth of a solve of 32 boxes of 2,880 cells).
+__global__ __launch_bounds__(kOneB) void k_lb_dir_one(LbState L, const int32_t* count, SolveNote* note,
+                                                      uint32_t seq) {
   __shared__ double sh[kOneB / 64];
   __shared__ double alph[kMaxPairs];
+  if (count) {
+    const int searching = count[0];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      note->searching = searching;
+      note->iterating = count[1];
+      __hip_atomic_store(&note->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    if (searching > 0) return;             // (uniform)
+  }
   const Part pt = L.P.part[blockIdx.x];
   const int s = pt.box;
   if (L.status[s] != 0) return;
@@ -572,7 +586,11 @@ void lb_armijo(const LbState& L, hipStream_t st) {
 }
 bool lb_one_part(const LbState& L) { return L.P.nparts == L.nsub && L.P.len <= kPartLen; }
 void lb_direction_one(const LbState& L, hipStream_t st) {
-  hipLaunchKernelGGL(k_lb_dir_one, parts_grid(L), dim3(kOneB), 0, st, L);
+  hipLaunchKernelGGL(k_lb_dir_one, parts_grid(L), dim3(kOneB), 0, st, L, nullptr, nullptr, 0u);
+}
+void lb_direction_next(const LbState& L, int round, SolveNote* note, uint32_t seq, hipStream_t st) {
+  hipLaunchKernelGGL(k_lb_dir_one, parts_grid(L), dim3(kOneB), 0, st, L, L.pending + 2 * (round & 1), note,
+                     seq);
 }
 void lb_armijo_one(const LbState& L, int round, hipStream_t st) {
   hipLaunchKernelGGL(k_lb_armijo_one, parts_grid(L), dim3(kOneB), 0, st, L, L.pending + 2 * (round & 1),
