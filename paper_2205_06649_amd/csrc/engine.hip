@@ -235,6 +235,8 @@ void build_parts(dd4dvar_ctx* c, int len, hipStream_t st) {
   c->parts.box = upload(c, boxp, st);
   c->parts.nparts = int(parts.size());
   c->parts.len = len;
+  c->parts.longest = 0;
+  for (const Part& q : parts) c->parts.longest = std::max(c->parts.longest, q.hi - q.lo);
   c->parts.acc = dalloc<double>(c, size_t(kPartSlots) * parts.size());
   c->part_len = len;
   // the host vectors are pageable: the copies complete before they go

@@ -29,6 +29,7 @@ struct PartMap {
   const int2* box;    // per box: (first part, number of parts)
   int nparts;
   int len;            // entries of a part (a box's last one has the rest)
+  int longest;        // entries of the longest part
   double* acc;        // [kPartSlots][nparts] partial sums
 };
 

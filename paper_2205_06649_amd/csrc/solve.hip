@@ -346,13 +346,17 @@ __global__ __launch_bounds__(64 * kBoxWaves) void k_lb_step_s(LbState L) {
 // registers (16 entries per thread) and every dot product stays in the
 // workgroup: 2 launches per iteration and round instead of 2 m + 5 and 4, whose
 // gaps and starts were the time (64 boxes of 8640 entries, m = 8: direction
-// and trial 20 launches, 270 us with their gaps, -> 1 of 43 us; Armijo round 36
-// -> 19 us).
+// and trial 20 launches, 270 us with their gaps, -> 1; Armijo round 36 us with
+// its gaps).
+// A thread's loads of a vector are issued together (entries past the box's own
+// load its last one and are not used: a branch around each load made them
+// wait for one another), and while a dot product is summed the next pair's
+// vectors are under way: direction 47 -> 40 us, Armijo round 20 -> 14 us (32
+// boxes of 8640 entries; a unit's 64 B per clock from L2 take 18 of the 40).
 // Sums: per thread over its entries, the wave's shuffle tree, the waves in
 // order.
 namespace {
 constexpr int kOneB = 1024;                // threads per box
-constexpr int kOneE = kPartLen / kOneB;    // entries per thread
 
 // sum over the workgroup, in every thread
 __device__ __forceinline__ double one_sum(double v, double* sh) {
@@ -365,12 +369,31 @@ __device__ __forceinline__ double one_sum(double v, double* sh) {
   for (int i = 0; i < kOneB / 64; ++i) r += sh[i];
   return r;
 }
-// f(entry in registers, entry of the box) over the thread's entries below n
-template <typename F>
-__device__ __forceinline__ void one_each(int n, F f) {
+// entry i by a 32-bit offset from the vector's (uniform) start
+__device__ __forceinline__ double& one_at(double* v, int i) {
+  return *reinterpret_cast<double*>(reinterpret_cast<char*>(v) + uint32_t(i) * uint32_t(sizeof(double)));
+}
+// the thread's first entry, recomputed where it is used (offsets kept from one
+// vector to the next would spill)
+__device__ __forceinline__ int one_first() {
+  int t = int(threadIdx.x);
+  asm volatile("" : "+v"(t));
+  return t;
+}
+// v into r: the thread's E entries of a box of n
+template <int E>
+__device__ __forceinline__ void one_load(double (&r)[E], const double* v, int n) {
+  const int t = one_first();
 #pragma unroll
-  for (int j = 0; j < kOneE; ++j) {
-    const int i = int(threadIdx.x) + j * kOneB;
+  for (int j = 0; j < E; ++j) r[j] = one_at(const_cast<double*>(v), min(t + j * kOneB, n - 1));
+}
+// f(entry in registers, entry of the box) over the thread's entries below n
+template <int E, typename F>
+__device__ __forceinline__ void one_each(int n, F f) {
+  const int t = one_first();
+#pragma unroll
+  for (int j = 0; j < E; ++j) {
+    const int i = t + j * kOneB;
     if (i < n) f(j, i);
   }
 }
@@ -384,6 +407,7 @@ __device__ __forceinline__ double one_sigma(const LbState& L, int ncell, int i) 
 // its own, and has this kernel's time to launch the next evaluation; a copy
 // and a wait for it left the device idle for 45 us a round (28 rounds, a
 // tenth of a solve of 32 boxes of 2,880 cells).
+template <int E>
 __global__ __launch_bounds__(kOneB) void k_lb_dir_one(LbState L, const int32_t* count, SolveNote* note,
                                                       uint32_t seq) {
   __shared__ double sh[kOneB / 64];
@@ -402,60 +426,71 @@ __global__ __launch_bounds__(kOneB) void k_lb_dir_one(LbState L, const int32_t* 
   if (L.status[s] != 0) return;
   const int n = pt.hi, np = L.npairs[s];
   const double* g = L.g + pt.off;
-  double q[kOneE];
-  double acc = 0.0;
+  const auto pair_s = [&](int k) { return L.S + int64_t(pair_slot(L, s, k)) * L.N + pt.off; };
+  const auto pair_y = [&](int k) { return L.Y + int64_t(pair_slot(L, s, k)) * L.N + pt.off; };
+  const auto pair_rho = [&](int k) { return L.rho[int64_t(pair_slot(L, s, k)) * L.nsub + s]; };
+  const auto dot = [&](const double (&u)[E], const double (&v)[E]) {
+    double acc = 0.0;
+    one_each<E>(n, [&](int j, int) { acc += u[j] * v[j]; });
+    return acc;
+  };
+  constexpr bool ahead = E <= 8;           // registers for both vectors of a pair
+  double q[E], gd = 0.0;
   if (np > 0) {
-    one_each(n, [&](int j, int i) { q[j] = g[i]; });
+    double sv[E], yv[E];
+    one_load(q, g, n);
+    one_load(sv, pair_s(0), n);
+    if (ahead) one_load(yv, pair_y(0), n);
     for (int k = 0; k < np; ++k) {         // newest pair first
-      const int slot = pair_slot(L, s, k);
-      const double* sv = L.S + int64_t(slot) * L.N + pt.off;
-      const double* yv = L.Y + int64_t(slot) * L.N + pt.off;
-      acc = 0.0;
-      one_each(n, [&](int j, int i) { acc += sv[i] * q[j]; });
-      const double a = L.rho[int64_t(slot) * L.nsub + s] * one_sum(acc, sh);
+      if (!ahead && k > 0) one_load(sv, pair_s(k), n);
+      const double acc = dot(sv, q), rho = pair_rho(k);
+      if (!ahead) one_load(yv, pair_y(k), n);
+      else if (k + 1 < np) one_load(sv, pair_s(k + 1), n);
+      const double a = rho * one_sum(acc, sh);
       if (threadIdx.x == 0) alph[k] = a;
-      one_each(n, [&](int j, int i) { q[j] -= a * yv[i]; });
+#pragma unroll
+      for (int j = 0; j < E; ++j) q[j] -= a * yv[j];
+      if (ahead && k + 1 < np) one_load(yv, pair_y(k + 1), n);
     }
     const double gamma = L.gamma[s];
-    one_each(n, [&](int j, int) { q[j] *= gamma; });
-    for (int k = np - 1; k >= 0; --k) {
-      const int slot = pair_slot(L, s, k);
-      const double* sv = L.S + int64_t(slot) * L.N + pt.off;
-      const double* yv = L.Y + int64_t(slot) * L.N + pt.off;
-      acc = 0.0;
-      one_each(n, [&](int j, int i) { acc += yv[i] * q[j]; });
-      const double b = L.rho[int64_t(slot) * L.nsub + s] * one_sum(acc, sh);
+#pragma unroll
+    for (int j = 0; j < E; ++j) q[j] *= gamma;
+    for (int k = np - 1; k >= 0; --k) {    // (the oldest pair, or its y, is still here)
+      if (!ahead && k + 1 < np) one_load(yv, pair_y(k), n);
+      const double acc = dot(yv, q), rho = pair_rho(k);
+      if (!ahead) one_load(sv, pair_s(k), n);
+      else if (k > 0) one_load(yv, pair_y(k - 1), n);
+      const double b = rho * one_sum(acc, sh);
       const double ab = alph[k] - b;       // (written before one_sum's barriers)
-      one_each(n, [&](int j, int i) { q[j] += sv[i] * ab; });
+#pragma unroll
+      for (int j = 0; j < E; ++j) q[j] += sv[j] * ab;
+      if (ahead && k > 0) one_load(sv, pair_s(k - 1), n);
     }
-    acc = 0.0;
-    one_each(n, [&](int j, int i) {
-      q[j] = -q[j];
-      acc += g[i] * q[j];
-    });
+    one_load(sv, g, n);
+#pragma unroll
+    for (int j = 0; j < E; ++j) q[j] = -q[j];
+    gd = one_sum(dot(sv, q), sh);
   }
-  double gd = np > 0 ? one_sum(acc, sh) : 0.0;
   if (!(gd < 0.0)) {                       // no pairs, or not a descent direction
-    acc = 0.0;
-    one_each(n, [&](int j, int i) {
-      q[j] = -g[i];
-      acc += q[j] * q[j];
-    });
-    gd = -one_sum(acc, sh);
+    one_load(q, g, n);
+#pragma unroll
+    for (int j = 0; j < E; ++j) q[j] = -q[j];
+    gd = -one_sum(dot(q, q), sh);
   }
   // a full step could not show a decrease above the noise floor of J
   const bool flat = -gd <= L.jnoise * fabs(L.J[s]);
-  const double* xi = L.xi + pt.off;
-  const double* xb = L.xb + pt.off;
   double* d = L.d + pt.off;
   double* xt = L.xt + pt.off;
   double* x = L.xphys + pt.off;
-  one_each(n, [&](int j, int i) {
-    d[i] = q[j];
+  double xi[E], xb[E];
+  one_load(xi, L.xi + pt.off, n);
+  one_load(xb, L.xb + pt.off, n);
+  one_each<E>(n, [&](int j, int i) {
+    one_at(d, i) = q[j];
     if (flat) return;
-    const double v = xi[i] + q[j];
-    xt[i] = v;
-    x[i] = xb[i] + one_sigma(L, pt.ncell, i) * v;
+    const double v = xi[j] + q[j];
+    one_at(xt, i) = v;
+    one_at(x, i) = xb[j] + one_sigma(L, pt.ncell, i) * v;
   });
   __syncthreads();                         // every thread has read J
   if (threadIdx.x != 0) return;
@@ -468,8 +503,9 @@ __global__ __launch_bounds__(kOneB) void k_lb_dir_one(LbState L, const int32_t* 
 
 // Armijo test of the evaluated trial.  count[0] += boxes still searching,
 // count[1] += boxes still iterating; the other pair of counters is cleared.
+template <int E>
 __global__ __launch_bounds__(kOneB) void k_lb_armijo_one(LbState L, int32_t* count, int32_t* clear) {
-  __shared__ double sh[kOneB / 64];
+  __shared__ double sh[4][kOneB / 64];
   if (blockIdx.x == 0 && threadIdx.x < 2) clear[threadIdx.x] = 0;
   const Part pt = L.P.part[blockIdx.x];
   const int s = pt.box, n = pt.hi;
@@ -488,13 +524,15 @@ __global__ __launch_bounds__(kOneB) void k_lb_armijo_one(LbState L, int32_t* cou
     const double a = 0.5 * alpha;
     const bool stop = t >= L.max_ls || a * fabs(gd) <= L.jnoise * fabs(J);
     if (!stop) {
-      const double* d = L.d + pt.off;
-      const double* xb = L.xb + pt.off;
+      double xv[E], dv[E], bv[E];
+      one_load(xv, xi, n);
+      one_load(dv, L.d + pt.off, n);
+      one_load(bv, L.xb + pt.off, n);
       double* x = L.xphys + pt.off;
-      one_each(n, [&](int, int i) {
-        const double v = xi[i] + a * d[i];
-        xt[i] = v;
-        x[i] = xb[i] + one_sigma(L, pt.ncell, i) * v;
+      one_each<E>(n, [&](int j, int i) {
+        const double v = xv[j] + a * dv[j];
+        one_at(xt, i) = v;
+        one_at(x, i) = bv[j] + one_sigma(L, pt.ncell, i) * v;
       });
     }
     __syncthreads();                       // every thread has read the scalars
@@ -512,33 +550,50 @@ __global__ __launch_bounds__(kOneB) void k_lb_armijo_one(LbState L, int32_t* cou
   }
   const int slot = L.head[s], np = L.npairs[s], it = L.iters[s] + 1;
   const double g0 = L.g0norm[s];
-  double sy = 0, yy = 0, ss = 0, gg = 0;
-  one_each(n, [&](int, int i) {
-    const double gn = one_sigma(L, pt.ncell, i) * gx[i];
-    const double a = xt[i] - xi[i];
-    const double b = gn - g[i];
-    sy += a * b;
-    yy += b * b;
-    ss += a * a;
-    gg += gn * gn;
-  });
-  sy = one_sum(sy, sh);
-  yy = one_sum(yy, sh);
-  ss = one_sum(ss, sh);
-  gg = one_sum(gg, sh);
+  // the pair stays in registers until it is known to be kept
+  double sum[4] = {0.0, 0.0, 0.0, 0.0}, av[E], bv[E];      // sy, yy, ss, gg
+  {
+    double to[E];
+    one_load(av, xi, n);
+    one_load(to, xt, n);
+    one_each<E>(n, [&](int j, int i) {
+      av[j] = to[j] - av[j];
+      sum[2] += av[j] * av[j];
+      one_at(xi, i) = to[j];
+    });
+    one_load(bv, g, n);
+    one_load(to, gx, n);
+    one_each<E>(n, [&](int j, int i) {
+      const double gn = one_sigma(L, pt.ncell, i) * to[j];
+      bv[j] = gn - bv[j];
+      sum[0] += av[j] * bv[j];
+      sum[1] += bv[j] * bv[j];
+      sum[3] += gn * gn;
+      one_at(g, i) = gn;
+    });
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    sum[k] = stencil::wave_sum(sum[k]);
+    if ((threadIdx.x & 63) == 0) sh[k][threadIdx.x >> 6] = sum[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    sum[k] = 0.0;
+    for (int i = 0; i < kOneB / 64; ++i) sum[k] += sh[k][i];
+  }
+  const double sy = sum[0], yy = sum[1], ss = sum[2], gg = sum[3];
   const bool keep = sy > 1e-12 * sqrt(ss) * sqrt(yy);
-  double* sv = L.S + int64_t(slot) * L.N + pt.off;
-  double* yv = L.Y + int64_t(slot) * L.N + pt.off;
-  one_each(n, [&](int, int i) {
-    const double gn = one_sigma(L, pt.ncell, i) * gx[i];
-    if (keep) {
-      sv[i] = xt[i] - xi[i];
-      yv[i] = gn - g[i];
-    }
-    xi[i] = xt[i];
-    g[i] = gn;
-  });
-  if (threadIdx.x != 0) return;            // (the sums' barriers: every thread has read the scalars)
+  if (keep) {
+    double* sv = L.S + int64_t(slot) * L.N + pt.off;
+    double* yv = L.Y + int64_t(slot) * L.N + pt.off;
+    one_each<E>(n, [&](int j, int i) {
+      one_at(sv, i) = av[j];
+      one_at(yv, i) = bv[j];
+    });
+  }
+  if (threadIdx.x != 0) return;            // (the sums' barrier: every thread has read the scalars)
   if (keep) {
     L.rho[int64_t(slot) * L.nsub + s] = 1.0 / sy;
     L.gamma[s] = sy / yy;
@@ -585,16 +640,34 @@ void lb_armijo(const LbState& L, hipStream_t st) {
   hipLaunchKernelGGL(k_lb_move, parts_grid(L), dim3(kPartB), 0, st, L);
 }
 bool lb_one_part(const LbState& L) { return L.P.nparts == L.nsub && L.P.len <= kPartLen; }
+namespace {
+// f(entries per thread that hold the largest box)
+template <typename F>
+void with_entries(const LbState& L, F f) {
+  if (L.P.longest <= 4 * kOneB) f(std::integral_constant<int, 4>{});
+  else if (L.P.longest <= 8 * kOneB) f(std::integral_constant<int, 8>{});
+  else if (L.P.longest <= 12 * kOneB) f(std::integral_constant<int, 12>{});
+  else f(std::integral_constant<int, kPartLen / kOneB>{});
+}
+}  // namespace
+
 void lb_direction_one(const LbState& L, hipStream_t st) {
-  hipLaunchKernelGGL(k_lb_dir_one, parts_grid(L), dim3(kOneB), 0, st, L, nullptr, nullptr, 0u);
+  with_entries(L, [&](auto e) {
+    hipLaunchKernelGGL(k_lb_dir_one<decltype(e)::value>, parts_grid(L), dim3(kOneB), 0, st, L, nullptr,
+                       nullptr, 0u);
+  });
 }
 void lb_direction_next(const LbState& L, int round, SolveNote* note, uint32_t seq, hipStream_t st) {
-  hipLaunchKernelGGL(k_lb_dir_one, parts_grid(L), dim3(kOneB), 0, st, L, L.pending + 2 * (round & 1), note,
-                     seq);
+  with_entries(L, [&](auto e) {
+    hipLaunchKernelGGL(k_lb_dir_one<decltype(e)::value>, parts_grid(L), dim3(kOneB), 0, st, L,
+                       L.pending + 2 * (round & 1), note, seq);
+  });
 }
 void lb_armijo_one(const LbState& L, int round, hipStream_t st) {
-  hipLaunchKernelGGL(k_lb_armijo_one, parts_grid(L), dim3(kOneB), 0, st, L, L.pending + 2 * (round & 1),
-                     L.pending + 2 * (~round & 1));
+  with_entries(L, [&](auto e) {
+    hipLaunchKernelGGL(k_lb_armijo_one<decltype(e)::value>, parts_grid(L), dim3(kOneB), 0, st, L,
+                       L.pending + 2 * (round & 1), L.pending + 2 * (~round & 1));
+  });
 }
 void lb_count(const LbState& L, hipStream_t st) {
   hipLaunchKernelGGL(k_lb_count, dim3((L.nsub + kPartB - 1) / kPartB), dim3(kPartB), 0, st, L);
