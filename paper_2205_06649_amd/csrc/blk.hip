@@ -8,9 +8,12 @@
 // one column wider on either side and one row above and below, which carries
 // the frozen ring of the level (zeros for the perturbation and the adjoint)
 // or, for a box spanning the circle, copies of the box's own cells across the
-// seam or the pole; the level before it (the leapfrog base, lambda^{n+2}) sits
-// in registers, one value per thread and pass, and the two are swapped after
-// each level.  A block that is a whole box runs all its levels in one launch.
+// seam or the pole.  The level before it (the leapfrog base, lambda^{n+2})
+// sits in a second frame where two fit (TWO, at most three passes): a cell's
+// new value replaces its base there, and the frames change roles at the one
+// barrier of a level.  Larger blocks hold it in registers, one value per thread
+// and pass, and swap the two after each level, between two barriers.  A block
+// that is a whole box runs all its levels in one launch.
 // A box too large for one frame, or worth spreading over idle compute units,
 // is cut into blocks that compute, besides their own cells, e rows above and
 // below them at the level e levels before the launch's last one, so that no
@@ -27,13 +30,14 @@
 // once (forward) or read once (adjoint), plus the launch's two levels in and
 // out.  Small blocks are bound by their passes' instructions and latencies (an
 // adjoint pass of 64 cells is about 200 vector instructions, 75 of them FP64;
-// of the adjoint's 211 us on 64 boxes of 40 x 72 cells, 50 are the launches'
-// starts, 17 the swaps between levels, 38 waiting for the state's loads), large
-// ones by memory.  Step kernels -> blocks, per evaluation: 8 boxes of 18 x 36
-// cells, 13 levels 113 -> 61 us; 64 boxes of 40 x 72, 34 levels 518 -> 290
-// us; 1024 boxes of 72 x 136, 34 levels 16.6 -> 8.0 ms (forward 4.9 -> 2.4
-// ms, 3.3 TB/s of its 7.9 GB; adjoint 11.7 -> 5.6 ms).  Loads of the adjoint's
-// state one pass ahead, or the next level's lines touched early, gained
+// of the adjoint's 190 us on 64 boxes of 40 x 72 cells, 50 are the launches'
+// starts, 38 waiting for the state's loads), large ones by memory.  Step
+// kernels -> one frame -> two, per evaluation: 8 boxes of 18 x 36 cells, 13
+// levels 113 -> 57 -> 52 us; 64 boxes of 40 x 72, 34 levels 518 -> 283 -> 273
+// us; 1024 boxes of 72 x 136, 34 levels, one frame 16.6 -> 8.0 ms (forward 4.9
+// -> 2.4 ms, 3.3 TB/s of its 7.9 GB; adjoint 11.7 -> 5.6 ms).  All loads of a
+// launch's start issued before the first is used, loads of the adjoint's state
+// one pass ahead, or the next level's lines touched early, gained
 // nothing (the waves hide them); 512 threads of twice the passes, with
 // registers to spare, were 25 % slower than 1024, which leave 128 registers:
 // hence the values pinned to their pass below.
@@ -246,7 +250,7 @@ struct State5 {
 // Levels n0 + 1 .. n0 + steps of the forward sweep from levels n0 and n0 - 1
 // (n0 = 0: from the packed FP64 controls x, level 0 written as well).
 // traj_out (nullable): the packed FP64 trajectory, written beside each level.
-template <int NT, int K>
+template <int NT, int K, bool TWO>
 __global__ __launch_bounds__(NT) void k_fwd_blk(Dom<double> D, const BlkWork* __restrict__ work,
                                                 int n0, int steps, const double* __restrict__ x,
                                                 double* __restrict__ traj_out) {
@@ -264,7 +268,8 @@ __global__ __launch_bounds__(NT) void k_fwd_blk(Dom<double> D, const BlkWork* __
   const Range first = grown(w, max(steps - 1, 0), nx, ncell);
   const Frame F = {in.lo / nx, (in.hi - 1) / nx, nx + 2};
   double* fr = lds;
-  double* tab = lds + F.size();
+  double* fo = lds + F.size();              // TWO: the frame of the level before
+  double* tab = lds + (TWO ? 2 : 1) * F.size();
   fill_rows<NT, false>(tab, D, S, F);
   const double h0 = D.h0, st = D.st, stg = D.stg;
 
@@ -320,8 +325,10 @@ __global__ __launch_bounds__(NT) void k_fwd_blk(Dom<double> D, const BlkWork* __
     const int r = m / nx, c = m - r * nx;
     rc[p] = cell_word(r - F.rb, c, 0);
     prev[p] = {0.0, 0.0, 0.0};
-    if (m >= first.lo && m < first.hi)
+    if (m >= first.lo && m < first.hi) {
       prev[p] = n0 > 0 ? ld_box(state(D, S, n0 - 1), plane, m, 1.0) : get(fr, F.pos(r, c));
+      if (TWO) put(fo, F.pos(r, c), prev[p]);
+    }
   }
 
   for (int i = 0; i < steps; ++i) {
@@ -344,8 +351,10 @@ __global__ __launch_bounds__(NT) void k_fwd_blk(Dom<double> D, const BlkWork* __
       const V3<double> C = get(fr, q), E = get(fr, q + 3), W = get(fr, q - 3);
       const V3<double> N = get(fr, q + up), Sv = get(fr, q - up);
       const V3<double> f = swe_increment(C, E, W, N, Sv, k[0], k[1], k[2], k[4], k[5], k[3], k[6], st, stg, h0);
-      const V3<double> z = {prev[p].h + wgt * f.h, prev[p].u + wgt * f.u, prev[p].v + wgt * f.v};
-      prev[p] = z;
+      const V3<double> b = TWO ? get(fo, q) : prev[p];
+      const V3<double> z = {b.h + wgt * f.h, b.u + wgt * f.u, b.v + wgt * f.v};
+      if (!TWO) prev[p] = z;
+      else if (more) put_cell(fo, F, S, D.half, F.rb + row, cell_col(cell), z, -1.0);
       if (m >= w.out0 && m < w.out1) {
         out[m] = z.h;
         out[plane + m] = z.u;
@@ -359,27 +368,34 @@ __global__ __launch_bounds__(NT) void k_fwd_blk(Dom<double> D, const BlkWork* __
       }
     }
     if (!more) break;
-    __syncthreads();
+    if (!TWO) {
+      __syncthreads();
 #pragma unroll
-    for (int p = 0; p < K; ++p) {
-      const int m = here(cb) + p * NT;
-      if (m < g.lo || m >= g.hi) continue;
-      const int cell = here(rc[p]), r = F.rb + cell_row(cell), c = cell_col(cell);
-      const V3<double> old = get(fr, F.pos(r, c));
-      put_cell(fr, F, S, D.half, r, c, prev[p], -1.0);
-      prev[p] = old;
+      for (int p = 0; p < K; ++p) {
+        const int m = here(cb) + p * NT;
+        if (m < g.lo || m >= g.hi) continue;
+        const int cell = here(rc[p]), r = F.rb + cell_row(cell), c = cell_col(cell);
+        const V3<double> old = get(fr, F.pos(r, c));
+        put_cell(fr, F, S, D.half, r, c, prev[p], -1.0);
+        prev[p] = old;
+      }
     }
 #pragma unroll
     for (int b = 0; b < NI; ++b)
-      if (bon[b]) put(fr, bpos[b], ring[b]);
+      if (bon[b]) put(TWO ? fo : fr, bpos[b], ring[b]);
     __syncthreads();
+    if (TWO) {
+      double* f = fr;
+      fr = fo;
+      fo = f;
+    }
   }
 }
 
 // Levels n0 + 1 .. n0 + steps of the tangent-linear sweep about the stored
 // trajectory (n0 = 0: from the packed FP64 perturbation dx).  dtraj_out
 // (nullable): the packed FP64 perturbation trajectory.
-template <int NT, int K, bool SPAN>
+template <int NT, int K, bool SPAN, bool TWO>
 __global__ __launch_bounds__(NT) void k_tlm_blk(Dom<double> D, const BlkWork* __restrict__ work,
                                                 int n0, int steps, const double* __restrict__ dx,
                                                 double* __restrict__ dtraj_out) {
@@ -397,7 +413,8 @@ __global__ __launch_bounds__(NT) void k_tlm_blk(Dom<double> D, const BlkWork* __
   const Range first = grown(w, max(steps - 1, 0), nx, ncell);
   const Frame F = {in.lo / nx, (in.hi - 1) / nx, nx + 2};
   double* fr = lds;
-  double* tab = lds + F.size();
+  double* fo = lds + F.size();              // TWO: the frame of the level before
+  double* tab = lds + (TWO ? 2 : 1) * F.size();
   fill_rows<NT, false>(tab, D, S, F);
   const double h0 = D.h0, st = D.st, stg = D.stg;
   double* dz = D.dz + S.zoff;
@@ -424,6 +441,7 @@ __global__ __launch_bounds__(NT) void k_tlm_blk(Dom<double> D, const BlkWork* __
   // ring of a level is staged behind the row table
   const Border B(S, F);
   double* ring = tab + kRowTab * F.rows();
+  double* ringo = ring + 3 * B.count();     // TWO: the next level's
   int bk[NI];
   auto ring_at = [&](int n, int b) {
     return ld_ring(D.ring + S.ring_off + int64_t(n) * 3 * S.nring, S.nring, bk[b]);
@@ -434,6 +452,7 @@ __global__ __launch_bounds__(NT) void k_tlm_blk(Dom<double> D, const BlkWork* __
     B.item(t + i * NT, S, F, &pos, &bk[i]);
     if (t + i * NT < B.count()) {
       put(fr, pos, {0.0, 0.0, 0.0});
+      if (TWO) put(fo, pos, {0.0, 0.0, 0.0});
       put(ring, 3 * (t + i * NT), ring_at(n0, i));
     }
   }
@@ -449,6 +468,7 @@ __global__ __launch_bounds__(NT) void k_tlm_blk(Dom<double> D, const BlkWork* __
     const int r = m / nx, c = m - r * nx;
     rc[p] = cell_word(r - F.rb, c, 0);
     prev[p] = n0 > 0 ? ld_box(dz + int64_t(n0 - 1) * 3 * plane, plane, m, 1.0) : get(fr, F.pos(r, c));
+    if (TWO && m == cb + p * NT) put(fo, F.pos(r, c), prev[p]);
   }
   // the state's loads of a pass are issued one pass ahead, the first pass's
   // before the level before it is finished
@@ -484,25 +504,38 @@ __global__ __launch_bounds__(NT) void k_tlm_blk(Dom<double> D, const BlkWork* __
                                        get(fr, a - 3), get(fr, a + up), get(fr, a - up), k[0], k[1],
                                        k[2], k[4], k[5], k[3], k[6], st, stg, h0);
       if (m >= g.lo && m < g.hi) {
-        prev[p] = {prev[p].h + wgt * f.h, prev[p].u + wgt * f.u, prev[p].v + wgt * f.v};
-        if (m >= w.out0 && m < w.out1) store(n + 1, m, prev[p]);
+        const V3<double> b = TWO ? get(fo, a) : prev[p];
+        const V3<double> z = {b.h + wgt * f.h, b.u + wgt * f.u, b.v + wgt * f.v};
+        if (!TWO) prev[p] = z;
+        else if (more) put_cell(fo, F, S, D.half, F.rb + row, c, z, -1.0);
+        if (m >= w.out0 && m < w.out1) store(n + 1, m, z);
       }
     }
     if (!more) break;
-    __syncthreads();
+    if (!TWO) {
+      __syncthreads();
 #pragma unroll
-    for (int p = 0; p < K; ++p) {
-      const int m = here(cb) + p * NT;
-      if (m < g.lo || m >= g.hi) continue;
-      const int cell = here(rc[p]), r = F.rb + cell_row(cell), c = cell_col(cell);
-      const V3<double> old = get(fr, F.pos(r, c));
-      put_cell(fr, F, S, D.half, r, c, prev[p], -1.0);
-      prev[p] = old;
+      for (int p = 0; p < K; ++p) {
+        const int m = here(cb) + p * NT;
+        if (m < g.lo || m >= g.hi) continue;
+        const int cell = here(rc[p]), r = F.rb + cell_row(cell), c = cell_col(cell);
+        const V3<double> old = get(fr, F.pos(r, c));
+        put_cell(fr, F, S, D.half, r, c, prev[p], -1.0);
+        prev[p] = old;
+      }
     }
 #pragma unroll
     for (int b = 0; b < NI; ++b)
-      if (t + b * NT < B.count()) put(ring, 3 * (t + b * NT), rv[b]);
+      if (t + b * NT < B.count()) put(TWO ? ringo : ring, 3 * (t + b * NT), rv[b]);
     __syncthreads();
+    if (TWO) {
+      double* f = fr;
+      fr = fo;
+      fo = f;
+      f = ring;
+      ring = ringo;
+      ringo = f;
+    }
   }
 }
 
@@ -511,7 +544,7 @@ __global__ __launch_bounds__(NT) void k_tlm_blk(Dom<double> D, const BlkWork* __
 // from slots 2 pin, 2 pin + 1 and leaves lambda^{nlo}, lambda^{nlo+1} in
 // slots 2 (1 - pin), 2 (1 - pin) + 1 (other blocks of the box still read the
 // first two).
-template <int NT, int K, int MODE, bool SPAN>
+template <int NT, int K, int MODE, bool SPAN, bool TWO>
 __global__ __launch_bounds__(NT) void k_adj_blk(Dom<double> D, const BlkWork* __restrict__ work,
                                                 int nhi, int nlo, int pin,
                                                 const double* __restrict__ x,
@@ -532,13 +565,16 @@ __global__ __launch_bounds__(NT) void k_adj_blk(Dom<double> D, const BlkWork* __
   const Range in = grown(w, steps, nx, ncell), first = grown(w, steps - 1, nx, ncell);
   const Frame F = {in.lo / nx, (in.hi - 1) / nx, nx + 2};
   double* fr = lds;
-  double* tab = lds + F.size();
+  double* fo = lds + F.size();              // TWO: the frame of the level before
+  double* tab = lds + (TWO ? 2 : 1) * F.size();
   // the state's ring of a level, staged; J of each 64-cell chunk of the block
   const Border B(S, F);
   double* ring = tab + kRowTab * F.rows();
-  double* pj = ring + 3 * B.count();
-  const int nchunk = (w.out1 - w.out0 + 63) / 64;
-  int* tcnt = reinterpret_cast<int*>(pj + ((nchunk + 3) & ~3));   // intervals covering a level
+  double* ringo = ring + 3 * B.count();     // TWO: the next level's
+  double* pj = ring + (TWO ? 6 : 3) * B.count();
+  const int nchunk = (w.out1 - w.out0 + 63) / 64, npj = (nchunk + 3) & ~3;
+  double* pjo = pj + npj;                   // TWO: the next level's
+  int* tcnt = reinterpret_cast<int*>(pj + (TWO ? 2 : 1) * npj);   // intervals covering a level
   if (MODE != 1)
     for (int i = t; i < steps; i += NT) tcnt[i] = D.tcount[S.lev0 + nlo + i];
   fill_rows<NT, true>(tab, D, S, F);
@@ -549,8 +585,8 @@ __global__ __launch_bounds__(NT) void k_adj_blk(Dom<double> D, const BlkWork* __
   const double* l2 = A + int64_t(2 * pin + 1) * 3 * plane;
 
   // lambda^{top+1}, zero past the box's last level and on the border
-  for (int i = t; i < F.size(); i += NT) fr[i] = 0.0;
-  for (int i = t; i < ((nchunk + 3) & ~3); i += NT) pj[i] = 0.0;
+  for (int i = t; i < (TWO ? 2 : 1) * F.size(); i += NT) fr[i] = 0.0;
+  for (int i = t; i < (TWO ? 2 : 1) * npj; i += NT) pj[i] = 0.0;
   int bk[NI];
   auto ring_at = [&](int n, int b) {
     return ld_ring(D.ring + S.ring_off + int64_t(n) * 3 * S.nring, S.nring, bk[b]);
@@ -580,7 +616,10 @@ __global__ __launch_bounds__(NT) void k_adj_blk(Dom<double> D, const BlkWork* __
     const int r = m / nx;
     rc[p] = cell_word(r - F.rb, m - r * nx, MODE != 1 ? int(D.cover[S.cell_off + m]) : 0);
     prev[p] = {0.0, 0.0, 0.0};
-    if (!begin) prev[p] = ld_box(l2, plane, m, 1.0);
+    if (!begin) {
+      prev[p] = ld_box(l2, plane, m, 1.0);
+      if (TWO && m == cb + p * NT) put(fo, F.pos(r, m - r * nx), prev[p]);
+    }
   }
   // thread q: J of the block's q-th tile
   const int ntile = (w.out1 - w.out0 + kTile - 1) / kTile;
@@ -670,10 +709,14 @@ __global__ __launch_bounds__(NT) void k_adj_blk(Dom<double> D, const BlkWork* __
           const V3<double> e = MODE == 3 ? tg : V3<double>{C.h - tg.h, C.u - tg.u, C.v - tg.v};
           overlap_terms(e, kc, mis, MODE != 3, f, jloc);
         }
-        const double bh = f[0] + ah + prev[p].h;
-        const double bu = f[1] + au + prev[p].u;
-        const double bv = f[2] + av + prev[p].v;
-        if (m >= g.lo && m < g.hi) prev[p] = {bh, bu, bv};
+        const V3<double> b = TWO ? get(fo, a) : prev[p];
+        const double bh = f[0] + ah + b.h;
+        const double bu = f[1] + au + b.u;
+        const double bv = f[2] + av + b.v;
+        if (m >= g.lo && m < g.hi) {
+          if (!TWO) prev[p] = {bh, bu, bv};
+          else if (n > nlo) put_cell(fo, F, S, D.half, F.rb + row, c, {bh, bu, bv}, 1.0);
+        }
         const bool own = m >= w.out0 && m < w.out1;
         if (n == nlo && n > 0 && own) {
           double* b0 = A + int64_t(2 - 2 * pin) * 3 * plane + m;
@@ -709,6 +752,11 @@ __global__ __launch_bounds__(NT) void k_adj_blk(Dom<double> D, const BlkWork* __
         if ((t & 63) == 0) pj[(chunk - w.out0) / 64] = jloc;
       }
     }
+    if (TWO && n > nlo) {
+#pragma unroll
+      for (int b = 0; b < NI; ++b)
+        if (t + b * NT < B.count()) put(ringo, 3 * (t + b * NT), rv[b]);
+    }
     __syncthreads();
     if ((MODE == 0 || MODE == 2) && t < ntile) {
       const double* s = pj + 4 * t;
@@ -716,6 +764,18 @@ __global__ __launch_bounds__(NT) void k_adj_blk(Dom<double> D, const BlkWork* __
       jt = n == L ? tot : jt + tot;
     }
     if (n == nlo) break;
+    if (TWO) {
+      double* f = fr;
+      fr = fo;
+      fo = f;
+      f = ring;
+      ring = ringo;
+      ringo = f;
+      f = pj;
+      pj = pjo;
+      pjo = f;
+      continue;
+    }
 #pragma unroll
     for (int p = 0; p < K; ++p) {
       const int m = here(cb) + p * NT;
@@ -737,6 +797,7 @@ __global__ __launch_bounds__(NT) void k_adj_blk(Dom<double> D, const BlkWork* __
 namespace {
 constexpr int kBlkThreads = 1024;
 constexpr int kBlkPassMax = 6;             // 128 registers hold six passes
+constexpr int kBlkPassTwo = 3;             // and the LDS two frames of three
 
 // whether a block fits one workgroup, and what its levels cost
 struct BlkFit {
@@ -744,7 +805,7 @@ struct BlkFit {
   int passes;                 // cells computed at a launch's first level, in passes
   double us;                  // a level's time, both sweeps, on a compute unit of its own
   double bytes;               // a level's memory traffic, both sweeps
-  size_t lds;
+  size_t lds, lds2;           // with one frame, with two
 };
 BlkFit blk_fit(const SubDev& S, const BlkWork& w, int steps) {
   auto lo = [&](int e) { return std::max(0, w.out0 - e * S.nx); };
@@ -754,6 +815,8 @@ BlkFit blk_fit(const SubDev& S, const BlkWork& w, int steps) {
   f.lds = size_t(rows + 2) * (S.nx + 2) * 3 * sizeof(double) + size_t(rows) * kRowTab * sizeof(double) +
           size_t(2 * rows + 2 * S.nx) * 3 * sizeof(double) +
           size_t((w.out1 - w.out0 + 255) / 64) * sizeof(double) + size_t(std::max(steps, S.nlev) + 2) * sizeof(int);
+  f.lds2 = f.lds + size_t(rows + 2) * (S.nx + 2) * 3 * sizeof(double) + size_t(2 * rows + 2 * S.nx) * 3 * sizeof(double) +
+           size_t((w.out1 - w.out0 + 255) / 64) * sizeof(double);
   f.passes = (hi(steps - 1) - (lo(steps - 1) & ~63) + kBlkThreads - 1) / kBlkThreads;
   double cells = 0.0;
   for (int e = 0; e < steps; ++e) cells += double(hi(e) - lo(e)) / steps;
@@ -795,13 +858,14 @@ BlkPlan plan_blocks(const std::vector<SubDev>& subs, int maxlev, int cus) {
       p.ok = true;
       p.levels = k;
       double sum = 0.0, longest = 0.0, bytes = 0.0;
+      size_t lds2 = 0;
       std::vector<std::pair<double, BlkWork>> work;
       // boxes of one shape are cut alike
       struct Cut {
         bool ok = false;
         std::vector<std::pair<double, BlkWork>> blocks;
         double us = 0.0, most = 0.0, bytes = 0.0;
-        size_t lds = 0;
+        size_t lds = 0, lds2 = 0;
         int passes = 0;
       };
       std::map<std::array<int, 4>, Cut> cuts;
@@ -820,6 +884,7 @@ BlkPlan plan_blocks(const std::vector<SubDev>& subs, int maxlev, int cus) {
             const BlkFit f = blk_fit(S, w, k);
             c.ok = c.ok && f.ok;
             c.lds = std::max(c.lds, f.lds);
+            c.lds2 = std::max(c.lds2, f.lds2);
             c.passes = std::max(c.passes, f.passes);
             c.us += f.us;
             c.most = std::max(c.most, f.us);
@@ -830,6 +895,7 @@ BlkPlan plan_blocks(const std::vector<SubDev>& subs, int maxlev, int cus) {
         }
         p.ok = c.ok;
         p.lds = std::max(p.lds, c.lds);
+        lds2 = std::max(lds2, c.lds2);
         p.passes = std::max(p.passes, c.passes);
         for (auto w : c.blocks) {
           w.second.box = int(s);
@@ -842,6 +908,8 @@ BlkPlan plan_blocks(const std::vector<SubDev>& subs, int maxlev, int cus) {
       const double pack = int(work.size()) <= cus ? longest : sum / cus + 0.5 * longest;
       const double us = (levels + k - 1) / k * 10.0 + levels * std::max(pack, bytes / 4.0e6);
       if (!p.ok || us >= best_us) continue;
+      p.two = p.passes <= kBlkPassTwo && lds2 <= kBlkLdsMax;
+      if (p.two) p.lds = lds2;
       best = p;
       best_us = us;
       best.us = us;
@@ -864,22 +932,29 @@ hipError_t blk_allow(F* k) {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
                              int(kBlkLdsMax));
 }
-template <int K, bool SPAN>
+template <int K, bool SPAN, bool TWO>
 hipError_t blk_prepare_k() {
-  hipError_t e = blk_allow(&k_fwd_blk<kBlkThreads, K>);
-  if (e == hipSuccess) e = blk_allow(&k_tlm_blk<kBlkThreads, K, SPAN>);
-  if (e == hipSuccess) e = blk_allow(&k_adj_blk<kBlkThreads, K, 0, SPAN>);
-  if (e == hipSuccess) e = blk_allow(&k_adj_blk<kBlkThreads, K, 1, SPAN>);
-  if (e == hipSuccess) e = blk_allow(&k_adj_blk<kBlkThreads, K, 2, SPAN>);
-  if (e == hipSuccess) e = blk_allow(&k_adj_blk<kBlkThreads, K, 3, SPAN>);
+  hipError_t e = blk_allow(&k_fwd_blk<kBlkThreads, K, TWO>);
+  if (e == hipSuccess) e = blk_allow(&k_tlm_blk<kBlkThreads, K, SPAN, TWO>);
+  if (e == hipSuccess) e = blk_allow(&k_adj_blk<kBlkThreads, K, 0, SPAN, TWO>);
+  if (e == hipSuccess) e = blk_allow(&k_adj_blk<kBlkThreads, K, 1, SPAN, TWO>);
+  if (e == hipSuccess) e = blk_allow(&k_adj_blk<kBlkThreads, K, 2, SPAN, TWO>);
+  if (e == hipSuccess) e = blk_allow(&k_adj_blk<kBlkThreads, K, 3, SPAN, TWO>);
   return e;
 }
-// f(passes, span) with the smallest compiled pass count that holds p
+// f(passes, span, two frames) with the smallest compiled pass count that holds p
 template <typename F>
-void with_plan(int p, bool span, F f) {
+void with_plan(int p, bool span, bool two, F f) {
   auto go = [&](auto k) {
-    if (span) f(k, std::true_type{});
-    else f(k, std::false_type{});
+    constexpr int K = decltype(k)::value;
+    auto frames = [&](auto sp) {
+      if constexpr (K <= kBlkPassTwo) {
+        if (two) return f(k, sp, std::true_type{});
+      }
+      f(k, sp, std::false_type{});
+    };
+    if (span) frames(std::true_type{});
+    else frames(std::false_type{});
   };
   if (p <= 1) go(std::integral_constant<int, 1>{});
   else if (p <= 2) go(std::integral_constant<int, 2>{});
@@ -889,35 +964,37 @@ void with_plan(int p, bool span, F f) {
 }
 }  // namespace
 
-hipError_t blk_prepare(int passes, bool span) {
+hipError_t blk_prepare(int passes, bool span, bool two) {
   hipError_t e = hipSuccess;
-  with_plan(passes, span, [&](auto k, auto s) { e = blk_prepare_k<decltype(k)::value, decltype(s)::value>(); });
+  with_plan(passes, span, two, [&](auto k, auto s, auto w) {
+    e = blk_prepare_k<decltype(k)::value, decltype(s)::value, decltype(w)::value>();
+  });
   return e;
 }
 
 void launch_fwd_blk(const Dom<double>& D, const BlkLaunch& b, int n0, int levels, const double* x, double* traj_out,
                     hipStream_t st) {
-  with_plan(b.passes, false, [&](auto k, auto) {
-    auto* kern = &k_fwd_blk<kBlkThreads, decltype(k)::value>;
+  with_plan(b.passes, false, b.two, [&](auto k, auto, auto w) {
+    auto* kern = &k_fwd_blk<kBlkThreads, decltype(k)::value, decltype(w)::value>;
     hipLaunchKernelGGL(kern, dim3(b.nwork), dim3(kBlkThreads), b.lds, st, D, b.work, n0, levels, x, traj_out);
   });
 }
 void launch_tlm_blk(const Dom<double>& D, const BlkLaunch& b, int n0, int levels, const double* dx, double* dtraj_out,
                     hipStream_t st) {
-  with_plan(b.passes, b.span, [&](auto k, auto s) {
-    auto* kern = &k_tlm_blk<kBlkThreads, decltype(k)::value, decltype(s)::value>;
+  with_plan(b.passes, b.span, b.two, [&](auto k, auto s, auto w) {
+    auto* kern = &k_tlm_blk<kBlkThreads, decltype(k)::value, decltype(s)::value, decltype(w)::value>;
     hipLaunchKernelGGL(kern, dim3(b.nwork), dim3(kBlkThreads), b.lds, st, D, b.work, n0, levels, dx, dtraj_out);
   });
 }
 void launch_adj_blk(const Dom<double>& D, const BlkLaunch& b, int mode, int nhi, int nlo, int pin,
                     const double* x, const double* xb, const double* forcing, double* out,
                     hipStream_t st) {
-  with_plan(b.passes, b.span, [&](auto k, auto s) {
+  with_plan(b.passes, b.span, b.two, [&](auto k, auto s, auto w) {
     constexpr int K = decltype(k)::value;
-    constexpr bool SPAN = decltype(s)::value;
-    auto* kern = mode == 0 ? &k_adj_blk<kBlkThreads, K, 0, SPAN>
-                 : mode == 1 ? &k_adj_blk<kBlkThreads, K, 1, SPAN>
-                 : mode == 2 ? &k_adj_blk<kBlkThreads, K, 2, SPAN> : &k_adj_blk<kBlkThreads, K, 3, SPAN>;
+    constexpr bool SPAN = decltype(s)::value, TWO = decltype(w)::value;
+    auto* kern = mode == 0 ? &k_adj_blk<kBlkThreads, K, 0, SPAN, TWO>
+                 : mode == 1 ? &k_adj_blk<kBlkThreads, K, 1, SPAN, TWO>
+                 : mode == 2 ? &k_adj_blk<kBlkThreads, K, 2, SPAN, TWO> : &k_adj_blk<kBlkThreads, K, 3, SPAN, TWO>;
     hipLaunchKernelGGL(kern, dim3(b.nwork), dim3(kBlkThreads), b.lds, st, D, b.work, nhi, nlo, pin, x, xb,
                        forcing, out);
   });

@@ -1054,9 +1054,9 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
     if (plan.ok) {
       bool span = false;
       for (const SubDev& S : c->subs) span = span || S.span;
-      chk(blk_prepare(plan.passes, span), "block sweep set-up");
+      chk(blk_prepare(plan.passes, span, plan.two), "block sweep set-up");
       c->blk = BlkLaunch{upload(c, plan.work, st), int(plan.work.size()), plan.levels, plan.passes, span,
-                         plan.lds};
+                         plan.two, plan.lds};
       c->blk_ok = true;
       // the pageable list is copied before it goes
       chk(hipStreamSynchronize(st), "upload sync");

@@ -126,10 +126,10 @@ struct BlkWork {
   int32_t box, out0, out1;
 };
 // the decomposition of every box into blocks: levels per launch (all of them
-// where no box is cut), passes of 1024 cells, LDS bytes of the largest
-// block; us: the model's time per evaluation
+// where no box is cut), passes of 1024 cells, frames (two: one for either level on chip),
+// LDS bytes of the largest block; us: the model's time per evaluation
 struct BlkPlan {
-  bool ok;
+  bool ok, two;
   int levels, passes;
   size_t lds;
   double us;
@@ -140,10 +140,10 @@ BlkPlan plan_blocks(const std::vector<SubDev>& subs, int maxlev, int cus);
 struct BlkLaunch {
   const BlkWork* work;
   int nwork, levels, passes;
-  bool span;                              // some box spans the circle
+  bool span, two;                         // some box spans the circle; two frames
   size_t lds;
 };
-hipError_t blk_prepare(int passes, bool span);   // once, before any launch: the LDS allowance
+hipError_t blk_prepare(int passes, bool span, bool two);   // once, before any launch: the LDS allowance
 // levels n0 + 1 .. n0 + levels, levels <= b.levels (n0 = 0: from the packed
 // controls, level 0 too)
 void launch_fwd_blk(const Dom<double>& D, const BlkLaunch& b, int n0, int levels, const double* x,

@@ -17,6 +17,10 @@ CASES = {
     "whole": {},
     "band": dict(bands=3, pieces=1, nlat=33, nlon=64),
     "sphere": dict(bands=1, pieces=1, nlat=24, nlon=48, overlap_cells=0, ntime=2),
+    # three passes, in one frame and in two
+    "three_two": dict(bands=1, pieces=1, nlat=40, nlon=64, overlap_cells=0, ntime=2),
+    "three_one": dict(bands=8, pieces=8, nlat=320, nlon=480, overlap_cells=3, nsteps=22, ntime=2),
+    "three_cut": dict(bands=8, pieces=8, nlat=384, nlon=528, overlap_cells=3, nsteps=22, ntime=2),
     "cut": dict(nlat=96, nlon=192, nsteps=30),
     "six_passes": dict(nlat=134, nlon=268, bands=2, pieces=2, overlap_cells=4, nsteps=24, ntime=2),
     "many": dict(nlat=270, nlon=1072, bands=4, pieces=8, overlap_cells=3, nsteps=14, ntime=8,
