@@ -160,15 +160,15 @@ def gn_product_bytes(ctx, prec_bytes, persistent=False):
 # digest of the kernel sources they were measured on: a changed kernel (or
 # another workload) reports null until it is measured again.
 MEASURED_TRAFFIC = {
-    "k_adj": ("sweep", "ff254c10224ff0ba", 1158229105),
-    "k_adj_box/10": ("box", "d0a69a4840912446", 16093533656),
-    "k_adj_box/11": ("box", "d0a69a4840912446", 16089092536),
-    "k_adj_strip/11": ("box", "d0a69a4840912446", 16657258389),
-    "k_eval_box/10": ("box", "d0a69a4840912446", 29856191456),
+    "k_adj": ("sweep", "d6e5bb3a6f9a6c4f", 1158712346),
+    "k_adj_box/10": ("box", "aafc5cb4490ad332", 16097146272),
+    "k_adj_box/11": ("box", "aafc5cb4490ad332", 16095416032),
+    "k_adj_strip/11": ("box", "aafc5cb4490ad332", 16653200131),
+    "k_eval_box/10": ("box", "aafc5cb4490ad332", 29699040304),
     # Gauss-Newton normal-matrix product: tangent-linear sweep (10 passes)
     # and the adjoint with the Gauss-Newton forcing (column strips, 11 rows)
-    "k_tlm_box/10": ("box", "d0a69a4840912446", 16788000987),
-    "k_adj_strip_gn/11": ("box", "d0a69a4840912446", 15650230395),
+    "k_tlm_box/10": ("box", "aafc5cb4490ad332", 16797037168),
+    "k_adj_strip_gn/11": ("box", "aafc5cb4490ad332", 15638795709),
 }
 KERNEL_SOURCES = {"sweep": ("sweep.hip", "kernels.h", "stencil.h"),
                   "box": ("box.hip", "kernels.h", "stencil.h")}
