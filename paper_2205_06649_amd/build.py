@@ -20,8 +20,9 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 CXX = os.environ.get("CXX", "g++")
 
 # (source, object, extra flags): the sweep kernels are compiled once per state
-# type; FP64 without floating-point contraction (separately rounded multiply
-# and add, as in the FP64 reference), FP32 with the default FMA contraction.
+# type; FP64 without the compiler's floating-point contraction (the plain
+# scheme's terms are contracted by hand, so that every FP64 kernel rounds
+# alike), FP32 with the default FMA contraction.
 HIP_UNITS = [
     ("sweep.hip", "sweep_f32.o", ["-DDD4DVAR_SWEEP_T=float", "-DDD4DVAR_SWEEP_PRIMARY=1"]),
     ("sweep.hip", "sweep_f64.o", ["-DDD4DVAR_SWEEP_T=double", "-DDD4DVAR_SWEEP_PRIMARY=0",

@@ -9,6 +9,8 @@
 //   subdomain, the constant sum_{s'} (T_{s'} - mean)^2 / sigma_b^2, so that
 //   sum_{s'} (Z - T_{s'})^2 = K (Z - mean)^2 + constant.
 // * Before any local solve both come from the global background run.
+#include <algorithm>
+
 #include "kernels.h"
 #include "launch.h"
 #include "stencil.h"
@@ -34,8 +36,9 @@ constexpr int kWaves = kTile / 64;         // partial sums per tile
 // h is stored as h - h_ref
 template <typename T>
 __global__ __launch_bounds__(kTile) void k_from_global(Dom<T> D, const double* __restrict__ bg,
-                                                       int64_t gplane, double* __restrict__ xb) {
-  const int n = blockIdx.y;
+                                                       int64_t gplane, double* __restrict__ xb,
+                                                       int n0) {
+  const int n = n0 + blockIdx.y;
   const int2 wt = D.tiles[xcd_tile(blockIdx.x, gridDim.x)];
   const SubDev S = D.subs[wt.x];
   if (n >= S.nlev) return;
@@ -326,7 +329,10 @@ __global__ void k_fill(double* p, int64_t n, double v) {
 template <typename T>
 void launch_from_global(const Dom<T>& D, const double* bg, int64_t gplane, double* xb, int nlev,
                         int ntiles, hipStream_t st) {
-  hipLaunchKernelGGL(k_from_global<T>, dim3(ntiles, nlev), dim3(kTile), 0, st, D, bg, gplane, xb);
+  constexpr int kGrid = 32768;             // levels per launch: within the grid's limit of 65535
+  for (int n = 0; n < nlev; n += kGrid)
+    hipLaunchKernelGGL(k_from_global<T>, dim3(ntiles, std::min(nlev - n, kGrid)), dim3(kTile), 0, st, D, bg,
+                       gplane, xb, n);
 }
 // grid.y covers the largest ring; positions beyond a box's own ring exit
 template <typename T>
