@@ -35,12 +35,15 @@
 // kernels -> one frame -> two, per evaluation: 8 boxes of 18 x 36 cells, 13
 // levels 113 -> 57 -> 52 us; 64 boxes of 40 x 72, 34 levels 518 -> 283 -> 273
 // us; 1024 boxes of 72 x 136, 34 levels, one frame 16.6 -> 8.0 ms (forward 4.9
-// -> 2.4 ms, 3.3 TB/s of its 7.9 GB; adjoint 11.7 -> 5.6 ms).  All loads of a
-// launch's start issued before the first is used, loads of the adjoint's state
-// one pass ahead, or the next level's lines touched early, gained
-// nothing (the waves hide them); 512 threads of twice the passes, with
-// registers to spare, were 25 % slower than 1024, which leave 128 registers:
-// hence the values pinned to their pass below.
+// -> 2.4 ms, 3.3 TB/s of its 7.9 GB; adjoint 11.7 -> 5.6 ms).  In a small
+// block an adjoint level takes about 6800 clocks on its compute unit, 2500 to
+// 3400 of them until the state, target and observation bin are there: 31 KB
+// from beyond the L2, a unit's own rate, and no latency to hide: all loads of a
+// launch's start issued before the first is used, a pass's or a whole level's
+// loads issued ahead, the state in a third frame (12 of 15 loads fewer), 10 %
+// fewer instructions by scalar bases gained nothing or lost.  512 threads of
+// twice the passes, with registers to spare, were 25 % slower than 1024, which
+// leave 128 registers: hence the values pinned to their pass below.
 #include <algorithm>
 #include <array>
 #include <map>
