@@ -160,15 +160,15 @@ def gn_product_bytes(ctx, prec_bytes, persistent=False):
 # digest of the kernel sources they were measured on: a changed kernel (or
 # another workload) reports null until it is measured again.
 MEASURED_TRAFFIC = {
-    "k_adj": ("sweep", "d6e5bb3a6f9a6c4f", 1158712346),
-    "k_adj_box/10": ("box", "aafc5cb4490ad332", 16097146272),
-    "k_adj_box/11": ("box", "aafc5cb4490ad332", 16095416032),
-    "k_adj_strip/11": ("box", "aafc5cb4490ad332", 16653200131),
-    "k_eval_box/10": ("box", "aafc5cb4490ad332", 29699040304),
+    "k_adj": ("sweep", "1e11ad93baab328b", 1158710447),
+    "k_adj_box/10": ("box", "83b79d81c53ce558", 16094724112),
+    "k_adj_box/11": ("box", "83b79d81c53ce558", 16089913856),
+    "k_adj_strip/11": ("box", "83b79d81c53ce558", 16647845633),
+    "k_eval_box/10": ("box", "83b79d81c53ce558", 29696822280),
     # Gauss-Newton normal-matrix product: tangent-linear sweep (10 passes)
     # and the adjoint with the Gauss-Newton forcing (column strips, 11 rows)
-    "k_tlm_box/10": ("box", "aafc5cb4490ad332", 16797037168),
-    "k_adj_strip_gn/11": ("box", "aafc5cb4490ad332", 15638795709),
+    "k_tlm_box/10": ("box", "83b79d81c53ce558", 16793360928),
+    "k_adj_strip_gn/11": ("box", "83b79d81c53ce558", 15641908405),
 }
 KERNEL_SOURCES = {"sweep": ("sweep.hip", "kernels.h", "stencil.h"),
                   "box": ("box.hip", "kernels.h", "stencil.h")}

@@ -254,12 +254,10 @@ struct State5 {
 // (n0 = 0: from the packed FP64 controls x, level 0 written as well).
 // traj_out (nullable): the packed FP64 trajectory, written beside each level.
 template <int NT, int K, bool TWO>
-__global__ __launch_bounds__(NT) void k_fwd_blk(Dom<double> D, const BlkWork* __restrict__ work,
-                                                int n0, int steps, const double* __restrict__ x,
-                                                double* __restrict__ traj_out) {
+__device__ __forceinline__ void fwd_blk(const Dom<double>& D, const BlkWork& w, int n0, int steps,
+                                        const double* __restrict__ x, double* __restrict__ traj_out) {
   constexpr int NI = border_items(NT);
   extern __shared__ double lds[];
-  const BlkWork w = work[blockIdx.x];
   if (D.active && !D.active[w.box]) return;
   const SubDev S = D.subs[w.box];
   const int L = S.nlev - 1;
@@ -393,6 +391,14 @@ __global__ __launch_bounds__(NT) void k_fwd_blk(Dom<double> D, const BlkWork* __
       fo = f;
     }
   }
+}
+
+template <int NT, int K, bool TWO>
+__global__ __launch_bounds__(NT) void k_fwd_blk(Dom<double> D, const BlkWork* __restrict__ work,
+                                                int n0, int steps, const double* __restrict__ x,
+                                                double* __restrict__ traj_out) {
+  const BlkWork w = work[blockIdx.x];
+  fwd_blk<NT, K, TWO>(D, w, n0, steps, x, traj_out);
 }
 
 // Levels n0 + 1 .. n0 + steps of the tangent-linear sweep about the stored
@@ -548,15 +554,11 @@ __global__ __launch_bounds__(NT) void k_tlm_blk(Dom<double> D, const BlkWork* __
 // slots 2 (1 - pin), 2 (1 - pin) + 1 (other blocks of the box still read the
 // first two).
 template <int NT, int K, int MODE, bool SPAN, bool TWO>
-__global__ __launch_bounds__(NT) void k_adj_blk(Dom<double> D, const BlkWork* __restrict__ work,
-                                                int nhi, int nlo, int pin,
-                                                const double* __restrict__ x,
-                                                const double* __restrict__ xb,
-                                                const double* __restrict__ forcing,
-                                                double* __restrict__ out) {
+__device__ __forceinline__ void adj_blk(const Dom<double>& D, const BlkWork& w, int nhi, int nlo, int pin,
+                                        const double* __restrict__ x, const double* __restrict__ xb,
+                                        const double* __restrict__ forcing, double* __restrict__ out) {
   constexpr int NI = border_items(NT);
   extern __shared__ double lds[];
-  const BlkWork w = work[blockIdx.x];
   if (D.active && !D.active[w.box]) return;
   const SubDev S = D.subs[w.box];
   const int L = S.nlev - 1;
@@ -796,6 +798,32 @@ __global__ __launch_bounds__(NT) void k_adj_blk(Dom<double> D, const BlkWork* __
   if ((MODE == 0 || MODE == 2) && t < ntile) *jp = jt;
 }
 
+template <int NT, int K, int MODE, bool SPAN, bool TWO>
+__global__ __launch_bounds__(NT) void k_adj_blk(Dom<double> D, const BlkWork* __restrict__ work,
+                                                int nhi, int nlo, int pin,
+                                                const double* __restrict__ x,
+                                                const double* __restrict__ xb,
+                                                const double* __restrict__ forcing,
+                                                double* __restrict__ out) {
+  const BlkWork w = work[blockIdx.x];
+  adj_blk<NT, K, MODE, SPAN, TWO>(D, w, nhi, nlo, pin, x, xb, forcing, out);
+}
+
+// Both sweeps of the cost and its gradient, where every block is a whole box:
+// the adjoint reads the levels that its own workgroup has just written, from
+// its XCD's L2 (a launch of its own starts with that cache's lines dropped),
+// and one launch is saved: 8 boxes of 18 x 36, 13 levels 52.4 -> 49.5 us.
+template <int NT, int K, bool SPAN, bool TWO>
+__global__ __launch_bounds__(NT) void k_eval_blk(Dom<double> D, const BlkWork* __restrict__ work,
+                                                 int levels, const double* __restrict__ x,
+                                                 const double* __restrict__ xb,
+                                                 double* __restrict__ out) {
+  const BlkWork w = work[blockIdx.x];
+  fwd_blk<NT, K, TWO>(D, w, 0, levels - 1, x, nullptr);
+  __syncthreads();
+  adj_blk<NT, K, 0, SPAN, TWO>(D, w, levels - 1, 0, 0, x, xb, nullptr, out);
+}
+
 // ---- plan and launchers -------------------------------------------------------
 namespace {
 constexpr int kBlkThreads = 1024;
@@ -938,6 +966,7 @@ hipError_t blk_allow(F* k) {
 template <int K, bool SPAN, bool TWO>
 hipError_t blk_prepare_k() {
   hipError_t e = blk_allow(&k_fwd_blk<kBlkThreads, K, TWO>);
+  if (e == hipSuccess) e = blk_allow(&k_eval_blk<kBlkThreads, K, SPAN, TWO>);
   if (e == hipSuccess) e = blk_allow(&k_tlm_blk<kBlkThreads, K, SPAN, TWO>);
   if (e == hipSuccess) e = blk_allow(&k_adj_blk<kBlkThreads, K, 0, SPAN, TWO>);
   if (e == hipSuccess) e = blk_allow(&k_adj_blk<kBlkThreads, K, 1, SPAN, TWO>);
@@ -1000,6 +1029,14 @@ void launch_adj_blk(const Dom<double>& D, const BlkLaunch& b, int mode, int nhi,
                  : mode == 2 ? &k_adj_blk<kBlkThreads, K, 2, SPAN, TWO> : &k_adj_blk<kBlkThreads, K, 3, SPAN, TWO>;
     hipLaunchKernelGGL(kern, dim3(b.nwork), dim3(kBlkThreads), b.lds, st, D, b.work, nhi, nlo, pin, x, xb,
                        forcing, out);
+  });
+}
+
+void launch_eval_blk(const Dom<double>& D, const BlkLaunch& b, int levels, const double* x, const double* xb,
+                     double* out, hipStream_t st) {
+  with_plan(b.passes, b.span, b.two, [&](auto k, auto s, auto w) {
+    auto* kern = &k_eval_blk<kBlkThreads, decltype(k)::value, decltype(s)::value, decltype(w)::value>;
+    hipLaunchKernelGGL(kern, dim3(b.nwork), dim3(kBlkThreads), b.lds, st, D, b.work, levels, x, xb, out);
   });
 }
 

@@ -602,6 +602,17 @@ void cost_grad_impl(dd4dvar_ctx* c, const std::vector<int32_t>* ids, const doubl
       return;
     }
   }
+  if constexpr (std::is_same<T, double>::value) {
+    // (phase timing keeps the sweeps apart)
+    if (!ids && blk_sweeps(c) && c->blk.levels >= c->maxlev && !c->timing) {
+      launch_eval_blk(D, c->blk, c->maxlev, x, c->xb, grad, st);
+      chk(hipGetLastError(), "evaluation launch");
+      c->have_forward = true;
+      launch_reduce_j(c->d_subs, c->nsub, nullptr, D.jpart, c->jconst, J, c->nonfinite, st);
+      chk(hipGetLastError(), "reduce launch");
+      return;
+    }
+  }
   if (ids) {
     for (int32_t s : *ids) {
       const SubDev& S = c->subs[s];

@@ -78,15 +78,11 @@ struct Dom {
   const RowCoef<T>* rows;    // [nlat]
   const T* cosx;             // [nlat+2]: cos of rows -1..nlat (pole-mapped)
   const uint8_t* cover;      // spatial coverage count per box cell
-  const int32_t* perm;       // per spatial piece, its box cells: those that other boxes of the
-                             // interval cover first, like sets of boxes together
   const int32_t* tcount;     // temporal coverage count per global level
   const int32_t* obs_ptr;    // CSR over the (tile, level) bins, keyed by obs_key
   const int32_t* obs_code;   // local cell * 4 + field
   const double* obs_val;     // value (h as anomaly)
   const double* obs_q;       // lambda * w_o / sigma_o^2
-  const int32_t* obs_bin;    // per bin (obs_key): its ObsTile, -1 without entries
-  const ObsTile* obs_tile;
   double* jpart;             // per-tile cost accumulator
   const int32_t* nbr_idx;
   const int32_t* hsrc;
@@ -104,6 +100,10 @@ struct Dom {
   double mu;
   double isb2[3];            // 1 / sigma_b^2
   int32_t nlon, half, maxlev, weight_mode;
+  const int32_t* perm;       // per spatial piece, its box cells: those that other boxes of the
+                             // interval cover first, like sets of boxes together
+  const int32_t* obs_bin;    // per bin (obs_key): its ObsTile, -1 without entries
+  const ObsTile* obs_tile;
 };
 
 // flags a non-finite output value (no store while every value is finite)

@@ -155,5 +155,8 @@ void launch_tlm_blk(const Dom<double>& D, const BlkLaunch& b, int n0, int levels
 void launch_adj_blk(const Dom<double>& D, const BlkLaunch& b, int mode, int nhi, int nlo, int pin,
                     const double* x, const double* xb, const double* forcing, double* out,
                     hipStream_t st);
+// both sweeps of the cost and its gradient; only where every block is a box (b.levels >= levels)
+void launch_eval_blk(const Dom<double>& D, const BlkLaunch& b, int levels, const double* x, const double* xb,
+                     double* out, hipStream_t st);
 
 }  // namespace dd4dvar
