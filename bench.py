@@ -160,7 +160,7 @@ def gn_product_bytes(ctx, prec_bytes, persistent=False):
 # digest of the kernel sources they were measured on: a changed kernel (or
 # another workload) reports null until it is measured again.
 MEASURED_TRAFFIC = {
-    "k_adj": ("sweep", "1e11ad93baab328b", 1158710447),
+    "k_adj": ("sweep", "605567ab3d514195", 1158231803),
     "k_adj_box/10": ("box", "83b79d81c53ce558", 16094724112),
     "k_adj_box/11": ("box", "83b79d81c53ce558", 16089913856),
     "k_adj_strip/11": ("box", "83b79d81c53ce558", 16647845633),
