@@ -71,6 +71,34 @@ __device__ __forceinline__ Range grown(const BlkWork& w, int e, int nx, int ncel
   return {max(0, w.out0 - e * nx), min(ncell, w.out1 + e * nx)};
 }
 
+// Observation entries of the calling lane's cell at one level, one wave per
+// 64-cell chunk of a tile (bin: the tile's entry of Dom::obs_bin; bin and
+// chunk uniform over the wave).  z is the state (or, dz true, the perturbation, whose
+// misfit is itself); adds nothing where the lane's cell is not observed.
+// Forcing q r into f, the terms of J into jloc, field by field.  By masks and
+// not through LDS as in the step kernels: a wave takes its chunks by itself, with
+// no barrier per tile.
+__device__ __forceinline__ void obs_terms(const Dom<double>& D, int bin, int chunk, const V3<double>& z,
+                                          bool dz, double* f, double& jloc) {
+  const ObsTile& o = D.obs_tile[__builtin_amdgcn_readfirstlane(bin)];
+  const uint64_t m[3] = {o.mask[chunk][0], o.mask[chunk][1], o.mask[chunk][2]};   // scalar registers
+  const int lane = int(threadIdx.x & 63);
+  int k = o.base[chunk];
+#pragma unroll
+  for (int i = 0; i < 3; ++i)               // entries of the lanes below
+    k = __builtin_amdgcn_mbcnt_hi(uint32_t(m[i] >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m[i]), k));
+  const double zz[3] = {z.h, z.u, z.v};
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    if (!(m[i] >> lane & 1)) continue;
+    const double qo = D.obs_q[k];
+    const double rr = dz ? zz[i] : zz[i] - D.obs_val[k];
+    f[i] = qo * rr;
+    if (!dz) jloc += 0.5 * qo * rr * rr;
+    ++k;
+  }
+}
+
 // a block's frame: rows rb - 1 .. re + 1 of the box, columns -1 .. nx
 struct Frame {
   int rb, re, fw;

@@ -29,10 +29,11 @@ __host__ __device__ inline int64_t obs_key(int tile0, int ntile, int maxlev, int
   return int64_t(tile0) * maxlev + int64_t(n) * ntile + t_local;
 }
 
-// The observed cells of one non-empty (tile, level) bin: for each of the
-// tile's four 64-cell chunks one bit per cell and field, and the entry of
-// the chunk's first observation (a bin's entries are ordered by cell, then
-// field), so that a lane finds its own cell's entries by counting bits.
+// The observed cells of one non-empty (tile, level) bin as the block sweeps
+// read them: for each of the tile's four 64-cell chunks one bit per cell and
+// field, and the entry of the chunk's first observation (a bin's entries are
+// ordered by cell, then field), so that a lane finds its own cell's entries by
+// counting bits.
 struct ObsTile {
   uint64_t mask[4][3];
   int32_t base[4];
@@ -49,6 +50,7 @@ struct SubDev {
   int64_t traj_off;          // packed FP64 trajectory and overlap-target offset
   int64_t ring_off;          // ring arena offset, level stride 3*nring
   int64_t adj_off;           // adjoint arena offset: 3 slots x 3 x ncell
+                             // (with block sweeps 4 slots, from 4/3 of it)
   int64_t ctrl_off;          // packed control offset
   int64_t cell_off;          // per-cell coverage offset
   int64_t hmap_off;          // halo map offset
@@ -102,7 +104,7 @@ struct Dom {
   int32_t nlon, half, maxlev, weight_mode;
   const int32_t* perm;       // per spatial piece, its box cells: those that other boxes of the
                              // interval cover first, like sets of boxes together
-  const int32_t* obs_bin;    // per bin (obs_key): its ObsTile, -1 without entries
+  const int32_t* obs_bin;    // (block sweeps) per bin (obs_key): its ObsTile, -1 without entries
   const ObsTile* obs_tile;
 };
 

@@ -1,6 +1,8 @@
-// Stencil helpers shared by the step kernels (sweep.hip) and the per-box
-// kernels (box.hip): neighbour indexing of a box cell (inside, wrapped, or a
-// frozen ring position) and branch-free loads.
+// Stencil helpers shared by the step kernels (sweep.hip, tlm.hip), the block
+// sweeps (blk.hip) and the per-box kernels (box.hip): neighbour indexing of a
+// box cell (inside, wrapped, or a frozen ring position), branch-free loads,
+// the FP64 arithmetic that step kernels and block sweeps have in common, and
+// sums over a wave and a workgroup.
 #pragma once
 
 #include "kernels.h"
@@ -154,33 +156,6 @@ __device__ __forceinline__ void overlap_terms(const V3<double>& e, int K, const 
   f[1] += gu;
   f[2] += gv;
   if (cost) jloc = fma(0.5, fma(gv, e.v, fma(gu, e.u, gh * e.h)), jloc);
-}
-
-// Observation entries of the calling lane's cell at one level, one wave per
-// 64-cell chunk of a tile (bin: the tile's entry of Dom::obs_bin, uniform;
-// lane m of the tile).  z is the state (or, dz true, the perturbation, whose
-// misfit is itself); adds nothing where the lane's cell is not observed.
-// Forcing q r into f, the terms of J into jloc, field by field.
-template <typename T>
-__device__ __forceinline__ void obs_terms(const Dom<T>& D, int bin, int chunk, const V3<T>& z,
-                                          bool dz, double* f, double& jloc) {
-  const ObsTile& o = D.obs_tile[__builtin_amdgcn_readfirstlane(bin)];
-  const uint64_t m[3] = {o.mask[chunk][0], o.mask[chunk][1], o.mask[chunk][2]};   // scalar registers
-  const int lane = int(threadIdx.x & 63);
-  int k = o.base[chunk];
-#pragma unroll
-  for (int i = 0; i < 3; ++i)               // entries of the lanes below
-    k = __builtin_amdgcn_mbcnt_hi(uint32_t(m[i] >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m[i]), k));
-  const T zz[3] = {z.h, z.u, z.v};
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    if (!(m[i] >> lane & 1)) continue;
-    const double qo = D.obs_q[k];
-    const double rr = dz ? double(zz[i]) : double(zz[i]) - D.obs_val[k];
-    f[i] = qo * rr;
-    if (!dz) jloc += 0.5 * qo * rr * rr;
-    ++k;
-  }
 }
 
 // Sum of a wave's 64 values in every lane, in the order of block_sum's

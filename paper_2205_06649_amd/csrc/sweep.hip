@@ -105,7 +105,11 @@ __global__ __launch_bounds__(kTile) void k_adj(Dom<T> D, int n, int tile_base,
                                                const double* __restrict__ xb,
                                                const double* __restrict__ forcing,
                                                double* __restrict__ out) {
-  __shared__ double fo[3][sizeof(T) == 4 ? kTile : 1];
+  // FP64: a cell's observation terms of J are summed by its own thread, field by
+  // field, as in the block sweeps (FP32: by the threads that hold the entries)
+  constexpr bool kCellJ = sizeof(T) == 8 && (MODE == 0 || MODE == 2);
+  __shared__ double fo[3][MODE != 1 ? kTile : 1];
+  __shared__ double jo[3][kCellJ ? kTile : 1];
   __shared__ double red[kTile / 64];
   const int w = tile_base + xcd_tile(blockIdx.x, gridDim.x);
   const int2 wt = D.tiles[w];
@@ -165,40 +169,32 @@ __global__ __launch_bounds__(kTile) void k_adj(Dom<T> D, int n, int tile_base,
 
   // ---- observation misfits of this tile at level n (uniform test) --------
   if (MODE != 1) {
+    // (the entries through LDS: each cell's thread finding its own by the block
+    // sweeps' masks was slower, FP64 8 boxes of 103 x 400 cells and 24 or 27 levels
+    // 390 -> 434 us a sweep, FP32 122 x 238 in 4 boxes 270 -> 277 us an evaluation)
     const int64_t key = obs_key(S.tile0, S.ntile, D.maxlev, wt.y, n);
-    if constexpr (sizeof(T) == 8) {
-      const int bin = __builtin_amdgcn_readfirstlane(D.obs_bin[key]);
-      if (bin >= 0 && valid) {
-        double f[3] = {0.0, 0.0, 0.0};
-        obs_terms(D, bin, int(threadIdx.x >> 6), MODE == 3 ? tg : C, MODE == 3, f, jloc);
-        fh = f[0];
-        fu = f[1];
-        fv = f[2];
+    const int o0 = D.obs_ptr[key], o1 = D.obs_ptr[key + 1];
+    if (o1 > o0) {
+      fo[0][threadIdx.x] = 0.0;
+      fo[1][threadIdx.x] = 0.0;
+      fo[2][threadIdx.x] = 0.0;
+      if constexpr (kCellJ) jo[0][threadIdx.x] = jo[1][threadIdx.x] = jo[2][threadIdx.x] = 0.0;
+      __syncthreads();
+      for (int o = o0 + int(threadIdx.x); o < o1; o += kTile) {
+        const int code = D.obs_code[o];
+        const int loc = code >> 2, f = code & 3;
+        const double rr = MODE == 3 ? double(D.dz[S.zoff + int64_t(n) * 3 * plane + f * plane + loc])
+                                    : double(Z[f * plane + loc]) - D.obs_val[o];
+        const double qo = D.obs_q[o];
+        if constexpr (kCellJ) jo[f][loc - wt.y * kTile] = 0.5 * qo * rr * rr;
+        else if (MODE != 3) jloc += 0.5 * qo * rr * rr;
+        fo[f][loc - wt.y * kTile] = qo * rr;
       }
-    } else {
-      // (through LDS: the cell's own entries by the masks were 2.7 % slower
-      // here, 122 x 238 in 4 boxes 270 -> 277 us; FP64 shares the masks with
-      // the block sweeps, which take a tile's chunks in any order)
-      const int o0 = D.obs_ptr[key], o1 = D.obs_ptr[key + 1];
-      if (o1 > o0) {
-        fo[0][threadIdx.x] = 0.0;
-        fo[1][threadIdx.x] = 0.0;
-        fo[2][threadIdx.x] = 0.0;
-        __syncthreads();
-        for (int o = o0 + int(threadIdx.x); o < o1; o += kTile) {
-          const int code = D.obs_code[o];
-          const int loc = code >> 2, f = code & 3;
-          const double rr = MODE == 3 ? double(D.dz[S.zoff + int64_t(n) * 3 * plane + f * plane + loc])
-                                      : double(Z[f * plane + loc]) - D.obs_val[o];
-          const double qo = D.obs_q[o];
-          if (MODE != 3) jloc += 0.5 * qo * rr * rr;
-          fo[f][loc - wt.y * kTile] = qo * rr;
-        }
-        __syncthreads();
-        fh = fo[0][threadIdx.x];
-        fu = fo[1][threadIdx.x];
-        fv = fo[2][threadIdx.x];
-      }
+      __syncthreads();
+      fh = fo[0][threadIdx.x];
+      fu = fo[1][threadIdx.x];
+      fv = fo[2][threadIdx.x];
+      if constexpr (kCellJ) jloc = jo[0][threadIdx.x] + jo[1][threadIdx.x] + jo[2][threadIdx.x];
     }
   }
 
