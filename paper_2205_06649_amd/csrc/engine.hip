@@ -842,6 +842,21 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
   for (int s = 0; s < P.nsub; ++s)
     for (int t = 0; t < c->subs[s].ntile; ++t) c->tiles[c->subs[s].tile0 + t] = make_int2(s, t);
 
+  // block sweeps (FP64, plain scheme), where their model finds them faster
+  BlkPlan blk{};
+  if (c->prec == DD4DVAR_FP64 && m.tz_p == 0) {
+    int cus = 0;
+    chk(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device), "attribute");
+    blk = plan_blocks(c->subs, c->maxlev, cus);
+    if (blk.ok) {
+      bool span = false;
+      for (const SubDev& S : c->subs) span = span || S.span;
+      chk(blk_prepare(blk.passes, span, blk.two), "block sweep set-up");
+      c->blk = BlkLaunch{nullptr, int(blk.work.size()), blk.levels, blk.passes, span, blk.two, blk.lds};
+      c->blk_ok = true;
+    }
+  }
+
   // whole-grid box
   SubDev& G = c->gsub;
   G = SubDev{};
@@ -943,14 +958,15 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
     }
   }
 
-  // each bin's entries ordered by cell, then field, and (plain scheme) the
-  // masks by which a lane finds its own cell's entries
+  // for the block sweeps: each bin's entries ordered by cell, then field, and
+  // the masks by which a lane finds its own cell's (112 B per bin that has
+  // entries: contexts without block sweeps do without)
   std::vector<int32_t> obin;
   std::vector<ObsTile> otile;
-  {
+  if (c->blk_ok) {
     std::vector<std::pair<int32_t, int32_t>> ord;
     std::vector<double> v2, q2;
-    if (m.tz_p == 0) obin.assign(nkeys, -1);
+    obin.assign(nkeys, -1);
     for (int64_t k = 0; k < nkeys; ++k) {
       const int32_t o0 = optr[k], o1 = optr[k + 1];
       if (o1 == o0) continue;
@@ -966,7 +982,6 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
           oq[o] = q2[ord[o - o0].second - o0];
         }
       }
-      if (m.tz_p != 0) continue;
       ObsTile t{};
       for (int32_t o = o1; o-- > o0;) {
         const int loc = (ocode[o] >> 2) % kTile;
@@ -1031,6 +1046,7 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
   c->obs_q = upload(c, oq, st);
   c->obs_bin = upload(c, obin, st);
   c->obs_tile = upload(c, otile, st);
+  c->blk.work = upload(c, blk.work, st);
   c->nbr_idx = upload(c, P.nbr_idx, st);
   c->hsrc = upload(c, P.halo_src, st);
   c->hoff = upload(c, P.halo_off, st);
@@ -1058,21 +1074,6 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
   c->targ = dalloc<char>(c, size_t(P.traj_total) * tsz + kBoxArenaTail);
   c->ring_bytes = size_t(std::max<int64_t>(ring_off, 1)) * tsz;
   c->ring = dalloc<char>(c, c->ring_bytes);
-  if (c->prec == DD4DVAR_FP64 && m.tz_p == 0) {
-    int cus = 0;
-    chk(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device), "attribute");
-    const BlkPlan plan = plan_blocks(c->subs, c->maxlev, cus);
-    if (plan.ok) {
-      bool span = false;
-      for (const SubDev& S : c->subs) span = span || S.span;
-      chk(blk_prepare(plan.passes, span, plan.two), "block sweep set-up");
-      c->blk = BlkLaunch{upload(c, plan.work, st), int(plan.work.size()), plan.levels, plan.passes, span,
-                         plan.two, plan.lds};
-      c->blk_ok = true;
-      // the pageable list is copied before it goes
-      chk(hipStreamSynchronize(st), "upload sync");
-    }
-  }
   // rolling adjoint levels: three per box, four for the block sweeps
   c->adj = dalloc<char>(c, size_t(std::max<int64_t>(c->blk_ok ? adj_off / 3 * 4 : adj_off, 1)) * tsz);
   if (P.model.tz_p > 0) {
