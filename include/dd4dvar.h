@@ -145,6 +145,13 @@ dd4dvar_status dd4dvar_plan_sizes(const dd4dvar_plan* plan, int32_t* nsub,
 dd4dvar_status dd4dvar_plan_subdomain_info(const dd4dvar_plan* plan, int32_t s,
                                            int64_t out[10]);
 
+/* The block sweeps that a context of this decomposition in FP64 plans on a
+ * device of `compute_units` compute units: out[5] = {levels per launch (0:
+ * step kernels), 1024-cell passes of the largest block, level frames on chip
+ * (1 or 2), blocks, boxes}.  Zeros for the Turkel-Zwas variant.  Host only. */
+dd4dvar_status dd4dvar_plan_block_sweeps(const dd4dvar_plan* plan, int32_t compute_units,
+                                         int32_t out[5]);
+
 /* Integer maps for bit-exact checks.  kind:
  *   0 HALO_SRC   per s, [nring]: source subdomain of each ring position, -1
  *                when the position wraps inside the box.  Ring positions:
@@ -294,7 +301,7 @@ dd4dvar_status dd4dvar_gather(dd4dvar_ctx* ctx, int32_t level, double* out_dev,
  *       per time step; in an FP64 context of the plain scheme with every
  *       level stored, where they are faster, block sweeps of the same
  *       results that take several steps, up to the whole window, per launch
- *       (get_timing counts the launches);
+ *       (get_block_sweeps tells which, get_timing counts the launches);
  *   1 = one launch per subdomain per step (the plain baseline);
  *   2 = persistent sweeps: one workgroup per subdomain holds the current
  *       level in LDS and the level before it in registers, one launch per
@@ -370,6 +377,11 @@ dd4dvar_status dd4dvar_get_solver_parts(const dd4dvar_ctx* ctx, int32_t out[2]);
  * adjoint (0 when it does not apply), 1 if the persistent modes apply}. */
 dd4dvar_status dd4dvar_get_exec_plan(const dd4dvar_ctx* ctx, int32_t out[4]);
 
+/* The block sweeps that mode 0 runs at present, as dd4dvar_plan_block_sweeps
+ * reports them; zeros where it runs the step kernels (FP32, Turkel-Zwas,
+ * checkpoints on, no plan, or another mode selected). */
+dd4dvar_status dd4dvar_get_block_sweeps(const dd4dvar_ctx* ctx, int32_t out[5]);
+
 /* Waits for the work queued on stream, then reads and clears the context's
  * non-finite flag: E_NONFINITE if any cost J_s, gradient entry, or
  * first-level adjoint entry (adjoint_integrate, gn_hessvec) computed since
@@ -432,7 +444,8 @@ dd4dvar_status dd4dvar_autotune(dd4dvar_ctx* ctx, const double* x_dev, double* J
  * sweep and the final reduction.  dd4dvar_get_timing waits for them and
  * returns, summed over the calls since the last query, out[6] = {forward ms,
  * adjoint ms, reduction ms, forward launches, adjoint launches, calls}, then
- * clears the record. */
+ * clears the record.  Block sweeps of whole boxes, which otherwise run forward
+ * and adjoint in one launch, take two while timing is on (the same results). */
 dd4dvar_status dd4dvar_set_timing(dd4dvar_ctx* ctx, int32_t on);
 dd4dvar_status dd4dvar_get_timing(dd4dvar_ctx* ctx, double out[6]);
 

@@ -79,6 +79,7 @@ _SIGS = {
     "dd4dvar_plan_destroy": (None, [_VP]),
     "dd4dvar_plan_sizes": (C.c_int, [_VP, C.POINTER(C.c_int32), C.POINTER(C.c_int64),
                                      C.POINTER(C.c_int64)]),
+    "dd4dvar_plan_block_sweeps": (C.c_int, [_VP, C.c_int32, C.POINTER(C.c_int32)]),
     "dd4dvar_plan_subdomain_info": (C.c_int, [_VP, C.c_int32, C.POINTER(C.c_int64)]),
     "dd4dvar_plan_get_map": (C.c_int, [_VP, C.c_int32, C.c_int32, C.POINTER(C.c_int64),
                                        C.POINTER(C.c_int32)]),
@@ -99,6 +100,7 @@ _SIGS = {
     "dd4dvar_set_exec_mode": (C.c_int, [_VP, C.c_int32]),
     "dd4dvar_set_exec_plan": (C.c_int, [_VP, C.c_int32, C.c_int32]),
     "dd4dvar_get_exec_plan": (C.c_int, [_VP, C.POINTER(C.c_int32)]),
+    "dd4dvar_get_block_sweeps": (C.c_int, [_VP, C.POINTER(C.c_int32)]),
     "dd4dvar_set_tz_kernels": (C.c_int, [_VP, C.c_int32]),
     "dd4dvar_get_tz_kernels": (C.c_int, [_VP, C.POINTER(C.c_int32)]),
     "dd4dvar_set_solver_parts": (C.c_int, [_VP, C.c_int32]),
@@ -178,6 +180,16 @@ def dd4dvar_plan_subdomain_info(plan, s):
     out = (C.c_int64 * 10)()
     check(lib().dd4dvar_plan_subdomain_info(plan, s, out))
     return list(out)
+
+
+def _block_sweeps(out):
+    return dict(zip(("levels", "passes", "frames", "blocks", "boxes"), out))
+
+
+def dd4dvar_plan_block_sweeps(plan, compute_units):
+    out = (C.c_int32 * 5)()
+    check(lib().dd4dvar_plan_block_sweeps(plan, compute_units, out))
+    return _block_sweeps(out)
 
 
 def dd4dvar_plan_get_map(plan, kind, s):
@@ -264,6 +276,12 @@ def dd4dvar_get_exec_plan(ctx):
     out = (C.c_int32 * 4)()
     check(lib().dd4dvar_get_exec_plan(ctx, out), ctx)
     return {"mode": out[0], "passes": out[1], "strip_rows": out[2], "persistent": bool(out[3])}
+
+
+def dd4dvar_get_block_sweeps(ctx):
+    out = (C.c_int32 * 5)()
+    check(lib().dd4dvar_get_block_sweeps(ctx, out), ctx)
+    return _block_sweeps(out)
 
 
 def dd4dvar_set_tz_kernels(ctx, kind):

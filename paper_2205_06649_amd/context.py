@@ -74,6 +74,11 @@ class Context:
         """{mode, passes, strip_rows, persistent} of the plan in use."""
         return L.dd4dvar_get_exec_plan(self.handle)
 
+    def block_sweeps(self):
+        """{levels per launch, passes, frames, blocks, boxes} of the FP64 block
+        sweeps in use (zeros: step kernels)."""
+        return L.dd4dvar_get_block_sweeps(self.handle)
+
     def set_tz_kernels(self, kind):
         """Turkel-Zwas forward and adjoint step kernels: 0 gather form,
         1 column walk (q = 2, p <= 8; the default where it applies), 2 the

@@ -858,41 +858,107 @@ constexpr int kBlkThreads = 1024;
 constexpr int kBlkPassMax = 6;             // 128 registers hold six passes
 constexpr int kBlkPassTwo = 3;             // and the LDS two frames of three
 
-// whether a block fits one workgroup, and what its levels cost
+// what a block of `steps` levels a launch takes of a workgroup
 struct BlkFit {
-  bool ok;
+  bool ok;                    // it has that
   int passes;                 // cells computed at a launch's first level, in passes
-  double us;                  // a level's time, both sweeps, on a compute unit of its own
-  double bytes;               // a level's memory traffic, both sweeps
   size_t lds, lds2;           // with one frame, with two
 };
+// first cell, and the one past the last, of the block grown by e rows
+int blk_lo(const SubDev& S, const BlkWork& w, int e) { return std::max(0, w.out0 - e * S.nx); }
+int blk_hi(const SubDev& S, const BlkWork& w, int e) { return std::min(S.ncell, w.out1 + e * S.nx); }
 BlkFit blk_fit(const SubDev& S, const BlkWork& w, int steps) {
-  auto lo = [&](int e) { return std::max(0, w.out0 - e * S.nx); };
-  auto hi = [&](int e) { return std::min(S.ncell, w.out1 + e * S.nx); };
-  const int rows = (hi(steps) - 1) / S.nx - lo(steps) / S.nx + 1;
+  const int rows = (blk_hi(S, w, steps) - 1) / S.nx - blk_lo(S, w, steps) / S.nx + 1;
   BlkFit f{};
   f.lds = size_t(rows + 2) * (S.nx + 2) * 3 * sizeof(double) + size_t(rows) * kRowTab * sizeof(double) +
           size_t(2 * rows + 2 * S.nx) * 3 * sizeof(double) +
           size_t((w.out1 - w.out0 + 255) / 64) * sizeof(double) + size_t(std::max(steps, S.nlev) + 2) * sizeof(int);
   f.lds2 = f.lds + size_t(rows + 2) * (S.nx + 2) * 3 * sizeof(double) + size_t(2 * rows + 2 * S.nx) * 3 * sizeof(double) +
            size_t((w.out1 - w.out0 + 255) / 64) * sizeof(double);
-  f.passes = (hi(steps - 1) - (lo(steps - 1) & ~63) + kBlkThreads - 1) / kBlkThreads;
-  double cells = 0.0;
-  for (int e = 0; e < steps; ++e) cells += double(hi(e) - lo(e)) / steps;
-  const double own = w.out1 - w.out0, in = hi(steps) - lo(steps);
-  f.us = 2.0 + 0.0031 * cells;
-  f.bytes = 24.0 * (own + 1.65 * cells + (4.0 * in + 2.0 * own) / steps);
+  f.passes = (blk_hi(S, w, steps - 1) - (blk_lo(S, w, steps - 1) & ~63) + kBlkThreads - 1) / kBlkThreads;
   f.ok = f.lds <= kBlkLdsMax && f.passes <= kBlkPassMax && 2 * (rows + S.nx) <= kBorderMax &&
          S.nx >= 2 && S.ny >= 2;
   return f;
 }
-// box s as nb blocks of whole tiles
-void cut_box(const SubDev& S, int s, int nb, std::vector<BlkWork>& out) {
-  for (int b = 0; b < nb; ++b) {
-    const int t0 = int(int64_t(S.ntile) * b / nb), t1 = int(int64_t(S.ntile) * (b + 1) / nb);
-    out.push_back(BlkWork{s, t0 * kTile, std::min(S.ncell, t1 * kTile)});
-  }
+// what a block's level costs, both sweeps
+struct BlkCost {
+  double us;                  // time on a compute unit of its own
+  double bytes;               // memory traffic
+};
+BlkCost blk_cost(const SubDev& S, const BlkWork& w, int steps) {
+  double cells = 0.0;
+  for (int e = 0; e < steps; ++e) cells += double(blk_hi(S, w, e) - blk_lo(S, w, e)) / steps;
+  const double own = w.out1 - w.out0, in = blk_hi(S, w, steps) - blk_lo(S, w, steps);
+  return {2.0 + 0.0031 * cells, 24.0 * (own + 1.65 * cells + (4.0 * in + 2.0 * own) / steps)};
 }
+// block b of a box cut into nb blocks of whole tiles: its first tile
+int cut_at(const SubDev& S, int nb, int b) { return int(int64_t(S.ntile) * b / nb); }
+BlkWork tiles_of(const SubDev& S, int t0, int t1) { return {0, t0 * kTile, std::min(S.ncell, t1 * kTile)}; }
+
+// The boxes of one shape and their cuts into blocks of one number of levels a
+// launch.  What a block takes grows with it: reach holds, for each first tile,
+// the tiles of the longest block that fits, so that a cut is tested by
+// comparisons, and boxes too wide for any block are known at once.
+struct BlkShape {
+  SubDev S;
+  std::vector<int> reach;
+  int most, least;            // most tiles of any block that fits; of as many every block fits
+  struct Cut {
+    std::vector<std::pair<double, BlkWork>> blocks;       // a launch's time, block
+    double us = 0.0, longest = 0.0, bytes = 0.0;
+    size_t lds = 0, lds2 = 0;
+    int passes = 0;
+  };
+  std::map<int, Cut> cuts;    // by the number of blocks
+  std::map<int, int> found;   // fewest blocks that fit, by the number asked for
+
+  // whether every tile fits as a block of its own
+  bool prepare(int steps) {
+    cuts.clear();
+    found.clear();
+    reach.assign(S.ntile, 0);
+    most = 0;
+    least = S.ntile;
+    for (int t = 0, end = 0; t < S.ntile; ++t) {
+      end = std::max(end, t);
+      while (end < S.ntile && blk_fit(S, tiles_of(S, t, end + 1), steps).ok) ++end;
+      if (end == t) return false;
+      reach[t] = end - t;
+      most = std::max(most, reach[t]);
+      if (end < S.ntile) least = std::min(least, reach[t]);
+    }
+    return true;
+  }
+  // the fewest blocks, at least nb0, of a cut whose blocks all fit
+  int blocks(int nb0) {
+    auto [it, fresh] = found.try_emplace(nb0, 0);
+    if (!fresh) return it->second;
+    int nb = std::max(nb0, (S.ntile + most - 1) / most);
+    for (; (S.ntile + nb - 1) / nb > least; ++nb) {       // (one block per tile fits)
+      int b = 0;
+      while (b < nb && cut_at(S, nb, b + 1) - cut_at(S, nb, b) <= reach[cut_at(S, nb, b)]) ++b;
+      if (b == nb) break;
+    }
+    return it->second = nb;
+  }
+  const Cut& cut(int nb, int steps) {
+    auto [it, fresh] = cuts.try_emplace(nb);
+    Cut& c = it->second;
+    for (int b = 0; fresh && b < nb; ++b) {
+      const BlkWork w = tiles_of(S, cut_at(S, nb, b), cut_at(S, nb, b + 1));
+      const BlkFit f = blk_fit(S, w, steps);
+      const BlkCost q = blk_cost(S, w, steps);
+      c.lds = std::max(c.lds, f.lds);
+      c.lds2 = std::max(c.lds2, f.lds2);
+      c.passes = std::max(c.passes, f.passes);
+      c.us += q.us;
+      c.longest = std::max(c.longest, q.us);
+      c.bytes += q.bytes;
+      c.blocks.emplace_back(q.us * std::min(steps, S.nlev), w);
+    }
+    return c;
+  }
+};
 }  // namespace
 
 // The decomposition into blocks that the model below finds fastest; not ok
@@ -908,75 +974,74 @@ BlkPlan plan_blocks(const std::vector<SubDev>& subs, int maxlev, int cus) {
   double cells = 0.0;
   for (const SubDev& S : subs) cells += S.ncell;
   const int levels = std::max(1, maxlev - 1);
+  // boxes of one shape are cut alike
+  std::vector<BlkShape> shapes;
+  std::vector<int> shape(subs.size());
+  {
+    std::map<std::array<int, 4>, int> index;
+    for (size_t s = 0; s < subs.size(); ++s) {
+      const SubDev& S = subs[s];
+      const auto [it, fresh] = index.try_emplace({S.ny, S.nx, S.nlev, S.span}, int(shapes.size()));
+      if (fresh) shapes.emplace_back().S = S;
+      shape[s] = it->second;
+    }
+  }
   BlkPlan best{};
   double best_us = levels * (std::max(4.5, cells * 72 / 4.4e6) + std::max(6.5, cells * 111 / 4.4e6));
   for (int k : {levels, 24, 16, 12, 10, 8, 7, 6, 5, 4, 3}) {
     if (k > levels) continue;
+    auto whole = [&](const SubDev& S) { return S.span || k == levels; };       // not to be cut
+    bool fits = true;
+    for (BlkShape& q : shapes) {
+      if (whole(q.S)) {
+        q.cuts.clear();
+        fits = blk_fit(q.S, tiles_of(q.S, 0, q.S.ntile), k).ok;
+      } else {
+        fits = q.prepare(k);
+      }
+      if (!fits) break;
+    }
+    if (!fits) continue;
+    std::vector<const BlkShape::Cut*> cut(shapes.size());
     for (int want : {1, cus / 2, cus * 3 / 4, cus * 7 / 8, cus, 2 * cus}) {     // blocks wanted on the whole
       BlkPlan p{};
       p.ok = true;
       p.levels = k;
       double sum = 0.0, longest = 0.0, bytes = 0.0;
-      size_t lds2 = 0;
-      std::vector<std::pair<double, BlkWork>> work;
-      // boxes of one shape are cut alike
-      struct Cut {
-        bool ok = false;
-        std::vector<std::pair<double, BlkWork>> blocks;
-        double us = 0.0, most = 0.0, bytes = 0.0;
-        size_t lds = 0, lds2 = 0;
-        int passes = 0;
-      };
-      std::map<std::array<int, 4>, Cut> cuts;
-      for (size_t s = 0; s < subs.size() && p.ok; ++s) {
-        const SubDev& S = subs[s];
-        const bool whole = S.span || k == levels;   // not to be cut
-        auto [it, fresh] = cuts.try_emplace({S.ny, S.nx, S.nlev, S.span});
-        Cut& c = it->second;
-        int nb = whole ? 1 : std::min(S.ntile, std::max(1, int(want * (S.ncell / cells) + 0.5)));
-        for (; fresh && nb <= S.ntile; ++nb) {
-          c = Cut{};
-          c.ok = true;
-          std::vector<BlkWork> blocks;
-          cut_box(S, 0, nb, blocks);
-          for (const BlkWork& w : blocks) {
-            const BlkFit f = blk_fit(S, w, k);
-            c.ok = c.ok && f.ok;
-            c.lds = std::max(c.lds, f.lds);
-            c.lds2 = std::max(c.lds2, f.lds2);
-            c.passes = std::max(c.passes, f.passes);
-            c.us += f.us;
-            c.most = std::max(c.most, f.us);
-            c.bytes += f.bytes;
-            c.blocks.emplace_back(f.us * std::min(k, S.nlev), w);
-          }
-          if (c.ok || whole) break;
-        }
-        p.ok = c.ok;
-        p.lds = std::max(p.lds, c.lds);
-        lds2 = std::max(lds2, c.lds2);
-        p.passes = std::max(p.passes, c.passes);
-        for (auto w : c.blocks) {
-          w.second.box = int(s);
-          work.push_back(w);
-        }
-        sum += c.us;
-        bytes += c.bytes;
-        longest = std::max(longest, c.most);
+      size_t lds2 = 0, nwork = 0;
+      for (size_t i = 0; i < shapes.size(); ++i) {
+        BlkShape& q = shapes[i];
+        const int nb0 = std::min(q.S.ntile, std::max(1, int(want * (q.S.ncell / cells) + 0.5)));
+        cut[i] = &q.cut(whole(q.S) ? 1 : q.blocks(nb0), k);
+        p.lds = std::max(p.lds, cut[i]->lds);
+        lds2 = std::max(lds2, cut[i]->lds2);
+        p.passes = std::max(p.passes, cut[i]->passes);
+        longest = std::max(longest, cut[i]->longest);
       }
-      const double pack = int(work.size()) <= cus ? longest : sum / cus + 0.5 * longest;
+      for (int i : shape) {
+        sum += cut[i]->us;
+        bytes += cut[i]->bytes;
+        nwork += cut[i]->blocks.size();
+      }
+      const double pack = int(nwork) <= cus ? longest : sum / cus + 0.5 * longest;
       const double us = (levels + k - 1) / k * 10.0 + levels * std::max(pack, bytes / 4.0e6);
-      if (!p.ok || us >= best_us) continue;
+      if (us >= best_us) continue;
       p.two = p.passes <= kBlkPassTwo && lds2 <= kBlkLdsMax;
       if (p.two) p.lds = lds2;
       best = p;
       best_us = us;
       best.us = us;
       if (k == levels) best.levels = maxlev;          // no box is cut: one launch per sweep
+      std::vector<std::pair<double, BlkWork>> work;
+      for (size_t s = 0; s < subs.size(); ++s)
+        for (auto w : cut[shape[s]]->blocks) {
+          w.second.box = int(s);
+          work.push_back(w);
+        }
       // launch order: the longest first where blocks differ, else box by box
       // (one XCD holding neighbouring blocks, as the step kernels do: 8.0 ->
       // 8.5 ms on 1024 boxes of 72 x 136 cells)
-      if (longest > 1.25 * sum / double(work.size()))
+      if (longest > 1.25 * sum / double(nwork))
         std::stable_sort(work.begin(), work.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
       best.work.clear();
       for (const auto& w : work) best.work.push_back(w.second);

@@ -1388,6 +1388,44 @@ dd4dvar_status dd4dvar_get_solver_parts(const dd4dvar_ctx* ctx, int32_t out[2]) 
   return DD4DVAR_OK;
 }
 
+dd4dvar_status dd4dvar_plan_block_sweeps(const dd4dvar_plan* plan, int32_t compute_units,
+                                         int32_t out[5]) {
+  if (!plan || !out || compute_units < 1) return DD4DVAR_E_INVALID;
+  std::fill(out, out + 5, 0);
+  if (plan->model.tz_p != 0) return DD4DVAR_OK;
+  API_GUARD(nullptr, {
+    std::vector<SubDev> subs;
+    int maxlev = 0;
+    for (const BoxInfo& b : plan->boxes) {
+      SubDev& S = subs.emplace_back();
+      S.ny = b.ny;
+      S.nx = b.nx;
+      S.nlev = b.nlev;
+      S.span = b.span;
+      S.ncell = int32_t(b.ncell());
+      S.ntile = (S.ncell + kTile - 1) / kTile;
+      maxlev = std::max(maxlev, b.nlev);
+    }
+    const BlkPlan p = plan_blocks(subs, maxlev, compute_units);
+    if (p.ok) {
+      const int32_t v[5] = {p.levels, p.passes, p.two ? 2 : 1, int32_t(p.work.size()), int32_t(subs.size())};
+      std::copy(v, v + 5, out);
+    }
+    return DD4DVAR_OK;
+  })
+}
+
+dd4dvar_status dd4dvar_get_block_sweeps(const dd4dvar_ctx* ctx, int32_t out[5]) {
+  if (!ctx || !out) return fail(const_cast<dd4dvar_ctx*>(ctx), DD4DVAR_E_INVALID, "null argument");
+  std::fill(out, out + 5, 0);
+  if (blk_sweeps(ctx)) {
+    const BlkLaunch& b = ctx->blk;
+    const int32_t v[5] = {b.levels, b.passes, b.two ? 2 : 1, b.nwork, ctx->nsub};
+    std::copy(v, v + 5, out);
+  }
+  return DD4DVAR_OK;
+}
+
 dd4dvar_status dd4dvar_get_exec_plan(const dd4dvar_ctx* ctx, int32_t out[4]) {
   if (!ctx || !out) return fail(const_cast<dd4dvar_ctx*>(ctx), DD4DVAR_E_INVALID, "null argument");
   out[0] = ctx->exec_mode;

@@ -77,6 +77,9 @@ class Plan:
     def sizes(self):
         return L.dd4dvar_plan_sizes(self.handle)
 
+    def block_sweeps(self, compute_units=256):
+        return L.dd4dvar_plan_block_sweeps(self.handle, compute_units)
+
     def info(self, s):
         return L.dd4dvar_plan_subdomain_info(self.handle, s)
 
