@@ -1,4 +1,10 @@
-"""Plans of the FP64 block sweeps (host)."""
+"""The FP64 block sweeps by the plan that they run: whole boxes and boxes cut
+into blocks, blocks of one to six passes of 1024 cells, one and two level frames
+on chip, boxes spanning the circle alone and beside cut ones.  The plan of
+every case is pinned on the host (256 compute units) and, on the device, every
+sweep of it equals the step kernels (mode 1, one launch per box and level) bit
+for bit.  Solves, whose evaluations and products leave out the boxes that have
+stopped, are compared the same way."""
 import time
 
 import numpy as np
@@ -7,6 +13,46 @@ import pytest
 import synth
 
 BASE = dict(index=350, overlap_cells=3, overlap_steps=2, obs_frac=0.02, obs_every=3)
+# levels per launch, passes, frames, blocks
+CASES = {
+    "whole_1_two": (dict(nlat=30, nlon=26, nsteps=5, bands=3, pieces=2, ntime=1), (6, 1, 2, 6)),
+    "whole_2_two": (dict(nlat=27, nlon=210, nsteps=4, bands=1, pieces=6, ntime=1), (5, 2, 2, 6)),
+    "whole_3_two": (dict(nlat=132, nlon=504, nsteps=20, bands=6, pieces=6, ntime=4), (10, 3, 2, 144)),
+    "whole_3_one": (dict(nlat=726, nlon=108, nsteps=20, bands=6, pieces=6, ntime=4), (10, 3, 1, 144)),
+    "whole_4_one": (dict(nlat=445, nlon=192, nsteps=20, bands=5, pieces=8, ntime=4, overlap_cells=4,
+                         overlap_steps=3), (12, 4, 1, 160)),
+    "whole_5_one": (dict(nlat=465, nlon=272, nsteps=20, bands=5, pieces=8, ntime=4, overlap_cells=4),
+                    (10, 5, 1, 160)),
+    "whole_6_one": (dict(nlat=348, nlon=444, nsteps=16, bands=6, pieces=6, ntime=4, overlap_cells=4,
+                         overlap_steps=1), (7, 6, 1, 144)),
+    "cut_1_two": (dict(nlat=24, nlon=60, nsteps=10, bands=1, pieces=2, ntime=2, overlap_cells=4,
+                       overlap_steps=1), (3, 1, 2, 16)),
+    "cut_2_two": (dict(nlat=20, nlon=156, nsteps=24, bands=1, pieces=2, ntime=1), (6, 2, 2, 14)),
+    "cut_2_one": (dict(nlat=28, nlon=590, nsteps=4, bands=1, pieces=2, ntime=1, overlap_cells=4),
+                  (3, 2, 1, 68)),
+    "cut_3_two": (dict(nlat=180, nlon=484, nsteps=10, bands=6, pieces=4, ntime=2, overlap_cells=4,
+                       overlap_steps=3), (4, 3, 2, 192)),
+    "cut_3_one": (dict(nlat=17, nlon=1354, nsteps=8, bands=1, pieces=3, ntime=2, overlap_cells=2),
+                  (3, 3, 1, 126)),
+    "cut_4_one": (dict(nlat=48, nlon=858, nsteps=10, bands=4, pieces=2, ntime=2, overlap_steps=3),
+                  (4, 4, 1, 192)),
+    "cut_5_one": (dict(nlat=66, nlon=1110, nsteps=16, bands=6, pieces=3, ntime=4), (4, 5, 1, 144)),
+    "cut_6_one": (dict(nlat=228, nlon=756, nsteps=16, bands=4, pieces=6, ntime=4, overlap_steps=3),
+                  (8, 6, 1, 192)),
+    "span_1_two": (dict(nlat=20, nlon=36, nsteps=4, bands=2, pieces=1, ntime=1), (5, 1, 2, 2)),
+    "span_2_two": (dict(nlat=43, nlon=30, nsteps=4, bands=1, pieces=1, ntime=1, overlap_cells=0),
+                   (5, 2, 2, 1)),
+    "span_3_two": (dict(nlat=81, nlon=26, nsteps=10, bands=1, pieces=1, ntime=2, overlap_cells=0),
+                   (8, 3, 2, 2)),
+    "span_3_one": (dict(nlat=33, nlon=182, nsteps=48, bands=3, pieces=1, ntime=2, overlap_cells=2,
+                        overlap_steps=1), (26, 3, 1, 6)),
+    "span_5_one": (dict(nlat=512, nlon=128, nsteps=96, bands=16, pieces=1, ntime=16, obs_frac=0.005),
+                   (11, 5, 1, 256)),
+    "span_6_one": (dict(nlat=320, nlon=200, nsteps=64, bands=16, pieces=1, ntime=8), (13, 6, 1, 128)),
+    # polar caps of one piece beside bands of three: caps whole, the others cut
+    "caps_cut": (dict(nlat=120, nlon=160, nsteps=24, bands=4, pieces=3, ntime=2, caps=True),
+                 (12, 2, 2, 116)),
+}
 
 
 def _problem(cfg, south_only=False):
@@ -32,6 +78,18 @@ def _problem(cfg, south_only=False):
         "obs_step", "obs_cell", "obs_field", "obs_sigma", "obs_noise")})
 
 
+def _pinned(which, plan):
+    assert (plan["levels"], plan["passes"], plan["frames"], plan["blocks"]) == CASES[which][1], plan
+
+
+@pytest.mark.parametrize("which", list(CASES))
+def test_plan(which):
+    from paper_2205_06649_amd.descriptors import Plan
+    p = Plan(_problem(CASES[which][0]))
+    _pinned(which, p.block_sweeps(256))
+    p.close()
+
+
 @pytest.mark.parametrize("pieces", [2, 4])
 def test_plan_of_wide_boxes_is_quick(pieces):
     """No block of a box of 1024 x 1032 cells fits a workgroup, nor one of
@@ -46,3 +104,77 @@ def test_plan_of_wide_boxes_is_quick(pieces):
     print(pieces, f"{t:.4f} s", flush=True)
     p.close()
     assert plan["levels"] == 0 and t < 0.5
+
+
+def _context(p):
+    import torch
+    from paper_2205_06649_amd.context import Context
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the pinned plans are for 256 compute units")
+    return Context(p, "fp64")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("which", list(CASES))
+def test_sweeps_equal_step_kernels(which):
+    import torch
+    ctx = _context(_problem(CASES[which][0]))
+    plan = ctx.block_sweeps()
+    _pinned(which, plan)
+    nlev = max(int(i[5]) for i in ctx.info)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(3)
+
+    def noise(n):
+        return torch.randn(n, generator=gen, device="cuda:0", dtype=torch.float64)
+
+    x = ctx.background_controls() + noise(ctx.ctrl_len)
+    dx, force = noise(ctx.ctrl_len), noise(ctx.traj_len)
+
+    def everything():
+        J, g = ctx.cost_grad(x)
+        return dict(J=J, grad=g, cost_adjoint=ctx.adjoint(), traj=ctx.forward(x),
+                    adjoint=ctx.adjoint(force), tangent=ctx.tangent_linear(dx),
+                    product=ctx.gn_hessvec(dx))
+
+    print(which, plan, flush=True)
+    blocks = everything()
+    ctx.set_timing(True)                     # forward and adjoint in launches of their own
+    J, g = ctx.cost_grad(x)
+    launches = ctx.get_timing()
+    ctx.set_timing(False)
+    blocks.update(J_timed=J, grad_timed=g)
+    assert launches["fwd_launches"] == max(1, -(-(nlev - 1) // plan["levels"]))
+    assert launches["adj_launches"] == -(-nlev // plan["levels"])
+    ctx.set_exec_mode(1)
+    assert ctx.block_sweeps()["levels"] == 0
+    steps = everything()
+    steps.update(J_timed=steps["J"], grad_timed=steps["grad"])
+    for k in blocks:
+        assert torch.equal(blocks[k], steps[k]), k
+        assert torch.isfinite(blocks[k]).all(), k
+    ctx.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("solver", ["lbfgs", "gn"])
+@pytest.mark.parametrize("which", ["whole_2_two", "whole_3_one", "cut_1_two", "cut_4_one", "span_1_two"])
+def test_solves_equal_step_kernels(which, solver):
+    """Boxes stop at different rounds (no observations in the north) and are
+    left out from then on."""
+    import torch
+    p = _problem(CASES[which][0], south_only=True)
+    out = []
+    for mode in (0, 1):
+        ctx = _context(p)
+        if mode == 0:
+            _pinned(which, ctx.block_sweeps())
+        ctx.set_exec_mode(mode)
+        xa, rep, _, xo = ctx.solve(max_outer=2, max_iter=6, outer_tol=0.0, grad_rtol=0.05, cg_max_iter=8,
+                                   local_solver=solver, want_controls=True)
+        out.append((xa, xo, rep.total_evals, rep.lbfgs_iters, rep.J_final, rep.gnorm_ratio_max))
+        ctx.close()
+    a, b = out
+    print(which, solver, a[2:], flush=True)
+    assert a[2:] == b[2:] and np.isfinite(a[0]).all()
+    assert np.array_equal(a[0], b[0]) and torch.equal(a[1], b[1])
