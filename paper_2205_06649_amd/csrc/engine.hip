@@ -696,7 +696,8 @@ void exchange_lockstep(dd4dvar_ctx* c, const double* x, hipStream_t st) {
       launch_targets_from_local<T>(D, n, tb[j], nt[j], c->jc_split, c->jc, st);
     }
   }
-  launch_reduce_jconst(c->d_subs, c->nsub, c->jc, c->jc_split, 0.5 * P.model.mu_overlap, c->jconst, st);
+  launch_reduce_jconst(c->d_subs, c->nsub, c->ntiles, c->jc, c->jc_split, 0.5 * P.model.mu_overlap, c->jconst,
+                       st);
   chk(hipGetLastError(), "exchange launch");
   // every frozen ring entry of every level has been staged; copied (not
   // swapped) so that recorded graphs keep pointing at the live rings
@@ -714,7 +715,8 @@ void exchange_impl(dd4dvar_ctx* c, const double* x, hipStream_t st) {
   Dom<T> D = local_dom<T>(c);
   launch_ring_from_local<T>(D, 0, c->nsub, c->ring_blocks, -1, st);
   launch_targets_from_local<T>(D, -1, 0, c->ntiles, c->jc_split, c->jc, st);   // every level
-  launch_reduce_jconst(c->d_subs, c->nsub, c->jc, c->jc_split, 0.5 * c->plan.model.mu_overlap, c->jconst, st);
+  launch_reduce_jconst(c->d_subs, c->nsub, c->ntiles, c->jc, c->jc_split, 0.5 * c->plan.model.mu_overlap,
+                       c->jconst, st);
   chk(hipGetLastError(), "exchange launch");
 }
 
@@ -1062,7 +1064,9 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
   // the sums are the same bits.  FP64, 128 x 256 in 32 boxes of half of 50 steps:
   // 110 us in rows with one sum, 64 us in the order of perm, 28 us with several.
   c->jc_split = std::max(1, std::min({8, 4096 / std::max(1, tile), c->maxlev}));
-  c->jc = dalloc<double>(c, int64_t(tile) * (kTile / 64) * c->jc_split);
+  const int64_t njc = int64_t(tile) * (kTile / 64) * c->jc_split;
+  c->jc = dalloc<double>(c, njc);
+  chk(hipMemsetAsync(c->jc, 0, size_t(njc) * sizeof(double), st), "memset sums");
   c->jconst = dalloc<double>(c, P.nsub);
   c->xb = dalloc<double>(c, P.ctrl_total);
   c->d_ids = dalloc<int32_t>(c, P.nsub);

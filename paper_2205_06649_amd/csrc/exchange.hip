@@ -30,6 +30,7 @@ constexpr int kGather = sizeof(T) == 4 ? 8 : 4;
 constexpr int kRingSplit = 8;
 
 constexpr int kWaves = kTile / 64;         // partial sums per tile
+constexpr int kRedMax = 1024;              // threads that add up a box's partial sums, at most
 }  // namespace
 
 // targets (and backgrounds at level 0) from the global FP64 trajectory, whose
@@ -131,8 +132,15 @@ __global__ __launch_bounds__(kTile) void k_targets_from_local(Dom<T> D, int leve
   // levels n0, n0 + split, ...: one of the sums z = 0 .. split - 1 of the wave
   const int n0 = level < 0 ? int(blockIdx.y) : level, n1 = level < 0 ? S.nlev : level + 1;
   if (n0 >= S.nlev) return;                 // uniform over the block
-  const int nq = S.nbr1 - S.nbr0;           // <= 64 (checked at set-up)
   const int lane = threadIdx.x & 63;
+  // the wave's cells in the exchange's order
+  const int e = wt.y * kTile + threadIdx.x;
+  const bool valid = e < S.ncell;
+  const int m = D.perm[S.perm0 + (valid ? e : 0)];
+  const int cov = valid ? int(D.cover[S.cell_off + m]) : 0;
+  // where the wave's sum of these levels goes
+  double* J = jc + (int64_t(w) * kWaves + (threadIdx.x >> 6)) * split + n0 % split;
+  const int nq = S.nbr1 - S.nbr0;           // <= 64 (checked at set-up)
   // the lane's entry: first level, levels, first row and column, width,
   // height, cells, state offset
   int my_lev0 = 0, my_nlev = 0, my_row0 = 0, my_col0 = 0, my_nx = 0, my_ny = 0, my_ncell = 0;
@@ -148,10 +156,6 @@ __global__ __launch_bounds__(kTile) void k_targets_from_local(Dom<T> D, int leve
     my_ncell = P.ncell;
     my_zoff = P.zoff;
   }
-  // the wave's cells in the exchange's order
-  const int e = wt.y * kTile + threadIdx.x;
-  const bool valid = e < S.ncell;
-  const int m = D.perm[S.perm0 + (valid ? e : 0)];
   const int r = m / S.nx, c = m - r * S.nx;
   const int grow = S.row0 + r;
   int gcol = S.col0 + c;
@@ -167,7 +171,6 @@ __global__ __launch_bounds__(kTile) void k_targets_from_local(Dom<T> D, int leve
     hits |= uint64_t(hit) << i;
     wave_hits |= uint64_t(__ballot(hit) != 0) << i;
   }
-  const int cov = valid ? int(D.cover[S.cell_off + m]) : 0;
   const bool band = __any(cov > 1);         // a cell that other boxes of the interval cover
   const int64_t plane = S.ncell;
   double acc = 0.0;                         // the wave's sum over levels
@@ -264,24 +267,31 @@ __global__ __launch_bounds__(kTile) void k_targets_from_local(Dom<T> D, int leve
     // every cell of the wave there is no spread to sum
     if (__any(jloc != 0.0)) acc += stencil::wave_sum(jloc);
   }
-  double* J = jc + (int64_t(w) * kWaves + (threadIdx.x >> 6)) * split + n0 % split;
   if (lane == 0) *J = (n0 < split) ? acc : *J + acc;
 }
 
-// one wave per box: lane l sums the partial sums l, l + 64, ... in order, then a
-// butterfly whose pairs add the same two values in either order
-__global__ __launch_bounds__(256) void k_reduce_jconst(const SubDev* __restrict__ subs, int nsub,
-                                                       const double* __restrict__ jc, int split,
-                                                       double half_mu, double* __restrict__ jconst) {
-  const int s = int(blockIdx.x) * 4 + int(threadIdx.x >> 6);
-  if (s >= nsub) return;                    // uniform over the wave
-  const SubDev S = subs[s];
+// One workgroup per box: thread t adds its partial sums t, t + blockDim.x, ... in order
+// (their loads are independent of one another), then the wave's tree, then
+// the waves in order.  Sums that hold no level of their box are zero since
+// the context's creation.  (One wave per box with an index division per sum:
+// exchange of two FP64 boxes of 256 x 512 cells, 8192 sums each, 208 us, now 171;
+// of four FP32 boxes of 1024 x 2048, 32768 sums each, 1.82 ms, now 1.57.)
+__global__ __launch_bounds__(kRedMax) void k_reduce_jconst(const SubDev* __restrict__ subs,
+                                                         const double* __restrict__ jc, int split,
+                                                         double half_mu, double* __restrict__ jconst) {
+  __shared__ double red[kRedMax / 64];
+  const SubDev& S = subs[blockIdx.x];
+  const double* p = jc + int64_t(S.tile0) * kWaves * split;
+  const int n = S.ntile * kWaves * split;
   double acc = 0.0;
-  const int nz = S.nlev < split ? S.nlev : split;        // sums that hold levels
-  for (int t = int(threadIdx.x & 63); t < S.ntile * kWaves * nz; t += 64)
-    acc += jc[(int64_t(S.tile0) * kWaves + t / nz) * split + t % nz];
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-  if ((threadIdx.x & 63) == 0) jconst[s] = half_mu * acc;
+#pragma unroll 8
+  for (int t = int(threadIdx.x); t < n; t += int(blockDim.x)) acc += p[t];
+  acc = stencil::wave_sum(acc);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int i = 1; i < int(blockDim.x >> 6); ++i) acc += red[i];
+  jconst[blockIdx.x] = half_mu * acc;
 }
 
 template <typename T>
@@ -353,10 +363,11 @@ void launch_targets_from_local(const Dom<T>& D, int level, int tile_base, int nt
   hipLaunchKernelGGL(k_targets_from_local<T>, dim3(ntiles, level < 0 ? split : 1), dim3(kTile), 0, st, D,
                      level, tile_base, split, jc);
 }
-void launch_reduce_jconst(const SubDev* subs, int nsub, const double* jc, int split,
+void launch_reduce_jconst(const SubDev* subs, int nsub, int ntiles, const double* jc, int split,
                           double half_mu, double* jconst, hipStream_t st) {
-  hipLaunchKernelGGL(k_reduce_jconst, dim3((nsub + 3) / 4), dim3(256), 0, st, subs, nsub, jc, split,
-                     half_mu, jconst);
+  // many sums in few boxes: a thread's own take longer than 16 waves' meeting
+  const int threads = int64_t(ntiles) * kWaves * split > int64_t(2048) * nsub ? kRedMax : 256;
+  hipLaunchKernelGGL(k_reduce_jconst, dim3(nsub), dim3(threads), 0, st, subs, jc, split, half_mu, jconst);
 }
 template <typename T>
 void launch_gather(const Dom<T>& D, int nspace, int ntime, int level, int64_t ncell,

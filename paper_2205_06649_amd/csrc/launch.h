@@ -35,7 +35,7 @@ void launch_ring_from_local(const Dom<T>& D, int box_base, int nbox, int ring_bl
 template <typename T>
 void launch_targets_from_local(const Dom<T>& D, int level, int tile_base, int ntiles, int split,
                                double* jc, hipStream_t st);
-void launch_reduce_jconst(const SubDev* subs, int nsub, const double* jc, int split,
+void launch_reduce_jconst(const SubDev* subs, int nsub, int ntiles, const double* jc, int split,
                           double half_mu, double* jconst, hipStream_t st);
 template <typename T>
 void launch_gather(const Dom<T>& D, int nspace, int ntime, int level, int64_t ncell,
