@@ -891,29 +891,43 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
   // other cells have nothing to do at levels that one interval holds)
   std::vector<int32_t> perm(size_t(P.cell_ptr[P.nspace]));
   {
-    std::vector<std::pair<uint64_t, int32_t>> band;
+    // by runs of cells of a row with one set: the boxes of a cell's row that
+    // are also boxes of its column
+    struct Run {
+      uint64_t set;
+      int32_t e0, e1;
+      bool operator<(const Run& o) const { return set != o.set ? set < o.set : e0 < o.e0; }
+    };
+    std::vector<Run> band, rest;
+    std::vector<uint64_t> in_row, in_col;
     for (int i = 0; i < P.nspace; ++i) {
       const BoxInfo& b = P.boxes[i];
       const int32_t* cov = P.cover_box.data() + P.cell_ptr[i];
-      int32_t* out = perm.data() + P.cell_ptr[i];
-      band.clear();
-      for (int e = 0; e < int(b.ncell()); ++e) {
-        if (cov[e] <= 1) continue;
-        uint64_t set = 0;
-        for (int64_t q = P.nbr_ptr[i]; q < P.nbr_ptr[i + 1]; ++q) {
-          const BoxInfo& o = P.boxes[P.nbr_idx[q]];
-          if (P.nbr_idx[q] >= P.nspace) break;        // (sorted: the first interval's boxes come first)
-          int cc = b.col0 + e % b.nx - o.col0;
-          cc = ((cc % m.nlon) + m.nlon) % m.nlon;
-          const int rr = b.row0 + e / b.nx - o.row0;
-          if (rr >= 0 && rr < o.ny && cc < o.nx) set |= uint64_t(1) << (q - P.nbr_ptr[i]);
-        }
-        band.emplace_back(set, e);
+      in_row.assign(b.ny, 0);
+      in_col.assign(b.nx, 0);
+      for (int64_t q = P.nbr_ptr[i]; q < P.nbr_ptr[i + 1]; ++q) {
+        if (P.nbr_idx[q] >= P.nspace) break;          // (sorted: the first interval's boxes come first)
+        const BoxInfo& o = P.boxes[P.nbr_idx[q]];
+        const uint64_t bit = uint64_t(1) << (q - P.nbr_ptr[i]);
+        for (int r = std::max(0, o.row0 - b.row0); r < std::min(b.ny, o.row0 + o.ny - b.row0); ++r) in_row[r] |= bit;
+        for (int c = 0; c < b.nx; ++c)
+          if ((b.col0 + c - o.col0 + 2 * m.nlon) % m.nlon < o.nx) in_col[c] |= bit;
       }
+      band.clear();
+      rest.clear();
+      for (int r = 0, e = 0; r < b.ny; ++r)
+        for (int c = 0; c < b.nx; ++c, ++e) {
+          const bool covered = cov[e] > 1;
+          const uint64_t set = covered ? in_row[r] & in_col[c] : 0;
+          std::vector<Run>& to = covered ? band : rest;
+          if (c > 0 && !to.empty() && to.back().e1 == e && to.back().set == set) to.back().e1 = e + 1;
+          else to.push_back({set, e, e + 1});
+        }
       std::sort(band.begin(), band.end());
-      for (const auto& cell : band) *out++ = cell.second;
-      for (int e = 0; e < int(b.ncell()); ++e)
-        if (cov[e] <= 1) *out++ = e;
+      int32_t* out = perm.data() + P.cell_ptr[i];
+      for (const auto* runs : {&band, &rest})
+        for (const Run& q : *runs)
+          for (int32_t e = q.e0; e < q.e1; ++e) *out++ = e;
     }
   }
   const int64_t nkeys = int64_t(tile) * c->maxlev;
@@ -969,6 +983,7 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
     std::vector<std::pair<int32_t, int32_t>> ord;
     std::vector<double> v2, q2;
     obin.assign(nkeys, -1);
+    otile.reserve(size_t(std::min(nkeys, nent)));
     for (int64_t k = 0; k < nkeys; ++k) {
       const int32_t o0 = optr[k], o1 = optr[k + 1];
       if (o1 == o0) continue;
