@@ -91,6 +91,10 @@ __global__ __launch_bounds__(kTile) void k_tlm(Dom<T> D, int n, int tile_base) {
   const T st = D.st, stg = D.stg, h0 = D.h0;
   T dH, dU, dV;
   if constexpr (sizeof(T) == 8) {
+    // (every load first: left to itself the compiler holds the rows' back behind
+    // the first products: two boxes of 256 x 512, 24 levels 219 -> 206 us, two of
+    // 33 x 86, 53 levels 208 -> 202, 64 of 38 x 1024 1387 -> 1359)
+    __builtin_amdgcn_sched_barrier(0);
     const V3<T> F = swe_tangent(C, E, W, N, Sv, dC, dE, dW, dN, dS, rc.a1, rc.a2, rc.a3, rc.cf, rc.ct,
                                 cN, cS, st, stg, h0);
     dH = F.h;
