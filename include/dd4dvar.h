@@ -146,11 +146,14 @@ dd4dvar_status dd4dvar_plan_subdomain_info(const dd4dvar_plan* plan, int32_t s,
                                            int64_t out[10]);
 
 /* The block sweeps that a context of this decomposition in FP64 plans on a
- * device of `compute_units` compute units: out[5] = {levels per launch (0:
+ * device of `compute_units` compute units: out[6] = {levels per launch (0:
  * step kernels), 1024-cell passes of the largest block, level frames on chip
- * (1 or 2), blocks, boxes}.  Zeros for the Turkel-Zwas variant.  Host only. */
+ * (1 or 2), blocks, boxes, the sweeps that run in blocks: 1 forward + 2
+ * adjoint of the cost + 4 adjoint of a forcing + 8 both of the Gauss-Newton
+ * product + 16 tangent linear (the others run the step kernels)}.  Zeros for the
+ * Turkel-Zwas variant.  Host only. */
 dd4dvar_status dd4dvar_plan_block_sweeps(const dd4dvar_plan* plan, int32_t compute_units,
-                                         int32_t out[5]);
+                                         int32_t out[6]);
 
 /* Integer maps for bit-exact checks.  kind:
  *   0 HALO_SRC   per s, [nring]: source subdomain of each ring position, -1
@@ -380,7 +383,7 @@ dd4dvar_status dd4dvar_get_exec_plan(const dd4dvar_ctx* ctx, int32_t out[4]);
 /* The block sweeps that mode 0 runs at present, as dd4dvar_plan_block_sweeps
  * reports them; zeros where it runs the step kernels (FP32, Turkel-Zwas,
  * checkpoints on, no plan, or another mode selected). */
-dd4dvar_status dd4dvar_get_block_sweeps(const dd4dvar_ctx* ctx, int32_t out[5]);
+dd4dvar_status dd4dvar_get_block_sweeps(const dd4dvar_ctx* ctx, int32_t out[6]);
 
 /* Waits for the work queued on stream, then reads and clears the context's
  * non-finite flag: E_NONFINITE if any cost J_s, gradient entry, or

@@ -183,11 +183,11 @@ def dd4dvar_plan_subdomain_info(plan, s):
 
 
 def _block_sweeps(out):
-    return dict(zip(("levels", "passes", "frames", "blocks", "boxes"), out))
+    return dict(zip(("levels", "passes", "frames", "blocks", "boxes", "sweeps"), out))
 
 
 def dd4dvar_plan_block_sweeps(plan, compute_units):
-    out = (C.c_int32 * 5)()
+    out = (C.c_int32 * 6)()
     check(lib().dd4dvar_plan_block_sweeps(plan, compute_units, out))
     return _block_sweeps(out)
 
@@ -279,7 +279,7 @@ def dd4dvar_get_exec_plan(ctx):
 
 
 def dd4dvar_get_block_sweeps(ctx):
-    out = (C.c_int32 * 5)()
+    out = (C.c_int32 * 6)()
     check(lib().dd4dvar_get_block_sweeps(ctx, out), ctx)
     return _block_sweeps(out)
 

@@ -75,8 +75,8 @@ class Context:
         return L.dd4dvar_get_exec_plan(self.handle)
 
     def block_sweeps(self):
-        """{levels per launch, passes, frames, blocks, boxes} of the FP64 block
-        sweeps in use (zeros: step kernels)."""
+        """{levels per launch, passes, frames, blocks, boxes, sweeps} of the FP64
+        block sweeps in use (zeros: step kernels)."""
         return L.dd4dvar_get_block_sweeps(self.handle)
 
     def set_tz_kernels(self, kind):

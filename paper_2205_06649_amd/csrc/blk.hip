@@ -882,6 +882,7 @@ BlkFit blk_fit(const SubDev& S, const BlkWork& w, int steps) {
 }
 // what a block's level costs, both sweeps
 struct BlkCost {
+  double cells;               // computed, on the mean of a launch's levels
   double us;                  // time on a compute unit of its own
   double bytes;               // memory traffic
 };
@@ -889,7 +890,7 @@ BlkCost blk_cost(const SubDev& S, const BlkWork& w, int steps) {
   double cells = 0.0;
   for (int e = 0; e < steps; ++e) cells += double(blk_hi(S, w, e) - blk_lo(S, w, e)) / steps;
   const double own = w.out1 - w.out0, in = blk_hi(S, w, steps) - blk_lo(S, w, steps);
-  return {2.0 + 0.0031 * cells, 24.0 * (own + 1.65 * cells + (4.0 * in + 2.0 * own) / steps)};
+  return {cells, 2.0 + 0.0031 * cells, 24.0 * (own + 1.65 * cells + (4.0 * in + 2.0 * own) / steps)};
 }
 // block b of a box cut into nb blocks of whole tiles: its first tile
 int cut_at(const SubDev& S, int nb, int b) { return int(int64_t(S.ntile) * b / nb); }
@@ -905,7 +906,7 @@ struct BlkShape {
   int most, least;            // most tiles of any block that fits; of as many every block fits
   struct Cut {
     std::vector<std::pair<double, BlkWork>> blocks;       // a launch's time, block
-    double us = 0.0, longest = 0.0, bytes = 0.0;
+    double us = 0.0, longest = 0.0, bytes = 0.0, cells = 0.0;   // cells: of the largest block
     size_t lds = 0, lds2 = 0;
     int passes = 0;
   };
@@ -953,6 +954,7 @@ struct BlkShape {
       c.passes = std::max(c.passes, f.passes);
       c.us += q.us;
       c.longest = std::max(c.longest, q.us);
+      c.cells = std::max(c.cells, q.cells);
       c.bytes += q.bytes;
       c.blocks.emplace_back(q.us * std::min(steps, S.nlev), w);
     }
@@ -961,15 +963,53 @@ struct BlkShape {
 };
 }  // namespace
 
-// The decomposition into blocks that the model below finds fastest; not ok
-// where no box decomposition fits or the step kernels are faster.  Measured
-// (both sweeps, one block to a compute unit): a level takes 3.9 us for 570
-// cells and 9.4 us for 2350, 10 us per launch besides; memory moves 4 TB/s
-// under these kernels; the step kernels take a launch of at least 4.5 and 6.5
-// us per level, or 72 + 111 B per cell at 4.4 TB/s.  More blocks than boxes
-// spread few boxes over the chip (64 boxes of 40 x 72 cells: 64 whole ones 430
-// us per evaluation, 256 blocks of 7 levels 301 us, 480 of 5 454 us), at the
-// price of the rows that two blocks compute both.
+// The sweeps that are faster in blocks, where every block has a compute unit of
+// its own: `most` cells computed per level in the largest block, `steps` levels
+// per launch, `whole` where no box is cut, `cells` of all boxes.  (With more blocks
+// than units the step kernels are bound by memory: every sweep was faster in
+// blocks, by a fifth at least.)  Lines through measured times of a level, us:
+// a block's grow with its cells and, cut, with the levels that a launch loads; a
+// step kernel's are a launch, and more with more cells, until memory binds it.
+// Step kernel against block:
+//                          forward     cost adj.  forced adj.  tangent   product
+//   2 spheres 20 x 50     3.6 -> 1.5  5.4 -> 3.2  4.0 -> 2.5  3.8 -> 2.7   8.4 -> 5.7
+//   2 spheres 24 x 70     3.5 -> 2.3  5.3 -> 4.6  3.9 -> 3.7  3.8 -> 4.0   8.4 -> 8.5
+//   2 spheres 25 x 84     3.5 -> 2.6  5.2 -> 5.7  3.9 -> 4.9  3.8 -> 5.0   8.4 -> 10.9
+//   2 spheres 33 x 86     3.6 -> 3.7  5.2 -> 7.6  4.0 -> 6.1  3.8 -> 6.5   8.6 -> 14.0
+//   64 boxes 26 x 64      4.3 -> 2.3  6.6 -> 5.1  5.2 -> 3.8  5.1 -> 4.2  11.4 -> 9.1
+//   4 boxes 40 x 358,
+//    128 blocks, 3 levels 3.5 -> 3.1  5.6 -> 6.4  4.4 -> 5.3  4.0 -> 4.8  11.9 -> 14.3
+//   24 boxes 34 x 266,
+//    192 blocks, 5 levels 5.1 -> 3.7  7.9 -> 7.9  6.6 -> 6.7  6.3 -> 6.3  16.3 -> 16.7
+//   32 boxes 38 x 246,
+//    192 blocks, 5 levels 6.6 -> 4.0 11.0 -> 8.7  9.2 -> 7.5  8.3 -> 7.0  21.9 -> 19.3
+int blk_faster(double most, int steps, bool whole, double cells) {
+  struct Line {
+    double block, per_cell, launch, launch_cut, step, step_per_cell, step_memory;
+    double gain(double most, int steps, bool whole, double cells) const {
+      return std::max(step + step_per_cell * cells, step_memory * cells) -
+             (block + per_cell * most + (whole ? launch : launch_cut) / steps);
+    }
+  };
+  constexpr Line fwd = {0.5, 0.00107, 2.0, 4.0, 3.5, 0.75e-5, 1.6e-5};
+  constexpr Line adj = {1.1, 0.00215, 3.0, 8.5, 5.2, 1.25e-5, 3.2e-5};
+  constexpr Line forced = {0.8, 0.0017, 4.0, 7.0, 4.0, 1.25e-5, 2.8e-5};
+  constexpr Line gn = {0.9, 0.00215, 4.0, 8.0, 4.6, 1.25e-5, 2.9e-5};
+  constexpr Line tlm = {0.85, 0.0020, 1.0, 4.5, 3.8, 1.25e-5, 2.5e-5};
+  auto gain = [&](const Line& l) { return l.gain(most, steps, whole, cells); };
+  return (gain(fwd) > 0 ? kBlkFwd : 0) | (gain(adj) > 0 ? kBlkAdj : 0) | (gain(forced) > 0 ? kBlkForced : 0) |
+         (gain(tlm) > 0 ? kBlkTlm : 0) | (gain(tlm) + gain(gn) > 0 ? kBlkProduct : 0);
+}
+
+// The decomposition into blocks that the model below finds fastest for an
+// evaluation, and the sweeps that it serves; not ok where no box decomposition
+// fits or the step kernels are faster.  Measured (both sweeps, one block to a
+// compute unit): a level takes 3.9 us for 570 cells and 9.4 us for 2350, 10 us
+// per launch besides; memory moves 4 TB/s under these kernels; the step kernels
+// are taken at 4.5 and 6.5 us per level, or 72 + 111 B per cell at 4.4 TB/s.  More
+// blocks than boxes spread few boxes over the chip (64 boxes of 40 x 72 cells: 64
+// whole ones 430 us per evaluation, 256 blocks of 7 levels 301 us, 480 of 5 454
+// us), at the price of the rows that two blocks compute both.
 BlkPlan plan_blocks(const std::vector<SubDev>& subs, int maxlev, int cus) {
   double cells = 0.0;
   for (const SubDev& S : subs) cells += S.ncell;
@@ -1007,7 +1047,7 @@ BlkPlan plan_blocks(const std::vector<SubDev>& subs, int maxlev, int cus) {
       BlkPlan p{};
       p.ok = true;
       p.levels = k;
-      double sum = 0.0, longest = 0.0, bytes = 0.0;
+      double sum = 0.0, longest = 0.0, bytes = 0.0, most = 0.0;
       size_t lds2 = 0, nwork = 0;
       for (size_t i = 0; i < shapes.size(); ++i) {
         BlkShape& q = shapes[i];
@@ -1017,6 +1057,7 @@ BlkPlan plan_blocks(const std::vector<SubDev>& subs, int maxlev, int cus) {
         lds2 = std::max(lds2, cut[i]->lds2);
         p.passes = std::max(p.passes, cut[i]->passes);
         longest = std::max(longest, cut[i]->longest);
+        most = std::max(most, cut[i]->cells);
       }
       for (int i : shape) {
         sum += cut[i]->us;
@@ -1026,6 +1067,7 @@ BlkPlan plan_blocks(const std::vector<SubDev>& subs, int maxlev, int cus) {
       const double pack = int(nwork) <= cus ? longest : sum / cus + 0.5 * longest;
       const double us = (levels + k - 1) / k * 10.0 + levels * std::max(pack, bytes / 4.0e6);
       if (us >= best_us) continue;
+      p.sweeps = int(nwork) <= cus ? blk_faster(most, k, nwork == subs.size(), cells) : kBlkAll;
       p.two = p.passes <= kBlkPassTwo && lds2 <= kBlkLdsMax;
       if (p.two) p.lds = lds2;
       best = p;
@@ -1047,6 +1089,7 @@ BlkPlan plan_blocks(const std::vector<SubDev>& subs, int maxlev, int cus) {
       for (const auto& w : work) best.work.push_back(w.second);
     }
   }
+  best.ok = best.ok && best.sweeps;
   return best;
 }
 

@@ -393,8 +393,11 @@ void global_forward(dd4dvar_ctx* c, const double* x, double* traj, hipStream_t s
   chk(hipGetLastError(), "global forward launch");
 }
 
-// whether the sweeps over every box take several levels per launch
-bool blk_sweeps(const dd4dvar_ctx* c) { return c->blk_ok && c->exec_mode == 0 && c->ckpt == 0; }
+// the sweeps over every box that take several levels per launch (BlkSweep bits)
+int blk_sweeps(const dd4dvar_ctx* c) {
+  return c->blk_ok && c->exec_mode == 0 && c->ckpt == 0 ? c->blk.sweeps : 0;
+}
+int blk_adjoint(int mode) { return mode == 1 ? kBlkForced : mode == 3 ? kBlkProduct : kBlkAdj; }
 // launches over `levels` levels, and levels of each but the last (even shares
 // within the plan's limit)
 int blk_launches(const dd4dvar_ctx* c, int levels, int* each) {
@@ -426,7 +429,7 @@ void local_forward(dd4dvar_ctx* c, const double* x, hipStream_t st, double* traj
     }
   }
   if constexpr (std::is_same<T, double>::value) {
-    if (blk_sweeps(c)) {
+    if (blk_sweeps(c) & kBlkFwd) {
       int each = 0;
       const int count = blk_launches(c, c->maxlev - 1, &each);
       for (int i = 0; i < count; ++i) launch_fwd_blk(D, c->blk, i * each, each, x, traj_out, st);
@@ -468,7 +471,7 @@ void local_adjoint(dd4dvar_ctx* c, int mode, const double* x, const double* forc
     }
   }
   if constexpr (std::is_same<T, double>::value) {
-    if (!ids && blk_sweeps(c)) {
+    if (!ids && (blk_sweeps(c) & blk_adjoint(mode))) {
       int each = 0;
       const int count = blk_launches(c, c->maxlev, &each);
       for (int i = 0; i < count; ++i) {
@@ -518,9 +521,11 @@ void ensure_dz(dd4dvar_ctx* c) {
 
 // tangent-linear sweeps of every box (or of the boxes in c->eval_mask) about
 // the stored trajectory: dZ = M' dx, every level into the dz arena (the
-// persistent per-box kernel in modes 2 and 3, else the step kernels)
+// persistent per-box kernel in modes 2 to 4, block sweeps in FP64 mode 0 where
+// they are faster, alone or (product) with the adjoint of the Gauss-Newton
+// product, else the step kernels)
 template <typename T>
-void local_tlm(dd4dvar_ctx* c, const double* dx, hipStream_t st, double* dtraj_out = nullptr) {
+void local_tlm(dd4dvar_ctx* c, const double* dx, hipStream_t st, bool product, double* dtraj_out = nullptr) {
   ensure_dz(c);
   Dom<T> D = local_dom<T>(c);
   if constexpr (std::is_same<T, float>::value) {
@@ -530,7 +535,7 @@ void local_tlm(dd4dvar_ctx* c, const double* dx, hipStream_t st, double* dtraj_o
       if (dtraj_out) launch_dz_out<T>(D, dtraj_out, 0, c->ntiles, st);
       return;
     }
-  } else if (blk_sweeps(c)) {
+  } else if (blk_sweeps(c) & (product ? kBlkProduct : kBlkTlm)) {
     int each = 0;
     const int count = blk_launches(c, c->maxlev - 1, &each);
     for (int i = 0; i < count; ++i) launch_tlm_blk(D, c->blk, i * each, each, dx, dtraj_out, st);
@@ -563,7 +568,7 @@ void local_tlm(dd4dvar_ctx* c, const double* dx, hipStream_t st, double* dtraj_o
 // adjoint sweep forced by the observation and overlap weights applied to dZ
 template <typename T>
 void gn_product(dd4dvar_ctx* c, const double* dx, double* out, hipStream_t st) {
-  local_tlm<T>(c, dx, st);
+  local_tlm<T>(c, dx, st, true);
   local_adjoint<T>(c, 3, nullptr, nullptr, out, nullptr, st);
 }
 
@@ -604,7 +609,8 @@ void cost_grad_impl(dd4dvar_ctx* c, const std::vector<int32_t>* ids, const doubl
   }
   if constexpr (std::is_same<T, double>::value) {
     // (phase timing keeps the sweeps apart)
-    if (!ids && blk_sweeps(c) && c->blk.levels >= c->maxlev && !c->timing) {
+    constexpr int both = kBlkFwd | kBlkAdj;
+    if (!ids && (blk_sweeps(c) & both) == both && c->blk.levels >= c->maxlev && !c->timing) {
       launch_eval_blk(D, c->blk, c->maxlev, x, c->xb, grad, st);
       chk(hipGetLastError(), "evaluation launch");
       c->have_forward = true;
@@ -645,10 +651,10 @@ void cost_grad_impl(dd4dvar_ctx* c, const std::vector<int32_t>* ids, const doubl
       nf = na = 1;                      // one persistent launch per sweep
     } else if (!ids && c->exec_mode == 0) {
       nf = na = c->maxlev;
-      if (std::is_same<T, double>::value && blk_sweeps(c)) {
+      if (std::is_same<T, double>::value) {
         int each = 0;
-        nf = blk_launches(c, c->maxlev - 1, &each);
-        na = blk_launches(c, c->maxlev, &each);
+        if (blk_sweeps(c) & kBlkFwd) nf = blk_launches(c, c->maxlev - 1, &each);
+        if (blk_sweeps(c) & kBlkAdj) na = blk_launches(c, c->maxlev, &each);
       }
     } else {
       for (const SubDev& S : c->subs)
@@ -854,7 +860,7 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
       bool span = false;
       for (const SubDev& S : c->subs) span = span || S.span;
       chk(blk_prepare(blk.passes, span, blk.two), "block sweep set-up");
-      c->blk = BlkLaunch{nullptr, int(blk.work.size()), blk.levels, blk.passes, span, blk.two, blk.lds};
+      c->blk = BlkLaunch{nullptr, int(blk.work.size()), blk.levels, blk.passes, blk.sweeps, span, blk.two, blk.lds};
       c->blk_ok = true;
     }
   }
@@ -979,7 +985,7 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
   // entries: contexts without block sweeps do without)
   std::vector<int32_t> obin;
   std::vector<ObsTile> otile;
-  if (c->blk_ok) {
+  if (c->blk_ok && (c->blk.sweeps & (kBlkAdj | kBlkProduct))) {
     std::vector<std::pair<int32_t, int32_t>> ord;
     std::vector<double> v2, q2;
     obin.assign(nkeys, -1);
@@ -1408,9 +1414,9 @@ dd4dvar_status dd4dvar_get_solver_parts(const dd4dvar_ctx* ctx, int32_t out[2]) 
 }
 
 dd4dvar_status dd4dvar_plan_block_sweeps(const dd4dvar_plan* plan, int32_t compute_units,
-                                         int32_t out[5]) {
+                                         int32_t out[6]) {
   if (!plan || !out || compute_units < 1) return DD4DVAR_E_INVALID;
-  std::fill(out, out + 5, 0);
+  std::fill(out, out + 6, 0);
   if (plan->model.tz_p != 0) return DD4DVAR_OK;
   API_GUARD(nullptr, {
     std::vector<SubDev> subs;
@@ -1427,20 +1433,21 @@ dd4dvar_status dd4dvar_plan_block_sweeps(const dd4dvar_plan* plan, int32_t compu
     }
     const BlkPlan p = plan_blocks(subs, maxlev, compute_units);
     if (p.ok) {
-      const int32_t v[5] = {p.levels, p.passes, p.two ? 2 : 1, int32_t(p.work.size()), int32_t(subs.size())};
-      std::copy(v, v + 5, out);
+      const int32_t v[6] = {p.levels, p.passes, p.two ? 2 : 1, int32_t(p.work.size()), int32_t(subs.size()),
+                            p.sweeps};
+      std::copy(v, v + 6, out);
     }
     return DD4DVAR_OK;
   })
 }
 
-dd4dvar_status dd4dvar_get_block_sweeps(const dd4dvar_ctx* ctx, int32_t out[5]) {
+dd4dvar_status dd4dvar_get_block_sweeps(const dd4dvar_ctx* ctx, int32_t out[6]) {
   if (!ctx || !out) return fail(const_cast<dd4dvar_ctx*>(ctx), DD4DVAR_E_INVALID, "null argument");
-  std::fill(out, out + 5, 0);
+  std::fill(out, out + 6, 0);
   if (blk_sweeps(ctx)) {
     const BlkLaunch& b = ctx->blk;
-    const int32_t v[5] = {b.levels, b.passes, b.two ? 2 : 1, b.nwork, ctx->nsub};
-    std::copy(v, v + 5, out);
+    const int32_t v[6] = {b.levels, b.passes, b.two ? 2 : 1, b.nwork, ctx->nsub, b.sweeps};
+    std::copy(v, v + 6, out);
   }
   return DD4DVAR_OK;
 }
@@ -1751,9 +1758,9 @@ dd4dvar_status dd4dvar_tangent_linear(dd4dvar_ctx* ctx, const double* dx_dev, do
   API_GUARD(ctx, {
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (ctx->prec == DD4DVAR_FP64) {
-      local_tlm<double>(ctx, dx_dev, st, dtraj_dev);
+      local_tlm<double>(ctx, dx_dev, st, false, dtraj_dev);
     } else {
-      local_tlm<float>(ctx, dx_dev, st, dtraj_dev);
+      local_tlm<float>(ctx, dx_dev, st, false, dtraj_dev);
     }
     chk(hipGetLastError(), "tangent-linear output launch");
     return DD4DVAR_OK;

@@ -125,12 +125,15 @@ hipError_t launch_eval_box(const Dom<float>& D, const double* x, const double* x
 struct BlkWork {
   int32_t box, out0, out1;
 };
+// the sweeps, as bits (product: both of the Gauss-Newton product)
+enum BlkSweep { kBlkFwd = 1, kBlkAdj = 2, kBlkForced = 4, kBlkProduct = 8, kBlkTlm = 16, kBlkAll = 31 };
 // the decomposition of every box into blocks: levels per launch (all of them
 // where no box is cut), passes of 1024 cells, frames (two: one for either level on chip),
-// LDS bytes of the largest block; us: the model's time per evaluation
+// the sweeps that are faster in blocks, LDS bytes of the largest block; us: the
+// model's time per evaluation
 struct BlkPlan {
   bool ok, two;
-  int levels, passes;
+  int levels, passes, sweeps;
   size_t lds;
   double us;
   std::vector<BlkWork> work;
@@ -139,7 +142,7 @@ constexpr size_t kBlkLdsMax = 160 * 1024 - 512;
 BlkPlan plan_blocks(const std::vector<SubDev>& subs, int maxlev, int cus);
 struct BlkLaunch {
   const BlkWork* work;
-  int nwork, levels, passes;
+  int nwork, levels, passes, sweeps;
   bool span, two;                         // some box spans the circle; two frames
   size_t lds;
 };

@@ -1,10 +1,11 @@
 """The FP64 block sweeps by the plan that they run: whole boxes and boxes cut
 into blocks, blocks of one to six passes of 1024 cells, one and two level frames
-on chip, boxes spanning the circle alone and beside cut ones.  The plan of
-every case is pinned on the host (256 compute units) and, on the device, every
-sweep of it equals the step kernels (mode 1, one launch per box and level) bit
-for bit.  Solves, whose evaluations and products leave out the boxes that have
-stopped, are compared the same way."""
+on chip, boxes spanning the circle alone and beside cut ones, and plans of which
+only some sweeps run in blocks (the others in step kernels).  The plan of every
+case is pinned on the host (256 compute units) and, on the device, every sweep
+of it equals the step kernels (mode 1, one launch per box and level) bit for bit.
+Solves, whose evaluations and products leave out the boxes that have stopped,
+are compared the same way."""
 import time
 
 import numpy as np
@@ -13,45 +14,55 @@ import pytest
 import synth
 
 BASE = dict(index=350, overlap_cells=3, overlap_steps=2, obs_frac=0.02, obs_every=3)
-# levels per launch, passes, frames, blocks
+# levels per launch, passes, frames, blocks, sweeps in blocks (1 forward, 2 cost adjoint, 4
+# forced adjoint, 8 Gauss-Newton product, 16 tangent linear)
 CASES = {
-    "whole_1_two": (dict(nlat=30, nlon=26, nsteps=5, bands=3, pieces=2, ntime=1), (6, 1, 2, 6)),
-    "whole_2_two": (dict(nlat=27, nlon=210, nsteps=4, bands=1, pieces=6, ntime=1), (5, 2, 2, 6)),
-    "whole_3_two": (dict(nlat=132, nlon=504, nsteps=20, bands=6, pieces=6, ntime=4), (10, 3, 2, 144)),
-    "whole_3_one": (dict(nlat=726, nlon=108, nsteps=20, bands=6, pieces=6, ntime=4), (10, 3, 1, 144)),
+    "whole_1_two": (dict(nlat=30, nlon=26, nsteps=5, bands=3, pieces=2, ntime=1), (6, 1, 2, 6, 31)),
+    "whole_2_two": (dict(nlat=27, nlon=210, nsteps=4, bands=1, pieces=6, ntime=1), (5, 2, 2, 6, 31)),
+    "whole_3_two": (dict(nlat=132, nlon=504, nsteps=20, bands=6, pieces=6, ntime=4), (10, 3, 2, 144, 31)),
+    "whole_3_one": (dict(nlat=726, nlon=108, nsteps=20, bands=6, pieces=6, ntime=4), (10, 3, 1, 144, 31)),
     "whole_4_one": (dict(nlat=445, nlon=192, nsteps=20, bands=5, pieces=8, ntime=4, overlap_cells=4,
-                         overlap_steps=3), (12, 4, 1, 160)),
+                         overlap_steps=3), (12, 4, 1, 160, 31)),
     "whole_5_one": (dict(nlat=465, nlon=272, nsteps=20, bands=5, pieces=8, ntime=4, overlap_cells=4),
-                    (10, 5, 1, 160)),
+                    (10, 5, 1, 160, 31)),
     "whole_6_one": (dict(nlat=348, nlon=444, nsteps=16, bands=6, pieces=6, ntime=4, overlap_cells=4,
-                         overlap_steps=1), (7, 6, 1, 144)),
+                         overlap_steps=1), (7, 6, 1, 144, 31)),
     "cut_1_two": (dict(nlat=24, nlon=60, nsteps=10, bands=1, pieces=2, ntime=2, overlap_cells=4,
-                       overlap_steps=1), (3, 1, 2, 16)),
-    "cut_2_two": (dict(nlat=20, nlon=156, nsteps=24, bands=1, pieces=2, ntime=1), (6, 2, 2, 14)),
-    "cut_2_one": (dict(nlat=28, nlon=590, nsteps=4, bands=1, pieces=2, ntime=1, overlap_cells=4),
-                  (3, 2, 1, 68)),
+                       overlap_steps=1), (3, 1, 2, 16, 31)),
+    "cut_2_two": (dict(nlat=20, nlon=156, nsteps=24, bands=1, pieces=2, ntime=1), (6, 2, 2, 14, 31)),
+    "cut_2_one": (dict(nlat=27, nlon=526, nsteps=8, bands=2, pieces=2, ntime=2, overlap_steps=3),
+                  (4, 2, 1, 140, 31)),
+    "cut_2_some": (dict(nlat=28, nlon=590, nsteps=4, bands=1, pieces=2, ntime=1, overlap_cells=4),
+                   (3, 2, 1, 68, 1)),
+    "cut_2_fwd_tlm": (dict(nlat=28, nlon=852, nsteps=5, bands=2, pieces=3, ntime=1, overlap_cells=2,
+                           overlap_steps=1), (3, 2, 1, 108, 17)),
     "cut_3_two": (dict(nlat=180, nlon=484, nsteps=10, bands=6, pieces=4, ntime=2, overlap_cells=4,
-                       overlap_steps=3), (4, 3, 2, 192)),
-    "cut_3_one": (dict(nlat=17, nlon=1354, nsteps=8, bands=1, pieces=3, ntime=2, overlap_cells=2),
-                  (3, 3, 1, 126)),
-    "cut_4_one": (dict(nlat=48, nlon=858, nsteps=10, bands=4, pieces=2, ntime=2, overlap_steps=3),
-                  (4, 4, 1, 192)),
-    "cut_5_one": (dict(nlat=66, nlon=1110, nsteps=16, bands=6, pieces=3, ntime=4), (4, 5, 1, 144)),
+                       overlap_steps=3), (4, 3, 2, 192, 31)),
+    "cut_3_one": (dict(nlat=13, nlon=2070, nsteps=12, bands=1, pieces=9, ntime=2, overlap_cells=4,
+                       overlap_steps=4), (5, 3, 1, 216, 31)),
+    "cut_4_one": (dict(nlat=37, nlon=1028, nsteps=20, bands=2, pieces=4, ntime=4), (5, 4, 1, 192, 31)),
+    "cut_4_some": (dict(nlat=37, nlon=1740, nsteps=16, bands=1, pieces=6, ntime=2, overlap_cells=2,
+                        overlap_steps=1), (5, 4, 1, 192, 5)),
+    "cut_5_one": (dict(nlat=66, nlon=1110, nsteps=16, bands=6, pieces=3, ntime=4), (4, 5, 1, 144, 31)),
     "cut_6_one": (dict(nlat=228, nlon=756, nsteps=16, bands=4, pieces=6, ntime=4, overlap_steps=3),
-                  (8, 6, 1, 192)),
-    "span_1_two": (dict(nlat=20, nlon=36, nsteps=4, bands=2, pieces=1, ntime=1), (5, 1, 2, 2)),
+                  (8, 6, 1, 192, 31)),
+    "span_1_two": (dict(nlat=20, nlon=36, nsteps=4, bands=2, pieces=1, ntime=1), (5, 1, 2, 2, 31)),
     "span_2_two": (dict(nlat=43, nlon=30, nsteps=4, bands=1, pieces=1, ntime=1, overlap_cells=0),
-                   (5, 2, 2, 1)),
-    "span_3_two": (dict(nlat=81, nlon=26, nsteps=10, bands=1, pieces=1, ntime=2, overlap_cells=0),
-                   (8, 3, 2, 2)),
-    "span_3_one": (dict(nlat=33, nlon=182, nsteps=48, bands=3, pieces=1, ntime=2, overlap_cells=2,
-                        overlap_steps=1), (26, 3, 1, 6)),
+                   (5, 2, 2, 1, 31)),
+    "span_2_some": (dict(nlat=27, nlon=92, nsteps=112, bands=2, pieces=1, ntime=8, overlap_cells=4),
+                    (19, 2, 2, 16, 15)),
+    "span_3_two": (dict(nlat=273, nlon=44, nsteps=48, bands=7, pieces=1, ntime=8, overlap_cells=4),
+                   (11, 3, 2, 56, 31)),
+    "span_3_some": (dict(nlat=33, nlon=182, nsteps=48, bands=3, pieces=1, ntime=2, overlap_cells=2,
+                         overlap_steps=1), (26, 3, 1, 6, 1)),
+    "span_3_one": (dict(nlat=192, nlon=150, nsteps=64, bands=16, pieces=1, ntime=8), (13, 3, 1, 128, 31)),
+    "span_4_one": (dict(nlat=400, nlon=100, nsteps=64, bands=16, pieces=1, ntime=8), (13, 4, 1, 128, 31)),
     "span_5_one": (dict(nlat=512, nlon=128, nsteps=96, bands=16, pieces=1, ntime=16, obs_frac=0.005),
-                   (11, 5, 1, 256)),
-    "span_6_one": (dict(nlat=320, nlon=200, nsteps=64, bands=16, pieces=1, ntime=8), (13, 6, 1, 128)),
+                   (11, 5, 1, 256, 31)),
+    "span_6_one": (dict(nlat=320, nlon=200, nsteps=64, bands=16, pieces=1, ntime=8), (13, 6, 1, 128, 31)),
     # polar caps of one piece beside bands of three: caps whole, the others cut
     "caps_cut": (dict(nlat=120, nlon=160, nsteps=24, bands=4, pieces=3, ntime=2, caps=True),
-                 (12, 2, 2, 116)),
+                 (12, 2, 2, 116, 31)),
 }
 
 
@@ -79,7 +90,7 @@ def _problem(cfg, south_only=False):
 
 
 def _pinned(which, plan):
-    assert (plan["levels"], plan["passes"], plan["frames"], plan["blocks"]) == CASES[which][1], plan
+    assert tuple(plan[k] for k in ("levels", "passes", "frames", "blocks", "sweeps")) == CASES[which][1], plan
 
 
 @pytest.mark.parametrize("which", list(CASES))
@@ -144,8 +155,9 @@ def test_sweeps_equal_step_kernels(which):
     launches = ctx.get_timing()
     ctx.set_timing(False)
     blocks.update(J_timed=J, grad_timed=g)
-    assert launches["fwd_launches"] == max(1, -(-(nlev - 1) // plan["levels"]))
-    assert launches["adj_launches"] == -(-nlev // plan["levels"])
+    # (the step kernels take a launch per level)
+    assert launches["fwd_launches"] == (max(1, -(-(nlev - 1) // plan["levels"])) if plan["sweeps"] & 1 else nlev)
+    assert launches["adj_launches"] == (-(-nlev // plan["levels"]) if plan["sweeps"] & 2 else nlev)
     ctx.set_exec_mode(1)
     assert ctx.block_sweeps()["levels"] == 0
     steps = everything()
@@ -158,7 +170,8 @@ def test_sweeps_equal_step_kernels(which):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("solver", ["lbfgs", "gn"])
-@pytest.mark.parametrize("which", ["whole_2_two", "whole_3_one", "cut_1_two", "cut_4_one", "span_1_two"])
+@pytest.mark.parametrize("which", ["whole_2_two", "whole_3_one", "cut_1_two", "cut_4_one",
+                                   "cut_2_some", "span_1_two"])
 def test_solves_equal_step_kernels(which, solver):
     """Boxes stop at different rounds (no observations in the north) and are
     left out from then on."""
