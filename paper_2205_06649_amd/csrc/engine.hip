@@ -894,7 +894,14 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
   // cells of every spatial piece in the exchange's order: those that other
   // boxes of the interval cover first, ordered by the set of those boxes (a
   // wave then visits the boxes that its own cells share, and the tiles of the
-  // other cells have nothing to do at levels that one interval holds)
+  // other cells have nothing to do at levels that one interval holds).  Rows
+  // of fewer than 56 cells stay as they are: their east and west overlaps lie in
+  // the same lines or adjacent ones, which waves of their own would each move (4
+  // bands of 64 rows, 4 intervals of 16 steps, overlap 3 or 4; targets and rings,
+  // rows -> sets: 20 columns FP32 396 -> 440 us, FP64 673 -> 872; 46 columns 309 ->
+  // 324, 432 -> 473; 58 columns 288 -> 275, 449 -> 458; 72 columns 272 -> 210, 368
+  // -> 301; 136 columns 222 -> 167, 275 -> 241)
+  constexpr int kRowsMin = 56;
   std::vector<int32_t> perm(size_t(P.cell_ptr[P.nspace]));
   {
     // by runs of cells of a row with one set: the boxes of a cell's row that
@@ -923,7 +930,7 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
       rest.clear();
       for (int r = 0, e = 0; r < b.ny; ++r)
         for (int c = 0; c < b.nx; ++c, ++e) {
-          const bool covered = cov[e] > 1;
+          const bool covered = cov[e] > 1 && b.nx >= kRowsMin;
           const uint64_t set = covered ? in_row[r] & in_col[c] : 0;
           std::vector<Run>& to = covered ? band : rest;
           if (c > 0 && !to.empty() && to.back().e1 == e && to.back().set == set) to.back().e1 = e + 1;
@@ -931,9 +938,16 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
         }
       std::sort(band.begin(), band.end());
       int32_t* out = perm.data() + P.cell_ptr[i];
+      bool in_rows = true;
+      int32_t next = 0;
       for (const auto* runs : {&band, &rest})
-        for (const Run& q : *runs)
+        for (const Run& q : *runs) {
+          in_rows = in_rows && q.e0 == next;
           for (int32_t e = q.e0; e < q.e1; ++e) *out++ = e;
+          next = q.e1;
+        }
+      // pieces that stay in rows need no index
+      for (int s = i; in_rows && s < P.nsub; s += P.nspace) c->subs[s].perm0 = -1;
     }
   }
   const int64_t nkeys = int64_t(tile) * c->maxlev;

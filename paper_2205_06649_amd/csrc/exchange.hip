@@ -113,10 +113,11 @@ __global__ void k_ring_from_local(Dom<T> D, int box_base, int level) {
 // differ little between boxes, so the shifted sums lose nothing to
 // cancellation).
 //
-// The cells come in the order of Dom::perm: in rows, almost every wave of a
-// box touches its east and west overlaps and visits their boxes with a
-// fraction of its lanes; in that order a wave's cells share their boxes and
-// the waves without a covered cell have nothing to do.  The waves need
+// The cells of wide pieces come in the order of Dom::perm: in rows, almost every
+// wave of a box touches its east and west overlaps and visits their boxes with
+// a fraction of its lanes; in that order a wave's cells share their boxes and
+// the waves without a covered cell have nothing to do.  (Narrow pieces stay in
+// rows, and so do those that share no cell; the rule is where the order is made.)  The waves need
 // nothing of each other: each adds up its own spreads, over the levels in
 // order (or every split-th of them, see dd4dvar_ctx::jc_split).  FP32, 64
 // pieces of 512 x 1024 in 4 intervals of 33 levels: 712 us in rows with a
@@ -136,7 +137,8 @@ __global__ __launch_bounds__(kTile) void k_targets_from_local(Dom<T> D, int leve
   // the wave's cells in the exchange's order
   const int e = wt.y * kTile + threadIdx.x;
   const bool valid = e < S.ncell;
-  const int m = D.perm[S.perm0 + (valid ? e : 0)];
+  int m = valid ? e : 0;
+  if (S.perm0 >= 0) m = D.perm[S.perm0 + m];   // (uniform; else in rows)
   const int cov = valid ? int(D.cover[S.cell_off + m]) : 0;
   // where the wave's sum of these levels goes
   double* J = jc + (int64_t(w) * kWaves + (threadIdx.x >> 6)) * split + n0 % split;
