@@ -160,15 +160,15 @@ def gn_product_bytes(ctx, prec_bytes, persistent=False):
 # digest of the kernel sources they were measured on: a changed kernel (or
 # another workload) reports null until it is measured again.
 MEASURED_TRAFFIC = {
-    "k_adj": ("sweep", "6726b376c5c0b2b0", 1158231111),
-    "k_adj_box/10": ("box", "944e0e1d3817a1f9", 16095286936),
-    "k_adj_box/11": ("box", "944e0e1d3817a1f9", 16091958256),
-    "k_adj_strip/11": ("box", "944e0e1d3817a1f9", 16651997525),
-    "k_eval_box/10": ("box", "944e0e1d3817a1f9", 29702395272),
+    "k_adj": ("sweep", "9ccf82aa8638b8a5", 1158232920),
+    "k_adj_box/10": ("box", "a9f4f6c01ff50f4c", 16094088040),
+    "k_adj_box/11": ("box", "a9f4f6c01ff50f4c", 16088683296),
+    "k_adj_strip/11": ("box", "a9f4f6c01ff50f4c", 16656724481),
+    "k_eval_box/10": ("box", "a9f4f6c01ff50f4c", 29703942392),
     # Gauss-Newton normal-matrix product: tangent-linear sweep (10 passes)
     # and the adjoint with the Gauss-Newton forcing (column strips, 11 rows)
-    "k_tlm_box/10": ("box", "944e0e1d3817a1f9", 16807531786),
-    "k_adj_strip_gn/11": ("box", "944e0e1d3817a1f9", 15639372757),
+    "k_tlm_box/10": ("box", "a9f4f6c01ff50f4c", 16797295040),
+    "k_adj_strip_gn/11": ("box", "a9f4f6c01ff50f4c", 15643761464),
 }
 KERNEL_SOURCES = {"sweep": ("sweep.hip", "kernels.h", "stencil.h"),
                   "box": ("box.hip", "kernels.h", "stencil.h")}

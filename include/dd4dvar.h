@@ -302,8 +302,8 @@ dd4dvar_status dd4dvar_gather(dd4dvar_ctx* ctx, int32_t level, double* out_dev,
  * adjoint_integrate launch their kernels:
  *   0 = all subdomains in every launch (default): step kernels, one launch
  *       per time step; in an FP64 context of the plain scheme with every
- *       level stored, where they are faster, block sweeps of the same
- *       results that take several steps, up to the whole window, per launch
+ *       level stored, sweep by sweep where they are faster, block sweeps of
+ *       the same results that take several steps, up to the whole window, per launch
  *       (get_block_sweeps tells which, get_timing counts the launches);
  *   1 = one launch per subdomain per step (the plain baseline);
  *   2 = persistent sweeps: one workgroup per subdomain holds the current

@@ -507,8 +507,7 @@ __global__ __launch_bounds__(NT) void k_tlm_blk(Dom<double> D, const BlkWork* __
     prev[p] = n0 > 0 ? ld_box(dz + int64_t(n0 - 1) * 3 * plane, plane, m, 1.0) : get(fr, F.pos(r, c));
     if (TWO && m == cb + p * NT) put(fo, F.pos(r, c), prev[p]);
   }
-  // the state's loads of a pass are issued one pass ahead, the first pass's
-  // before the level before it is finished
+  // the state's loads of a pass, issued together at its start
   auto issue = [&](State5<SPAN>& q, int p, int n, const Range& g) {
     const int m = here(cb) + p * NT;
     const int chunk = __builtin_amdgcn_readfirstlane(m & ~63);
@@ -661,10 +660,9 @@ __device__ __forceinline__ void adj_blk(const Dom<double>& D, const BlkWork& w, 
   if ((MODE == 0 || MODE == 2) && !begin && t < ntile) jt = *jp;
   __syncthreads();
 
-  // a pass's loads: the state around the cell, the overlap target (mode 3: the
-  // perturbation; mode 1: the caller's forcing), the tile's observations; they
-  // are issued one pass ahead, the first pass's before the level before it
-  // is finished
+  // a pass's loads, issued together at its start: the state around the cell, the
+  // overlap target (mode 3: the perturbation; mode 1: the caller's forcing), the
+  // tile's observations
   struct Pass {
     State5<SPAN> q;
     V3<double> f;
@@ -1006,10 +1004,11 @@ int blk_faster(double most, int steps, bool whole, double cells) {
 // fits or the step kernels are faster.  Measured (both sweeps, one block to a
 // compute unit): a level takes 3.9 us for 570 cells and 9.4 us for 2350, 10 us
 // per launch besides; memory moves 4 TB/s under these kernels; the step kernels
-// are taken at 4.5 and 6.5 us per level, or 72 + 111 B per cell at 4.4 TB/s.  More
-// blocks than boxes spread few boxes over the chip (64 boxes of 40 x 72 cells: 64
-// whole ones 430 us per evaluation, 256 blocks of 7 levels 301 us, 480 of 5 454
-// us), at the price of the rows that two blocks compute both.
+// are taken at 4.5 and 6.5 us per level (3.5 and 5.2 on the smallest problems:
+// blk_faster has the last word), or 72 + 111 B per cell at 4.4 TB/s.  More blocks
+// than boxes spread few boxes over the chip (64 boxes of 40 x 72 cells: 64 whole
+// ones 430 us per evaluation, 256 blocks of 7 levels 301 us, 480 of 5 454 us), at the
+// price of the rows that two blocks compute both.
 BlkPlan plan_blocks(const std::vector<SubDev>& subs, int maxlev, int cus) {
   double cells = 0.0;
   for (const SubDev& S : subs) cells += S.ncell;

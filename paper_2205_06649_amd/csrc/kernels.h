@@ -46,7 +46,7 @@ struct SubDev {
   int32_t span, pole_s, pole_n;
   int32_t ncell, nring, tile0, ntile;
   int32_t nbr0, nbr1;        // neighbour list range
-  int32_t perm0;             // first entry of the box's piece in Dom::perm
+  int32_t perm0;             // first entry of the box's piece in Dom::perm, -1: its cells in rows
   int64_t traj_off;          // packed FP64 trajectory and overlap-target offset
   int64_t ring_off;          // ring arena offset, level stride 3*nring
   int64_t adj_off;           // adjoint arena offset: 3 slots x 3 x ncell

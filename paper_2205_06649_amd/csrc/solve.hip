@@ -345,7 +345,7 @@ __global__ __launch_bounds__(64 * kBoxWaves) void k_lb_step_s(LbState L) {
 // the pair, the move and a rejected step's next trial.  The direction sits in
 // registers (16 entries per thread) and every dot product stays in the
 // workgroup: 2 launches per iteration and round instead of 2 m + 5 and 4, whose
-// gaps and starts were the time (64 boxes of 8640 entries, m = 8: direction
+// gaps and starts were the time (32 boxes of 8640 entries, m = 8: direction
 // and trial 20 launches, 270 us with their gaps, -> 1; Armijo round 36 us with
 // its gaps).
 // A thread's loads of a vector are issued together (entries past the box's own
