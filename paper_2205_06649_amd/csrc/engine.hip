@@ -913,12 +913,13 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
     };
     std::vector<Run> band, rest;
     std::vector<uint64_t> in_row, in_col;
+    std::vector<int> cols;
     for (int i = 0; i < P.nspace; ++i) {
       const BoxInfo& b = P.boxes[i];
-      const int32_t* cov = P.cover_box.data() + P.cell_ptr[i];
+      bool in_rows = true;                             // (needs no index)
       in_row.assign(b.ny, 0);
       in_col.assign(b.nx, 0);
-      for (int64_t q = P.nbr_ptr[i]; q < P.nbr_ptr[i + 1]; ++q) {
+      for (int64_t q = P.nbr_ptr[i]; b.nx >= kRowsMin && q < P.nbr_ptr[i + 1]; ++q) {
         if (P.nbr_idx[q] >= P.nspace) break;          // (sorted: the first interval's boxes come first)
         const BoxInfo& o = P.boxes[P.nbr_idx[q]];
         const uint64_t bit = uint64_t(1) << (q - P.nbr_ptr[i]);
@@ -928,17 +929,21 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
       }
       band.clear();
       rest.clear();
-      for (int r = 0, e = 0; r < b.ny; ++r)
-        for (int c = 0; c < b.nx; ++c, ++e) {
-          const bool covered = cov[e] > 1 && b.nx >= kRowsMin;
-          const uint64_t set = covered ? in_row[r] & in_col[c] : 0;
-          std::vector<Run>& to = covered ? band : rest;
-          if (c > 0 && !to.empty() && to.back().e1 == e && to.back().set == set) to.back().e1 = e + 1;
-          else to.push_back({set, e, e + 1});
+      cols.clear();                                  // columns of one set, up to the next
+      for (int c = 0; c < b.nx; ++c)
+        if (c == 0 || in_col[c] != in_col[c - 1]) cols.push_back(c);
+      cols.push_back(b.nx);
+      for (int r = 0, e = 0; r < b.ny; ++r, e += b.nx)
+        for (size_t k = 0; k + 1 < cols.size(); ++k) {
+          const uint64_t set = in_row[r] & in_col[cols[k]];
+          std::vector<Run>& to = set ? band : rest;
+          if (k > 0 && !to.empty() && to.back().e1 == e + cols[k] && to.back().set == set)
+            to.back().e1 = e + cols[k + 1];
+          else
+            to.push_back({set, e + cols[k], e + cols[k + 1]});
         }
       std::sort(band.begin(), band.end());
       int32_t* out = perm.data() + P.cell_ptr[i];
-      bool in_rows = true;
       int32_t next = 0;
       for (const auto* runs : {&band, &rest})
         for (const Run& q : *runs) {
@@ -946,7 +951,6 @@ void build_device(dd4dvar_ctx* c, hipStream_t st) {
           for (int32_t e = q.e0; e < q.e1; ++e) *out++ = e;
           next = q.e1;
         }
-      // pieces that stay in rows need no index
       for (int s = i; in_rows && s < P.nsub; s += P.nspace) c->subs[s].perm0 = -1;
     }
   }
