@@ -694,9 +694,8 @@ def cpu_baseline(spec, budget_s=20.0):
     single = pts / t_total
     log(f"cpu baseline: one process {single:.3e} local point-steps/s ({done} evaluations)")
     # a pool of forked processes over the subdomains of the sample, taken in
-    # turn (again from the first when the sample is exhausted); the GPU machine
-    # allots 16 host cores to its one GPU, whatever os.cpu_count() shows, so
-    # the pool has at most 16 workers
+    # turn (again from the first when the sample is exhausted), at most 16 of
+    # them, a GPU's share of its host's cores, whatever os.cpu_count() shows
     ncores = max(1, min(16, os.cpu_count() or 1))
     per_eval = t_total / done
     nwork = int(max(ncores, ncores * round(budget_s / 2 / per_eval))) if ncores > 1 else 0
